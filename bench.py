@@ -51,7 +51,9 @@ HBM_PEAK_GBS = 8000.0
 BYTES_PER_UPDATE = {"int8": 2.0, "bitpack": 0.25}   # each spin read and written once per sweep
 PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "traffic_sweep_kernel_160x480x600x3.md")
 PROFILE_VALU = os.path.join(ROOT, "profiles", "valu_sweep_kernel_160x480x600x3.md")
-KERNEL_SOURCE = os.path.join(ROOT, "paper_1411_5588_amd", "csrc", "islf_kernels.hip")
+_CSRC = os.path.join(ROOT, "paper_1411_5588_amd", "csrc")
+KERNEL_SOURCE = os.path.join(_CSRC, "islf_device.h")
+MORE_KERNEL_SOURCES = [os.path.join(_CSRC, f) for f in ("islf_internal.h", "islf_kernels.hip", "islf_resident.hip")]
 
 
 def parse():
@@ -240,11 +242,12 @@ def kernel_code_hash():
     lines removed: edits to comments leave it, and the counters it guards,
     unchanged (the source has no block comments and no "//" in strings)."""
     lines = []
-    with open(KERNEL_SOURCE, encoding="utf-8") as f:
-        for ln in f:
-            ln = ln.split("//", 1)[0].rstrip()
-            if ln:
-                lines.append(ln)
+    for path in (KERNEL_SOURCE, *MORE_KERNEL_SOURCES):
+        with open(path, encoding="utf-8") as f:
+            for ln in f:
+                ln = ln.split("//", 1)[0].rstrip()
+                if ln:
+                    lines.append(ln)
     return hashlib.sha256("\n".join(lines).encode()).hexdigest()[:16]
 
 

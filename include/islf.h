@@ -72,7 +72,12 @@ typedef enum { ISLF_INIT_RANDOM = 0, ISLF_INIT_UP = 1, ISLF_INIT_DOWN = 2, ISLF_
  *               replica group (islf_set_groups); the groups' launch chains
  *               run side by side on their own streams.
  *  PERSISTENT : one launch for all requested sweeps of every replica, with
- *               device-side grid barriers in place of the launch boundaries. */
+ *               device-side grid barriers in place of the launch boundaries.
+ * Replicas whose spins fit the device's LDS (one bit per site, about 3e8
+ * sites) are swept there instead, in one launch of up to 256 sweeps for the
+ * whole batch (PLAIN: per replica), where that is expected to be faster and
+ * no launch configuration was chosen (islf_set_grid, islf_set_groups,
+ * islf_set_taper, islf_set_barriers, islf_set_tile). */
 typedef enum { ISLF_EXEC_PLAIN = 0, ISLF_EXEC_BATCHED = 1, ISLF_EXEC_PERSISTENT = 2 } islf_exec;
 
 /* One replica (Sec. II.A Eq. 1 parameters plus the Markov-chain identity).

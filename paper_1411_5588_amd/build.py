@@ -12,7 +12,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libislf.so")
-SOURCES = ["islf_kernels.hip", "islf_api.hip"]
+SOURCES = ["islf_kernels.hip", "islf_resident.hip", "islf_api.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -46,6 +46,11 @@ hipError_t launch_means(const RepDesc *descs, const int *reps, int n, uint64_t f
 hipError_t launch_integrate(const double *h, const double *m1, const double *mn, int n, double c1, double cn,
                             double norm, double *out, hipStream_t s);
 hipError_t noalloc_scratch(double **out);
+hipError_t resident_lds_limit(int fmt, size_t bytes);
+hipError_t launch_resident(int fmt, bool small, const RepDesc *descs, RepState *st, const ResJob *jobs,
+                           const int *first, const ResRep *reps, int grid, int njobs, int members, int nreps,
+                           size_t lds, uint32_t n, ResSync *rs, GridSync *sync, int4 *part, unsigned long long *mbox,
+                           int check_error, hipStream_t s);
 }  // namespace islf
 
 using namespace islf;
@@ -204,6 +209,7 @@ struct Replica {
     uint64_t t_host = 0;     // sweeps issued so far
     bool failed = false;     // its chain was cut short by a failed persistent launch
     int tile = 0;
+    bool tile_set = false;   // chosen by islf_set_tile
     RepDesc d{};
     std::vector<Entry> main, slab;
 };
@@ -217,6 +223,25 @@ struct Plan {
     long items_cap = 0, first_cap = 0;
     int grid = 0, slab_grid = 0;
     bool valid = false;
+};
+
+// A launch of the resident form over some replicas: shares (jobs) by
+// workgroup, cluster workgroups first, with their mailboxes and per-sweep sums.
+struct ResPlan {
+    bool valid = false;    // built for the current replicas
+    bool usable = false;   // they fit and the form is expected to be the faster one
+    ResJob *jobs = nullptr;
+    int *first = nullptr;
+    ResRep *reps = nullptr;
+    int4 *part = nullptr;
+    std::vector<int4 *> outgrown;   // smaller `part` buffers that captured graphs may still use
+    unsigned long long *mbox = nullptr;
+    size_t jobs_b = 0, first_b = 0, reps_b = 0, part_b = 0, mbox_b = 0;   // bytes allocated
+    int grid = 0, njobs = 0, members = 0, nreps = 0;
+    bool small = false;    // no clusters and few words per film: one lane per four-site group
+    size_t lds = 0;
+    uint32_t max_sweeps = 0;
+    double sweep_us = 0.0, fixed_us = 0.0, chain_us = 0.0;   // expected: per sweep, per launch; a sweep of the launch chain
 };
 
 struct islf_ctx {
@@ -254,6 +279,9 @@ struct islf_ctx {
     int live_capacity = 0;
     Plan batched, persistent;
     std::vector<Plan> plain;                    // per slot
+    ResPlan resident;                           // all live replicas (batched and persistent forms)
+    std::vector<ResPlan> resident_plain;        // per slot (plain form)
+    ResSync *d_rsy = nullptr;
     // batched form with concurrent replica groups: group g sweeps its
     // replicas on side_stream[g], a stream the context creates; the
     // context's stream only forks them and joins them
@@ -642,6 +670,8 @@ static islf_status sync_tables(islf_ctx *c)
     c->persistent.valid = false;
     for (Plan &p : c->plain) p.valid = false;
     c->groups_valid = false;
+    c->resident.valid = false;
+    for (ResPlan &p : c->resident_plain) p.valid = false;
     c->dirty = false;
     c->graph_valid = false;
     return ISLF_OK;
@@ -856,6 +886,405 @@ static islf_status prepare_plans(islf_ctx *c, int exec)
     return ISLF_OK;
 }
 
+
+// ---------------------------------------------------------------------------
+// Resident form: shares, plan and choice
+// ---------------------------------------------------------------------------
+static void free_resident(islf_ctx *c, ResPlan &p)
+{
+    dev_free(c, p.jobs);
+    dev_free(c, p.first);
+    dev_free(c, p.reps);
+    dev_free(c, p.part);
+    for (int4 *o : p.outgrown) dev_free(c, o);
+    dev_free(c, p.mbox);
+    p = ResPlan();
+}
+
+constexpr size_t kLatticeLds = 160 * 1024 - kResStaticLds;   // of a gfx950 CU's LDS
+
+// Expected times (us) of the resident kernel: a chunk of 64 whole words on
+// one SIMD, the latency of a lone chunk, a partial word's four-site group,
+// the exchange of a phase, a workgroup barrier.
+constexpr double kChunkUs = 0.95, kLoneUs = 1.3, kGroupUs = 0.125, kExchangeUs = 2.0, kStageUs = 0.5;
+// Films of at most this many four-site groups per phase are updated by one
+// lane per group when no film of the launch needs a cluster.
+constexpr long kSmallGroups = (long)kSmallTasks * kResThreads;
+
+struct ShareCost {
+    const islf_replica_desc &d;
+    int Wq, Wf, ng;
+    explicit ShareCost(const islf_replica_desc &d_) : d(d_)
+    {
+        const int nbits = d.Lz / 2;
+        Wq = (nbits + 31) / 32;
+        Wf = nbits / 32;
+        ng = (nbits % 32 + 3) / 4;
+    }
+    size_t lds(int rows) const
+    {
+        return 4 * (size_t)(d.Lx + 2) * (size_t)(rows + 2) * 2 * (size_t)Wq;
+    }
+    double phase(long rows) const
+    {
+        const long full = ceil_div((long)d.Lx * rows * Wf, 64), part = ng ? ceil_div((long)d.Lx * rows, 64) : 0;
+        const double busy = (full * kChunkUs + part * ng * kGroupUs) / 4.0;
+        const double lone = std::max(full ? kLoneUs : 0.0, part ? 0.3 + 0.15 * ng : 0.0);
+        return std::max(busy, lone);
+    }
+    // a sweep of a share of `rows` rows
+    double sweep(long rows, bool row0, bool cluster) const
+    {
+        double t = 2.0 * (phase(row0 ? rows - 1 : rows) + (cluster ? kExchangeUs : 0.0) + kStageUs);
+        if (row0) t += 2.0 * (phase(1) + kStageUs);
+        return t;
+    }
+    // rows of share 0 (Ly-1, 0, 1 at least) and the most rows of the others
+    // when P >= 2 shares split the film; false if there are too few rows
+    bool split(int P, int &rows0, int &r) const
+    {
+        if (P < 2 || d.Ly < P + 2) return false;
+        // row 0's two stages cost share 0 as much as `extra` rows
+        const double row_us = std::max(1e-3, (2.0 * phase(64)) / 64.0);
+        const int extra = (int)(2.0 * (phase(1) + kStageUs) / row_us);
+        rows0 = std::max(3, d.Ly - (P - 1) * (int)ceil_div((long)d.Ly + extra, P));
+        r = (int)ceil_div((long)d.Ly - rows0, P - 1);
+        return true;
+    }
+    // expected sweep time with P shares, < 0 if they do not fit
+    double time(int P) const
+    {
+        if (P == 1) return lds(d.Ly) <= kLatticeLds ? sweep(d.Ly, true, false) : -1.0;
+        int rows0, r;
+        if (!split(P, rows0, r) || lds(std::max(rows0, r)) > kLatticeLds) return -1.0;
+        return std::max(sweep(rows0, true, true), sweep(r, false, true));
+    }
+};
+
+static uint32_t magic_of(int d) { return d >= 2 ? (uint32_t)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d) : 0u; }
+
+// A sweep of the launch chain, measured: one chain takes 20 us a sweep in
+// launches whose work does not overlap (19.5 us per launch of a 46 M-site
+// bit-packed film), concurrent groups hide all but a few us of that on large
+// replicas (3 x 160x480x600: 62 us bit-packed, 95 us int8) and less on many
+// small ones (64 x 40x120x120: 31 us bit-packed).
+static double chain_sweep_us(const islf_ctx *c, long long sites, int nreps)
+{
+    const double work = (double)sites / (c->fmt == ISLF_SPIN_BITPACK ? 2.45e6 : 1.53e6);
+    if (c->exec != ISLF_EXEC_BATCHED || nreps == 1) return std::max(14.0, 20.0 + work);
+    return std::max(20.0, 5.0 + 0.15 * nreps + work);
+}
+
+// Shares of the listed replicas for one launch of at most num_cu workgroups
+// (one per CU: the kernel's registers allow no second one).  Replicas that
+// need several workgroups get a share each on workgroups of their own, the
+// single-workgroup ones then go, largest first, to the workgroup with the
+// least work (they wait for nobody, so a workgroup may hold several).  The
+// target time per sweep that sets the shares is scanned for the shortest
+// launch.  Returns false if the replicas do not fit.
+static bool plan_resident(const islf_ctx *c, const std::vector<int> &reps, std::vector<ResJob> &jobs,
+                          std::vector<int> &first, std::vector<ResRep> &rr, ResPlan &p, size_t &mbox_words)
+{
+    const int n = (int)reps.size(), NW = c->num_cu;
+    std::vector<ShareCost> cost;
+    double total = 0.0;
+    for (int r : reps) {
+        cost.emplace_back(c->reps[r].desc);
+        const ShareCost &k = cost.back();
+        total += 2.0 * k.phase(k.d.Ly);
+    }
+    std::vector<int> P(n), bestP;
+    std::vector<double> tr(n);
+    double best = 1e300;
+    auto pack = [&](std::vector<int> *where) -> double {
+        // cluster workgroups first, then singles by LPT; returns the longest workgroup
+        std::vector<std::pair<double, int>> heap;   // (-load, workgroup)
+        double longest = 0.0;
+        int w = 0;
+        std::vector<int> single;
+        for (int i = 0; i < n; ++i) {
+            if (P[i] == 1) {
+                single.push_back(i);
+                continue;
+            }
+            for (int k = 0; k < P[i]; ++k) heap.push_back({-tr[i], w++});
+            longest = std::max(longest, tr[i]);
+        }
+        for (; w < NW; ++w) heap.push_back({0.0, w});
+        std::make_heap(heap.begin(), heap.end());
+        std::stable_sort(single.begin(), single.end(), [&](int a, int b) { return tr[a] > tr[b]; });
+        for (int i : single) {
+            std::pop_heap(heap.begin(), heap.end());
+            heap.back().first -= tr[i];
+            longest = std::max(longest, -heap.back().first);
+            if (where) (*where)[i] = heap.back().second;
+            std::push_heap(heap.begin(), heap.end());
+        }
+        return longest;
+    };
+    const double t0 = std::max(3.0, 0.7 * total / NW);
+    for (int step = 0; step < 48; ++step) {
+        const double T = t0 * pow(1.07, step);
+        long used = 0;
+        bool ok = true;
+        for (int i = 0; i < n && ok; ++i) {
+            int k = 1;
+            double t = cost[i].time(1);
+            if (t < 0 || t > T) {
+                // the fewest shares within T, else those with the shortest time
+                int bk = 0;
+                double bt = 1e300;
+                const int cap = std::min(NW, std::max(1, c->reps[reps[i]].desc.Ly - 2));
+                for (k = std::max(2, (int)(0.5 * 2.0 * cost[i].phase(cost[i].d.Ly) / T)); k <= cap; ++k) {
+                    const double tk = cost[i].time(k);
+                    if (tk < 0) continue;
+                    if (tk < bt) {
+                        bt = tk;
+                        bk = k;
+                    }
+                    if (tk <= T) break;
+                }
+                if (t >= 0 && (bk == 0 || t <= bt)) bk = 1;
+                else t = bt;
+                if (bk == 0) ok = false;
+                k = bk;
+            }
+            P[i] = k;
+            tr[i] = t;
+            if (k > 1) used += k;
+            if (used > NW) ok = false;
+        }
+        if (!ok) continue;
+        const double m = pack(nullptr);
+        if (m < best) {
+            best = m;
+            bestP = P;
+        }
+        if (m < T) break;
+    }
+    if (bestP.empty()) return false;
+    P = bestP;
+    for (int i = 0; i < n; ++i) tr[i] = cost[i].time(P[i]);
+    std::vector<int> where(n, -1);
+    p.sweep_us = pack(&where);
+    p.small = true;
+    for (int i = 0; i < n; ++i) {
+        const islf_replica_desc &d = cost[i].d;
+        const long row = (long)d.Lx * ((d.Lz + 7) / 8);   // groups of a row
+        p.small = p.small && P[i] == 1 && row <= kResThreads && row * (d.Ly - 1) <= kSmallGroups;
+    }
+    // jobs by workgroup
+    std::vector<std::vector<ResJob>> wg(NW);
+    p.members = 0;
+    p.lds = 0;
+    mbox_words = 0;
+    rr.clear();
+    int id = 0;
+    for (int i = 0; i < n; ++i) {
+        const ShareCost &k = cost[i];
+        rr.push_back(ResRep{reps[i], id, P[i], 0});
+        const islf_replica_desc &d = k.d;
+        const size_t box = (size_t)d.Lx * k.Wq;   // words of one mailbox slot
+        int rows0 = d.Ly, r = 0;
+        if (P[i] > 1) k.split(P[i], rows0, r);
+        const int before = P[i] > 1 ? rows0 / 2 : 0;   // share 0's rows below row 0
+        int y = P[i] > 1 ? rows0 - before : 0;          // first row of the next share
+        long left = d.Ly - rows0;
+        for (int q = 0; q < P[i]; ++q) {
+            ResJob j{};
+            j.rep = reps[i];
+            j.id = id++;
+            j.P = P[i];
+            j.p = q;
+            if (q == 0) {
+                j.R = rows0;
+                j.y0 = P[i] > 1 ? d.Ly - before : 0;
+                j.lr0 = P[i] > 1 ? before + 1 : 1;
+                j.ls = P[i] > 1 ? before : d.Ly;
+            } else {
+                j.R = (int)ceil_div(left, P[i] - q);
+                j.y0 = y;
+                y += j.R;
+                left -= j.R;
+            }
+            const bool cl = P[i] > 1;
+            auto rows = [](int base, int stride, int skip, int cnt, bool seam) {
+                return ResRows{base, stride, skip, std::max(0, cnt), magic_of(std::max(0, cnt)), seam ? 1 : 0};
+            };
+            if (cl) j.set[RES_EDGE] = rows(1, std::max(1, j.R - 1), 0, j.R == 1 ? 1 : 2, j.ls == 1);
+            if (j.lr0 == 0) {
+                j.set[RES_INNER] = rows(2, 1, 0, j.R - 2, false);
+            } else if (!cl) {
+                // row y = 0 first, y = Ly-1 last
+                j.set[RES_INNER] = p.small ? rows(2, 1, 0, j.R - 1, true) : rows(2, 1, 0, j.R - 2, false);
+                if (!p.small) j.set[RES_LAST] = rows(j.ls, 1, 0, 1, true);
+            } else if (j.ls == 1) {
+                j.set[RES_INNER] = rows(3, 1, 0, j.R - 3, false);
+            } else {
+                j.set[RES_INNER] = rows(2, 1, j.ls, j.R - 4, false);
+                j.set[RES_LAST] = rows(j.ls, 1, 0, 1, true);
+            }
+            if (j.lr0) j.set[RES_ROW0] = rows(j.lr0, 1, 0, 1, true);
+            j.Wf = k.Wf;
+            j.ng = k.ng;
+            j.m_w = magic_of(j.Wf);
+            j.m_c = magic_of((d.Lz + 7) / 8);
+            if (cl) {
+                auto inbox = [&](int s, int face) {
+                    const int t = (s + P[i]) % P[i];
+                    return (uint32_t)(mbox_words + ((size_t)t * 4 + 2 * (size_t)face) * box);
+                };
+                for (int f = 0; f < 2; ++f) j.in_off[f] = inbox(q, f);
+                j.out_off[0] = inbox(q - 1, 1);
+                j.out_off[1] = inbox(q + 1, 0);
+                wg[p.members++].push_back(j);
+            } else {
+                wg[where[i]].push_back(j);
+            }
+            p.lds = std::max(p.lds, k.lds(j.R));
+        }
+        if (P[i] > 1) mbox_words += (size_t)P[i] * 4 * box;
+    }
+    if (mbox_words >= (1ull << 32)) return false;
+    jobs.clear();
+    first.assign(1, 0);
+    for (int w = 0; w < NW; ++w) {
+        if (wg[w].empty()) continue;
+        jobs.insert(jobs.end(), wg[w].begin(), wg[w].end());
+        first.push_back((int)jobs.size());
+    }
+    p.grid = (int)first.size() - 1;
+    p.njobs = (int)jobs.size();
+    p.nreps = n;
+    return true;
+}
+
+// Grows a device buffer of the plan to `bytes`.
+template <class T>
+static bool grow(islf_ctx *c, T *&ptr, size_t &have, size_t bytes)
+{
+    if (bytes <= have) return true;
+    dev_free(c, ptr);
+    have = 0;
+    ptr = (T *)dev_alloc(c, bytes);
+    if (ptr) have = bytes;
+    return ptr != nullptr;
+}
+
+// Builds the resident plan of some replicas (synchronises).  A plan that
+// cannot be had (too large, no memory) is valid but not usable.
+static islf_status build_resident(islf_ctx *c, ResPlan &p, const std::vector<int> &reps)
+{
+    p.valid = true;
+    p.usable = false;
+    for (int4 *o : p.outgrown) dev_free(c, o);
+    p.outgrown.clear();
+    std::vector<ResJob> jobs;
+    std::vector<int> first;
+    std::vector<ResRep> rr;
+    size_t mbox_words = 0;
+    if (reps.empty() || !plan_resident(c, reps, jobs, first, rr, p, mbox_words)) return ISLF_OK;
+    long long sites = 0;
+    size_t bytes = 0;
+    for (int r : reps) {
+        const islf_replica_desc &d = c->reps[r].desc;
+        sites += (long long)d.Lx * d.Ly * d.Lz;
+        bytes += spin_bytes(&d, c->fmt);
+    }
+    p.chain_us = chain_sweep_us(c, sites, (int)reps.size());
+    p.fixed_us = 16.0 + 2.0 * (double)bytes / 2.0e6;
+    if (p.sweep_us >= p.chain_us) return ISLF_OK;
+    // per-sweep sums: 8 MiB at most (allocated by the longest run, see size_sums)
+    p.max_sweeps = (uint32_t)std::max<size_t>(1, std::min<size_t>(kResMaxSweeps, (8u << 20) / (16 * (size_t)p.njobs)));
+    if (!grow(c, p.jobs, p.jobs_b, sizeof(ResJob) * jobs.size()) ||
+        !grow(c, p.first, p.first_b, sizeof(int) * first.size()) ||
+        !grow(c, p.reps, p.reps_b, sizeof(ResRep) * rr.size()) ||
+        !grow(c, p.mbox, p.mbox_b, 8 * std::max<size_t>(1, mbox_words)))
+        return ISLF_OK;
+    HIP_TRY(resident_lds_limit(c->fmt, kLatticeLds));
+    HIP_TRY(hipMemcpyAsync(p.jobs, jobs.data(), sizeof(ResJob) * jobs.size(), hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(hipMemcpyAsync(p.first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(hipMemcpyAsync(p.reps, rr.data(), sizeof(ResRep) * rr.size(), hipMemcpyHostToDevice, c->stream));
+    // no mailbox word may carry an epoch still to come
+    HIP_TRY(launch_zero(p.mbox, (long)mbox_words, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    p.usable = true;
+    return ISLF_OK;
+}
+
+// Room for the per-sweep sums of a run of n sweeps.
+static bool size_sums(islf_ctx *c, ResPlan &p, uint32_t n)
+{
+    const size_t bytes = sizeof(int4) * std::min(n, p.max_sweeps) * (size_t)p.njobs;
+    if (bytes <= p.part_b) return true;
+    int4 *np = (int4 *)dev_alloc(c, bytes);
+    if (!np) return false;
+    if (p.part) p.outgrown.push_back(p.part);
+    p.part = np;
+    p.part_b = bytes;
+    return true;
+}
+
+// Whether a run of n sweeps takes the resident form (its plans are then
+// built).  A launch configuration chosen by the caller (grid, groups, taper,
+// barriers, a tile) asks for the launch chain or the persistent kernel.
+static islf_status resident_applies(islf_ctx *c, uint32_t n, bool *use)
+{
+    *use = false;
+    islf_status st = sync_tables(c);
+    if (st != ISLF_OK) return st;
+    if (n == 0 || c->live.empty()) return ISLF_OK;
+    if (c->grid_override || c->groups_req || c->taper_override >= 0.0 || c->team_mode >= 0) return ISLF_OK;
+    for (int r : c->live)
+        if (c->reps[r].tile_set) return ISLF_OK;
+    double res = 0.0, chain = 0.0;
+    auto add = [&](ResPlan &p, const std::vector<int> &reps) -> islf_status {
+        if (!p.valid) {
+            islf_status s = build_resident(c, p, reps);
+            if (s != ISLF_OK) return s;
+        }
+        res += p.usable ? p.fixed_us * (double)((n + p.max_sweeps - 1) / p.max_sweeps) + n * p.sweep_us : 1e300;
+        chain += 8.0 + n * p.chain_us;
+        return ISLF_OK;
+    };
+    if (c->exec == ISLF_EXEC_PLAIN) {
+        if (c->resident_plain.size() < c->reps.size()) c->resident_plain.resize(c->reps.size());
+        for (int r : c->live) {
+            st = add(c->resident_plain[r], std::vector<int>(1, r));
+            if (st != ISLF_OK) return st;
+        }
+    } else {
+        st = add(c->resident, c->live);
+        if (st != ISLF_OK) return st;
+    }
+    *use = res < chain;
+    // without room for the sums the launch chain does it
+    if (c->exec == ISLF_EXEC_PLAIN)
+        for (size_t i = 0; i < c->live.size() && *use; ++i) *use = size_sums(c, c->resident_plain[c->live[i]], n);
+    else if (*use) *use = size_sums(c, c->resident, n);
+    return ISLF_OK;
+}
+
+// Enqueues n sweeps in the resident form (plans built, no checks, no sync).
+static hipError_t enqueue_resident(islf_ctx *c, uint32_t n)
+{
+    const int check = c->exec == ISLF_EXEC_PERSISTENT;
+    auto run = [&](const ResPlan &p) -> hipError_t {
+        hipError_t e = hipSuccess;
+        for (uint32_t done = 0; done < n && e == hipSuccess;) {
+            const uint32_t k = std::min(n - done, p.max_sweeps);
+            e = launch_resident(c->fmt, p.small, c->d_desc, c->d_state, p.jobs, p.first, p.reps, p.grid, p.njobs, p.members,
+                                p.nreps, p.lds, k, c->d_rsy, c->d_sync, p.part, p.mbox, check, c->stream);
+            done += k;
+        }
+        return e;
+    };
+    if (c->exec != ISLF_EXEC_PLAIN) return run(c->resident);
+    hipError_t e = hipSuccess;
+    for (size_t i = 0; i < c->live.size() && e == hipSuccess; ++i) e = run(c->resident_plain[c->live[i]]);
+    return e;
+}
+
 // init spins + initial observables of slot i (synchronises)
 static islf_status init_replica(islf_ctx *c, int i, int mode, const int8_t *host_staged)
 {
@@ -906,6 +1335,7 @@ static islf_status add_replica(islf_ctx *c, const islf_replica_desc *desc, int *
         R.mem_bytes = bytes;
     }
     R.tile = default_tile(desc, c->fmt);
+    R.tile_set = false;
     fill_desc(R, c->fmt, c->cap);
     build_work(R, slot, c->fmt);
     const int mode = desc->init == ISLF_INIT_HOST ? ISLF_INIT_UP : desc->init;
@@ -935,6 +1365,9 @@ static void destroy_ctx(islf_ctx *c)
     dev_free(c, c->d_desc);
     dev_free(c, c->d_state);
     dev_free(c, c->d_sync);
+    dev_free(c, c->d_rsy);
+    free_resident(c, c->resident);
+    for (ResPlan &p : c->resident_plain) free_resident(c, p);
     dev_free(c, c->d_teams);
     dev_free(c, c->d_rsync);
     dev_free(c, c->d_scratch);
@@ -1026,11 +1459,13 @@ extern "C" islf_status islf_create_with_allocator(const islf_replica_desc *reps,
     }
     c->d_sync = (GridSync *)dev_alloc(c, sizeof(GridSync));
     c->d_scratch = (unsigned long long *)dev_alloc(c, 64 * sizeof(unsigned long long));
-    if (!c->d_sync || !c->d_scratch) {
+    c->d_rsy = (ResSync *)dev_alloc(c, sizeof(ResSync));
+    if (!c->d_sync || !c->d_scratch || !c->d_rsy) {
         destroy_ctx(c);
         return fail(ISLF_ENOMEM, "cannot allocate context buffers");
     }
-    if (launch_zero((unsigned long long *)c->d_sync, sizeof(GridSync) / 8, c->stream) != hipSuccess) {
+    if (launch_zero((unsigned long long *)c->d_sync, sizeof(GridSync) / 8, c->stream) != hipSuccess ||
+        launch_zero((unsigned long long *)c->d_rsy, sizeof(ResSync) / 8, c->stream) != hipSuccess) {
         destroy_ctx(c);
         return fail(ISLF_EDEVICE, "cannot clear sync words");
     }
@@ -1269,6 +1704,21 @@ static islf_status enqueue_sweeps(islf_ctx *c, uint32_t n)
     return ISLF_OK;
 }
 
+// The form a run of n sweeps takes, its plans built.
+static islf_status prepare_form(islf_ctx *c, uint32_t n, bool *resident)
+{
+    islf_status st = resident_applies(c, n, resident);
+    if (st != ISLF_OK || *resident) return st;
+    return prepare_plans(c, c->exec);
+}
+
+static islf_status enqueue_form(islf_ctx *c, uint32_t n, bool resident)
+{
+    if (!resident) return enqueue_sweeps(c, n);
+    HIP_TRY(enqueue_resident(c, n));
+    return ISLF_OK;
+}
+
 // Reads the persistent kernel's error word (synchronises).  A raised word
 // means a launch gave up at a grid barrier and left its sweeps half done, so
 // every live replica is marked failed (its calls return ESTATE until
@@ -1324,11 +1774,12 @@ extern "C" islf_status islf_sweep(islf_ctx *ctx, uint32_t n_sweeps)
     if (!ctx) return fail(ISLF_EINVAL, "NULL context");
     islf_status st = check_none_failed(ctx);
     if (st != ISLF_OK) return st;
-    st = prepare_plans(ctx, ctx->exec);
+    bool resident = false;
+    st = prepare_form(ctx, n_sweeps, &resident);
     if (st != ISLF_OK) return st;
     st = check_sweep_range(ctx, n_sweeps);
     if (st != ISLF_OK) return st;
-    st = enqueue_sweeps(ctx, n_sweeps);
+    st = enqueue_form(ctx, n_sweeps, resident);
     if (st != ISLF_OK) return st;
     for (int r : ctx->live) ctx->reps[r].t_host += n_sweeps;
     return ISLF_OK;
@@ -1660,21 +2111,22 @@ extern "C" islf_status islf_graph_capture(islf_ctx *ctx, uint32_t k_sweeps)
     if (!ctx->stream) return fail(ISLF_ESTATE, "graph capture needs a non-default stream");
     islf_status st = check_none_failed(ctx);
     if (st != ISLF_OK) return st;
-    st = prepare_plans(ctx, ctx->exec);
+    bool resident = false;
+    st = prepare_form(ctx, k_sweeps, &resident);
     if (st != ISLF_OK) return st;
     destroy_graphs(ctx);
     // concurrent groups: one graph per group, captured on the group's own
     // stream, so that replays run each group on a stream the context owns
     // (the streams a runtime picks for the branches of one multi-stream graph
     // may share a hardware queue and serialise the groups)
-    const bool grouped = ctx->exec == ISLF_EXEC_BATCHED && num_groups(ctx) > 1;
+    const bool grouped = !resident && ctx->exec == ISLF_EXEC_BATCHED && num_groups(ctx) > 1;
     const int G = grouped ? num_groups(ctx) : 1;
     for (int gi = 0; gi < G; ++gi) {
         hipStream_t sg = group_stream(ctx, gi, G);
         HIP_TRY(hipStreamBeginCapture(sg, hipStreamCaptureModeThreadLocal));
         hipError_t ee = hipSuccess;
         if (grouped) ee = enqueue_group(ctx, gi, k_sweeps);
-        else st = enqueue_sweeps(ctx, k_sweeps);
+        else st = enqueue_form(ctx, k_sweeps, resident);
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(sg, &g);
         if (st != ISLF_OK || ee != hipSuccess) {
@@ -1742,6 +2194,7 @@ extern "C" islf_status islf_set_tile(islf_ctx *ctx, int32_t rep, int32_t tile)
     if (tile < 0 || tile >= num_tiles_of(ctx->fmt)) return fail(ISLF_EINVAL, "tile %d out of range", tile);
     Replica &R = ctx->reps[rep];
     R.tile = tile;
+    R.tile_set = true;
     build_work(R, rep, ctx->fmt);
     ctx->dirty = true;
     return ISLF_OK;
@@ -1920,7 +2373,8 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
             ctx->groups_valid = false;
             ctx->batched.valid = false;
             ctx->persistent.valid = false;
-            islf_status rs = prepare_plans(ctx, ctx->exec);
+            bool resident = false;
+            islf_status rs = prepare_form(ctx, sweeps, &resident);
             if (rs != ISLF_OK) return rs;
             hipError_t e = hipSuccess;
             int G = 1;
@@ -1937,7 +2391,7 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
                         e = hipGraphLaunch(ctx->graph_execs[g], group_stream(ctx, g, G));
                     if (e == hipSuccess && G > 1) e = join_groups(ctx, G);
                 } else if (e == hipSuccess) {
-                    rs = enqueue_sweeps(ctx, run == 0 ? 1 : sweeps);
+                    rs = enqueue_form(ctx, run == 0 ? 1 : sweeps, resident);
                     if (rs != ISLF_OK) break;
                 }
                 if (run >= 1 && e == hipSuccess) {
@@ -2174,6 +2628,18 @@ extern "C" islf_status islf_testing_raise_barrier_error(islf_ctx *ctx)
     if (!ctx) return fail(ISLF_EINVAL, "NULL context");
     const unsigned long long one = 1;
     HIP_TRY(hipMemcpyAsync(&ctx->d_sync->error.v, &one, sizeof one, hipMemcpyHostToDevice, ctx->stream));
+    HIP_TRY(hipStreamSynchronize(ctx->stream));
+    return ISLF_OK;
+}
+
+// Test support, not part of the public header: puts the resident form's state
+// word to aborted, as a launch whose workgroups did not all become resident
+// would, so that the next launch's closing kernel sweeps its cluster replicas.
+extern "C" islf_status islf_testing_abort_resident(islf_ctx *ctx)
+{
+    if (!ctx) return fail(ISLF_EINVAL, "NULL context");
+    const unsigned int v = RES_ABORT;
+    HIP_TRY(hipMemcpyAsync(&ctx->d_rsy->state, &v, sizeof v, hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     return ISLF_OK;
 }

@@ -104,4 +104,55 @@ struct TeamInfo {
     int32_t pad_;
 };
 
+// ---------------------------------------------------------------------------
+// Resident form (islf_resident.hip): a launch keeps its replicas' spins in
+// LDS, one bit per site, for all of its sweeps.
+// ---------------------------------------------------------------------------
+constexpr int kResThreads = 1024;      // threads per workgroup: 4 waves per SIMD, one workgroup per CU
+constexpr int kResMaxSweeps = 256;     // sweeps one launch may run
+constexpr int kResStaticLds = 6784;    // LDS bytes beside the lattice: pair tables, thresholds, control words
+constexpr int kSmallTasks = 2;         // four-site groups a lane of the small form may hold per phase
+
+// A set of local rows base + i * stride, i = 0 .. n-1, with two rows left out
+// from row `skip` on (0: none).
+struct ResRows {
+    int32_t base, stride, skip, n;
+    uint32_t m;                   // ceil(2^32 / n), 0 for n = 1
+    int32_t seam;                 // holds row y = 0 or Ly-1
+};
+enum { RES_EDGE = 0, RES_LAST = 1, RES_INNER = 2, RES_ROW0 = 3 };
+
+// One workgroup's share of one replica: `R` consecutive rows of the y ring
+// (all x, all z) starting at row y0.  A replica's P shares form a cluster;
+// share 0 holds rows Ly-1, 0 and 1, so that the y seam and the phases of row
+// 0 stay inside one workgroup.  Local rows are 1 .. R, rows 0 and R+1 are
+// copies of the neighbouring shares' edge rows (unused when P = 1).
+struct ResJob {
+    int32_t rep, P, p;
+    int32_t id;                   // its slot in the per-sweep sums (a replica's shares are consecutive)
+    int32_t y0, R;
+    int32_t ls, lr0;              // local rows of y = Ly-1 and y = 0 (0: not in this share)
+    ResRows set[4];               // edge rows (updated first, sent to the neighbours), row Ly-1 (where it is no
+                                  // edge row), interior rows, and row 0 (phases 2 and 3)
+    int32_t Wf, ng;               // whole words of a sublattice row; 4-site groups of a partial last word
+    uint32_t m_w, m_c;            // ceil(2^32 / d) of d = Wf and of d = 4-site groups of a row
+    uint32_t in_off[2], out_off[2];   // mailboxes (64-bit words): [0] lower, [1] upper neighbour
+};
+// A replica of a resident launch and its jobs job0 .. job0 + P - 1.
+struct ResRep {
+    int32_t rep, job0, P, pad_;
+};
+// Launch state of the resident form (device memory, zero-initialised; the
+// last workgroup of each closing kernel resets it).
+struct ResSync {
+    unsigned int count;    // cluster workgroups that have started
+    unsigned int pad0_[31];
+    unsigned int state;    // RES_WAIT, RES_GO (all are resident) or RES_ABORT
+    unsigned int pad1_[31];
+    unsigned int done;     // closing kernel: workgroups finished
+    unsigned int epoch;    // mailbox epoch of the next launch
+    unsigned int pad2_[30];
+};
+enum { RES_WAIT = 0, RES_GO = 1, RES_ABORT = 2 };
+
 }  // namespace islf

@@ -131,6 +131,7 @@ def lib():
             "islf_get_barriers": [vp, P(i32)],
             "islf_get_taper": [vp, P(dbl)],
             "islf_testing_raise_barrier_error": [vp],
+            "islf_testing_abort_resident": [vp],
         }
         for name, args in sig.items():
             f = getattr(L, name)
