@@ -408,6 +408,21 @@ static void build_tables(const islf_replica_desc *d, RepDesc &D)
     }
 }
 
+// Without a bulk field (H = 0) and with J >= 0 a bulk move costs energy only
+// from four aligned neighbours on, and the same for both spins: four
+// thresholds, the first of them "always".
+static void build_sym(RepDesc &D)
+{
+    const uint64_t *t = D.thr;
+    bool sym = true;
+    for (int a = 0; a <= 6; ++a) {
+        const uint64_t up = t[8 + a], down = t[6 - a];   // a aligned neighbours of an up / a down spin
+        sym = sym && up == down && (a > 3 || up == 1ull << 32);
+    }
+    D.sym = sym ? 1 : 0;
+    for (int c = 0; c < 4; ++c) D.thr_q[c] = D.thr_m1[8 + 3 + c];
+}
+
 static void build_work(Replica &R, int rep_id, int fmt)
 {
     const islf_replica_desc &d = R.desc;
@@ -448,6 +463,7 @@ static void fill_desc(Replica &R, int fmt, uint32_t cap)
     D.rec = (islf_obs *)(m + sb);
     D.acc = (long long *)(m + sb + round_up((size_t)cap * sizeof(islf_obs), 256));
     build_tables(&d, D);
+    build_sym(D);
     D.Lx = d.Lx; D.Ly = d.Ly; D.Lz = d.Lz;
     D.C = (d.Lz + 7) / 8;
     D.K = (d.Lz + 15) / 16;
@@ -906,7 +922,7 @@ constexpr size_t kLatticeLds = 160 * 1024 - kResStaticLds;   // of a gfx950 CU's
 // Expected times (us) of the resident kernel: a chunk of 64 whole words on
 // one SIMD, the latency of a lone chunk, a partial word's four-site group,
 // the exchange of a phase, a workgroup barrier.
-constexpr double kChunkUs = 0.95, kLoneUs = 1.3, kGroupUs = 0.125, kExchangeUs = 2.0, kStageUs = 0.5;
+constexpr double kChunkUs = 0.90, kLoneUs = 1.3, kGroupUs = 0.12, kExchangeUs = 2.0, kStageUs = 0.5;
 // Films of at most this many four-site groups per phase are updated by one
 // lane per group when no film of the launch needs a cluster.
 constexpr long kSmallGroups = (long)kSmallTasks * kResThreads;
@@ -966,11 +982,11 @@ static uint32_t magic_of(int d) { return d >= 2 ? (uint32_t)(((1ull << 32) + (un
 // A sweep of the launch chain, measured: one chain takes 20 us a sweep in
 // launches whose work does not overlap (19.5 us per launch of a 46 M-site
 // bit-packed film), concurrent groups hide all but a few us of that on large
-// replicas (3 x 160x480x600: 62 us bit-packed, 95 us int8) and less on many
+// replicas (3 x 160x480x600: 57 us bit-packed, 95 us int8) and less on many
 // small ones (64 x 40x120x120: 31 us bit-packed).
 static double chain_sweep_us(const islf_ctx *c, long long sites, int nreps)
 {
-    const double work = (double)sites / (c->fmt == ISLF_SPIN_BITPACK ? 2.45e6 : 1.53e6);
+    const double work = (double)sites / (c->fmt == ISLF_SPIN_BITPACK ? 2.65e6 : 1.53e6);
     if (c->exec != ISLF_EXEC_BATCHED || nreps == 1) return std::max(14.0, 20.0 + work);
     return std::max(20.0, 5.0 + 0.15 * nreps + work);
 }

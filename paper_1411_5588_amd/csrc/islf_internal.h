@@ -49,6 +49,8 @@ struct RepDesc {
     uint32_t thr_m1[kThrEntries];  // thr - 1 (accept iff u <= thr_m1) where thr >= 1
     int32_t dpack[kThrEntries];    // change of (B, M) on a flip: dB + 65536 * dM
     uint64_t never_mask;           // bit i set when thr[i] == 0 (no draw can accept)
+    uint32_t thr_q[4];             // bulk class without a bulk field: thr - 1 by aligned neighbours <= 3, 4, 5, 6
+    int32_t sym;                   // 1: the bulk class depends on that number alone (thr_q holds it)
     int32_t Lx, Ly, Lz;
     int32_t C;             // Philox groups of 8 consecutive z per row, ceil(Lz/8)
     int32_t K;             // int8 8-byte columns per sublattice row, ceil(Lz/16)
@@ -110,7 +112,7 @@ struct TeamInfo {
 // ---------------------------------------------------------------------------
 constexpr int kResThreads = 1024;      // threads per workgroup: 4 waves per SIMD, one workgroup per CU
 constexpr int kResMaxSweeps = 256;     // sweeps one launch may run
-constexpr int kResStaticLds = 6784;    // LDS bytes beside the lattice: pair tables, thresholds, control words
+constexpr int kResStaticLds = 10880;    // LDS bytes beside the lattice: pair tables, thresholds, control words
 constexpr int kSmallTasks = 2;         // four-site groups a lane of the small form may hold per phase
 
 // A set of local rows base + i * stride, i = 0 .. n-1, with two rows left out

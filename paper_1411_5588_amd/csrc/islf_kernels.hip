@@ -68,8 +68,13 @@ struct Tables {
     TD td[kThrEntries];
     // bulk class, two neighbouring sites at once (bit-packed main tiles):
     // entry k, the index bits of the two sites interleaved (even bits: the
-    // first site's e = 8u + cnt, odd bits: the second's), holds their thr - 1
-    uint2 pair[256];
+    // first site's e = 8u + cnt, odd bits: the second's), holds their thr - 1;
+    // or, where those depend on the aligned neighbours alone, four
+    // neighbouring sites at once (quad_entry)
+    union {
+        uint2 pair[256];
+        uint4 quad[256];
+    };
 };
 
 template <bool PAIRS = false>
@@ -82,6 +87,10 @@ __device__ __forceinline__ void load_tables(const RepDesc &d, Tables *t)
     }
     if (PAIRS)
         for (int k = threadIdx.x; k < 256; k += blockDim.x) {
+            if (d.sym) {
+                t->quad[k] = quad_entry(d, k);
+                continue;
+            }
             const int ev = (k & 1) | ((k >> 1) & 2) | ((k >> 2) & 4) | ((k >> 3) & 8);
             const int od = ((k >> 1) & 1) | ((k >> 2) & 2) | ((k >> 3) & 4) | ((k >> 4) & 8);
             t->pair[k] = make_uint2(d.thr_m1[ev], d.thr_m1[od]);
@@ -418,6 +427,7 @@ __device__ __forceinline__ void bp_march(const RepView &v, const Entry &en, int 
         uint32_t F;
         if (SURF) F = bp_flips<NEVER>(S, b2, b1, b0, gq, u, tb, (x == 0 ? 1 : 0) + (x == Lx - 1 ? 2 : 0));
         else if (NEVER) F = bp_flips<true>(S, b2, b1, b0, gq, u, tb, 0);
+        else if (v.sym) F = bp_flips_quads(S, b2, b1, b0, gq, u, tb->quad);
         else F = bp_flips_pairs(S, b2, b1, b0, gq, u, tb->pair);
         F &= vmask;
         st32<COH>(v.spins, own, S ^ F);

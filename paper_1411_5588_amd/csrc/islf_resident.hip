@@ -45,7 +45,7 @@ struct Share {
     uint32_t SB, RB, PB;     // LDS bytes of a sublattice row, a local row, an x plane
     int R, ls, lr0, y0;
     uint32_t inv;            // seam inversion mask
-    bool refl, never;
+    bool refl, never, sym;
     uint32_t gx, gy;         // Philox counter steps of x and y
 };
 
@@ -57,6 +57,7 @@ struct Sums {
 // Static LDS of the kernels, ahead of the lattice: pair tables (see Tables) of
 // the bulk planes, x = 0 and x = Lx-1, all 64-bit thresholds, control words.
 struct ResTables {
+    uint4 quad[256];         // bulk planes, four sites at once (quad_entry), where RepDesc::sym holds
     uint2 pair[3 * 256];
     uint64_t thr[kThrEntries];
 };
@@ -210,15 +211,18 @@ __device__ __forceinline__ uint32_t exact_flips(uint32_t S, uint32_t b2, uint32_
 }
 
 // Accept bits of the word's first 4 ng sites from the pair tables, two groups
-// at a time from the top (a partial last word, or a replica with
-// never-accepted moves: those are rare misreadings of a draw of 0, found by
-// the smallest draw and done over).
-__device__ __forceinline__ uint32_t few_flips(const Word &o, int ng, const DrawKey &k, const uint2 *pair,
-                                              const uint64_t *thr, bool never)
+// at a time from the top: partial last words and, with QUADS = false, surface
+// planes and replicas that the four-site table does not cover (a bulk field,
+// or never-accepted moves: those are rare misreadings of a draw of 0, found
+// by the smallest draw and done over).
+template <bool QUADS>
+__device__ __forceinline__ uint32_t few_flips(const Word &o, int ng, const DrawKey &k, const uint4 *quad,
+                                              const uint2 *pair, const uint64_t *thr, bool never)
 {
     uint32_t w[4];
+    if (QUADS) quad_index(o.S, o.b2, o.b1, o.b0, w);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < 4 && !QUADS; ++j) {
         uint32_t acc = o.b0 >> (2 * j);
         acc = pick(0x0C0C0C0Cu, j == 0 ? o.b1 << 2 : o.b1 >> (2 * j - 2), acc);
         acc = pick(0x30303030u, j <= 2 ? o.b2 << (4 - 2 * j) : o.b2 >> 2, acc);
@@ -228,23 +232,35 @@ __device__ __forceinline__ uint32_t few_flips(const Word &o, int ng, const DrawK
     if (ng & 1) {
         const uint32_t sh = 4u * (uint32_t)(ng - 1);
         philox10(o.gq + 2u * (uint32_t)(ng - 1), k.t, k.replica, 0u, k.key0, k.key1, r);
-        F = reject_bits4(F, pair[(w[0] >> sh) & 0xFFu], pair[(w[1] >> sh) & 0xFFu], r);
-        low = min(min(r[0], r[1]), min(r[2], r[3]));
+        if (QUADS) {
+            const uint4 a = quad[(w[0] >> sh) & 0xFFu];
+            F = reject_bits4(F, make_uint2(a.x, a.y), make_uint2(a.z, a.w), r);
+        } else {
+            F = reject_bits4(F, pair[(w[0] >> sh) & 0xFFu], pair[(w[1] >> sh) & 0xFFu], r);
+        }
+        if (!QUADS) low = min(min(r[0], r[1]), min(r[2], r[3]));
     }
 #pragma unroll 1
     for (int h = (ng >> 1) - 1; h >= 0; --h) {
         const uint32_t sh = 8u * (uint32_t)h, c = o.gq + 4u * (uint32_t)h;
-        const uint2 l0 = pair[(w[0] >> sh) & 0xFFu], l1 = pair[(w[1] >> sh) & 0xFFu];
-        const uint2 h0 = pair[(w[2] >> sh) & 0xFFu], h1 = pair[(w[3] >> sh) & 0xFFu];
+        uint2 l0, l1, h0, h1;
+        if (QUADS) {
+            const uint4 a = quad[(w[0] >> sh) & 0xFFu], b = quad[(w[1] >> sh) & 0xFFu];
+            l0 = make_uint2(a.x, a.y), l1 = make_uint2(a.z, a.w);
+            h0 = make_uint2(b.x, b.y), h1 = make_uint2(b.z, b.w);
+        } else {
+            l0 = pair[(w[0] >> sh) & 0xFFu], l1 = pair[(w[1] >> sh) & 0xFFu];
+            h0 = pair[(w[2] >> sh) & 0xFFu], h1 = pair[(w[3] >> sh) & 0xFFu];
+        }
         uint32_t r1[4];
         philox10(c, k.t, k.replica, 0u, k.key0, k.key1, r);
         philox10<2u>(c, k.t, k.replica, 0u, k.key0, k.key1, r1);
         F = reject_bits4(F, h0, h1, r1);
         F = reject_bits4(F, l0, l1, r);
-        low = min(min(low, min(min(r[0], r[1]), min(r[2], r[3]))), min(min(r1[0], r1[1]), min(r1[2], r1[3])));
+        if (!QUADS) low = min(min(low, min(min(r[0], r[1]), min(r[2], r[3]))), min(min(r1[0], r1[1]), min(r1[2], r1[3])));
     }
     F = ~F;
-    if (never && __any(low == 0u))
+    if (!QUADS && never && __any(low == 0u))
         F = exact_flips(o.S, o.b2, o.b1, o.b0, o.gq, ng, k.t, k.replica, k.key0, k.key1, thr);
     return F;
 }
@@ -255,9 +271,9 @@ __device__ __forceinline__ uint32_t few_flips(const Word &o, int ng, const DrawK
 // numbers of chunks.  send: the new words of edge rows go to the neighbours'
 // mailboxes.
 template <bool SEAM>
-__device__ __forceinline__ void share_rows(const Share &g, const ResJob &jb, char *lat, const uint2 *pair,
-                                           const uint64_t *thr, const DrawKey &key, const ResRows &rs, int phase,
-                                           bool send, unsigned long long *mbox, uint32_t epoch, int &turn, Sums &a)
+__device__ __forceinline__ void share_rows(const Share &g, const ResJob &jb, char *lat, const uint4 *quad,
+                                           const uint2 *pair, const uint64_t *thr, const DrawKey &key,
+                                           const ResRows &rs, int phase, bool send, unsigned long long *mbox, uint32_t epoch, int &turn, Sums &a)
 {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     constexpr int W = kResThreads / 64;
@@ -283,13 +299,14 @@ __device__ __forceinline__ void share_rows(const Share &g, const ResJob &jb, cha
             const bool surf = c * 64 < plane || c * 64 + 63 >= T - plane;
             const bool x0 = x == 0, xl = x == g.Lx - 1;
             uint32_t F;
-            if (WHOLE && !g.never && !surf) {
-                F = bp_flips_pairs(o.S, o.b2, o.b1, o.b0, o.gq, key, pair);
+            if (g.sym && !surf) {
+                if (WHOLE) F = bp_flips_quads(o.S, o.b2, o.b1, o.b0, o.gq, key, quad);
+                else F = few_flips<true>(o, jb.ng, key, quad, pair, thr, false);
             } else {
-                F = few_flips(o, WHOLE ? 8 : jb.ng, key, pair + (x0 ? 256 : xl ? 512 : 0),
-                              thr + kThrPerClass * ((x0 ? 1 : 0) + (xl ? 2 : 0)), g.never);
-                if (!WHOLE) F &= (1u << g.rem) - 1u;
+                F = few_flips<false>(o, WHOLE ? 8 : jb.ng, key, quad, pair + (x0 ? 256 : xl ? 512 : 0),
+                                     thr + kThrPerClass * ((x0 ? 1 : 0) + (xl ? 2 : 0)), g.never);
             }
+            if (!WHOLE) F &= (1u << g.rem) - 1u;
             F = ok ? F : 0u;
             const uint32_t V = o.S ^ F;
             if (ok) *(uint32_t *)(lat + o.own) = V;
@@ -557,6 +574,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
         g.inv = d.seam_invert ? ~0u : 0u;
         g.refl = d.seam_reflect != 0;
         g.never = d.never_mask != 0;
+        g.sym = d.sym != 0 && !g.never;
         g.gy = 2u * (uint32_t)d.C;
         g.gx = g.gy * (uint32_t)d.Ly;
         DrawKey key{st[jb.rep].t, d.replica, d.key0, d.key1};
@@ -567,6 +585,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
             const int od = ((e >> 1) & 1) | ((e >> 2) & 2) | ((e >> 3) & 4) | ((e >> 4) & 8);
             pair[k] = make_uint2(d.thr_m1[cls * kThrPerClass + ev], d.thr_m1[cls * kThrPerClass + od]);
         }
+        for (int k = tid; k < 256 && g.sym; k += kResThreads) tb.quad[k] = quad_entry(d, k);
         if (tid < kThrEntries) thr[tid] = d.thr[tid];
         if (tid < 8) (&ctl->acc[0][0])[tid] = 0;
         if (tid == 8) ctl->bad = ~0u;
@@ -616,8 +635,8 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
                         const ResRows &rs = jb.set[k];
                         if (rs.n == 0) continue;
                         const bool send = xch && k == RES_EDGE;
-                        if (rs.seam) share_rows<true>(g, jb, lat, pair, thr, key, rs, phase, send, mbox, ep, turn, a);
-                        else share_rows<false>(g, jb, lat, pair, thr, key, rs, phase, send, mbox, ep, turn, a);
+                        if (rs.seam) share_rows<true>(g, jb, lat, tb.quad, pair, thr, key, rs, phase, send, mbox, ep, turn, a);
+                        else share_rows<false>(g, jb, lat, tb.quad, pair, thr, key, rs, phase, send, mbox, ep, turn, a);
                     }
                     if (xch && !share_receive(g, jb, lat, sync, mbox, ep, phase)) atomicMin(&ctl->bad, s + 1u);
                 }
