@@ -47,10 +47,7 @@ hipError_t launch_integrate(const double *h, const double *m1, const double *mn,
                             double norm, double *out, hipStream_t s);
 hipError_t noalloc_scratch(double **out);
 hipError_t resident_lds_limit(int fmt, size_t bytes);
-hipError_t launch_resident(int fmt, bool small, const RepDesc *descs, RepState *st, const ResJob *jobs,
-                           const int *first, const ResRep *reps, int grid, int njobs, int members, int nreps,
-                           size_t lds, uint32_t n, ResSync *rs, GridSync *sync, int4 *part, unsigned long long *mbox,
-                           int check_error, hipStream_t s);
+hipError_t launch_resident(int fmt, bool small, const ResLaunch &L, size_t lds, hipStream_t s);
 }  // namespace islf
 
 using namespace islf;
@@ -230,14 +227,9 @@ struct Plan {
 struct ResPlan {
     bool valid = false;    // built for the current replicas
     bool usable = false;   // they fit and the form is expected to be the faster one
-    ResJob *jobs = nullptr;
-    int *first = nullptr;
-    ResRep *reps = nullptr;
-    int4 *part = nullptr;
-    std::vector<int4 *> outgrown;   // smaller `part` buffers that captured graphs may still use
-    unsigned long long *mbox = nullptr;
-    size_t jobs_b = 0, first_b = 0, reps_b = 0, part_b = 0, mbox_b = 0;   // bytes allocated
-    int grid = 0, njobs = 0, members = 0, nreps = 0;
+    ResLaunch L{};         // tables (device memory) and counts; n, check_error and part per launch
+    size_t jobs_b = 0, first_b = 0, planes_b = 0, rows_b = 0, reps_b = 0, part_b = 0, mbox_b = 0;   // bytes allocated
+    std::vector<int4 *> outgrown;   // smaller sum buffers that captured graphs may still use
     bool small = false;    // no clusters and few words per film: one lane per four-site group
     size_t lds = 0;
     uint32_t max_sweeps = 0;
@@ -908,25 +900,31 @@ static islf_status prepare_plans(islf_ctx *c, int exec)
 // ---------------------------------------------------------------------------
 static void free_resident(islf_ctx *c, ResPlan &p)
 {
-    dev_free(c, p.jobs);
-    dev_free(c, p.first);
-    dev_free(c, p.reps);
-    dev_free(c, p.part);
+    dev_free(c, (void *)p.L.jobs);
+    dev_free(c, (void *)p.L.first);
+    dev_free(c, (void *)p.L.planes);
+    dev_free(c, (void *)p.L.rows);
+    dev_free(c, (void *)p.L.reps);
+    dev_free(c, p.L.part);
     for (int4 *o : p.outgrown) dev_free(c, o);
-    dev_free(c, p.mbox);
+    dev_free(c, p.L.mbox);
     p = ResPlan();
 }
 
 constexpr size_t kLatticeLds = 160 * 1024 - kResStaticLds;   // of a gfx950 CU's LDS
 
 // Expected times (us) of the resident kernel: a chunk of 64 whole words on
-// one SIMD, the latency of a lone chunk, a partial word's four-site group,
-// the exchange of a phase, a workgroup barrier.
-constexpr double kChunkUs = 0.90, kLoneUs = 1.3, kGroupUs = 0.12, kExchangeUs = 2.0, kStageUs = 0.5;
+// one SIMD; of partial words, and each of their four-site groups; the latency
+// of a lone chunk; the exchange of a phase, and per 1,000 words received; a
+// stage's barrier and the tail of its last chunks.
+constexpr double kChunkUs = 0.80, kPartUs = 0.18, kGroupUs = 0.092, kLoneUs = 1.3, kExchangeUs = 0.8, kMailUs = 0.4,
+                 kStageUs = 1.1;
 // Films of at most this many four-site groups per phase are updated by one
 // lane per group when no film of the launch needs a cluster.
 constexpr long kSmallGroups = (long)kSmallTasks * kResThreads;
 
+// A film cut into px x py shares: px blocks of mirrored plane pairs (the last
+// one the middle planes), py blocks of rows.
 struct ShareCost {
     const islf_replica_desc &d;
     int Wq, Wf, ng;
@@ -937,45 +935,115 @@ struct ShareCost {
         Wf = nbits / 32;
         ng = (nbits % 32 + 3) / 4;
     }
-    size_t lds(int rows) const
+    // block i of px: planes xa .. xa+n1-1 and n2 mirrored ones
+    void planes(int px, int i, int &xa, int &n1, int &n2) const
     {
-        return 4 * (size_t)(d.Lx + 2) * (size_t)(rows + 2) * 2 * (size_t)Wq;
+        const int H = (d.Lx + 1) / 2;
+        xa = (int)((long)i * H / px);
+        n1 = (int)((long)(i + 1) * H / px) - xa;
+        n2 = n1;
+        if (i == px - 1) {
+            n1 = d.Lx - 2 * xa;
+            n2 = 0;
+        }
     }
-    double phase(long rows) const
+    int max_planes(int px) const
     {
-        const long full = ceil_div((long)d.Lx * rows * Wf, 64), part = ng ? ceil_div((long)d.Lx * rows, 64) : 0;
-        const double busy = (full * kChunkUs + part * ng * kGroupUs) / 4.0;
-        const double lone = std::max(full ? kLoneUs : 0.0, part ? 0.3 + 0.15 * ng : 0.0);
-        return std::max(busy, lone);
+        int m = 0;
+        for (int i = 0; i < px; ++i) {
+            int xa, n1, n2;
+            planes(px, i, xa, n1, n2);
+            m = std::max(m, n1 + n2);
+        }
+        return m;
     }
-    // a sweep of a share of `rows` rows
-    double sweep(long rows, bool row0, bool cluster) const
+    // LDS of a share of np planes (in two runs) and `rows` rows, one of px > 1 blocks
+    size_t lds(int np, int px, int rows) const
     {
-        double t = 2.0 * (phase(row0 ? rows - 1 : rows) + (cluster ? kExchangeUs : 0.0) + kStageUs);
-        if (row0) t += 2.0 * (phase(1) + kStageUs);
-        return t;
+        const size_t lat = (size_t)(np + (px > 1 ? 4 : 2)) * (size_t)(rows + 2) * 8 * (size_t)Wq;
+        // planes, columns, and the mail of all four faces
+        return round_up(lat, 16) + 24 * (size_t)np + 28 * (size_t)rows * Wq + 4 * (size_t)(2 * np + (px > 1 ? 4 : 0) * rows) * Wq;
     }
-    // rows of share 0 (Ly-1, 0, 1 at least) and the most rows of the others
-    // when P >= 2 shares split the film; false if there are too few rows
-    bool split(int P, int &rows0, int &r) const
+    // SIMD time of a row set's chunks
+    double work(long np, long rows) const
     {
-        if (P < 2 || d.Ly < P + 2) return false;
-        // row 0's two stages cost share 0 as much as `extra` rows
-        const double row_us = std::max(1e-3, (2.0 * phase(64)) / 64.0);
-        const int extra = (int)(2.0 * (phase(1) + kStageUs) / row_us);
-        rows0 = std::max(3, d.Ly - (P - 1) * (int)ceil_div((long)d.Ly + extra, P));
-        r = (int)ceil_div((long)d.Ly - rows0, P - 1);
+        return ceil_div(np * rows * Wf, 64) * kChunkUs + (ng ? ceil_div(np * rows, 64) * (kPartUs + ng * kGroupUs) : 0.0);
+    }
+    double stage(double work_us) const
+    {
+        return std::max(work_us / 4.0, Wf ? kLoneUs : 0.4 + 0.15 * ng) + kStageUs;
+    }
+    // a sweep of a share of np planes and `rows` rows (see ResStage)
+    double sweep(long np, long rows, bool row0, bool has_x, bool has_y) const
+    {
+        const double mail = (has_y ? 2.0 * np * Wq : 0.0) + (has_x ? 4.0 * rows * Wq : 0.0);
+        const double xch = has_x || has_y ? 2.0 * (kExchangeUs + kMailUs * mail * 1e-3) : 0.0;
+        const double edge = has_y ? work(np, std::min(2l, rows)) : 0.0;
+        const long r = rows - (has_y ? 2 : 0);   // beside the edge rows
+        if (!row0) return 2.0 * stage(edge + (r > 0 ? work(np, r) : 0.0)) + xch;
+        const double seam = work(np, 2), inner = r > 3 ? work(np, r - 3) : 0.0;
+        return stage(edge + seam + inner) + stage(edge + seam) + 2.0 * stage(work(np, 1) + inner / 2.0) + xch;
+    }
+    // rows of the shares with row 0 (Ly-1, 0, 1 at least) and the most rows of
+    // the others when py >= 2; false if there are too few rows
+    bool split(int px, int py, int &rows0, int &r) const
+    {
+        rows0 = d.Ly;
+        r = 0;
+        if (py == 1) return true;
+        if (d.Ly < py + 2) return false;
+        // row 0's two more stages cost their share as much as `extra` rows
+        const double row_us = std::max(1e-3, work(max_planes(px), 64) / (2.0 * 64.0));
+        const int extra = (int)(2.0 * kStageUs / row_us + 0.5);
+        rows0 = std::max(3, d.Ly - (py - 1) * (int)ceil_div((long)d.Ly + extra, py));
+        r = (int)ceil_div((long)d.Ly - rows0, py - 1);
         return true;
     }
-    // expected sweep time with P shares, < 0 if they do not fit
-    double time(int P) const
+    // expected sweep time in px x py shares, < 0 if they do not fit
+    double time(int px, int py) const
     {
-        if (P == 1) return lds(d.Ly) <= kLatticeLds ? sweep(d.Ly, true, false) : -1.0;
         int rows0, r;
-        if (!split(P, rows0, r) || lds(std::max(rows0, r)) > kLatticeLds) return -1.0;
-        return std::max(sweep(rows0, true, true), sweep(r, false, true));
+        if (!split(px, py, rows0, r)) return -1.0;
+        const int np = max_planes(px);
+        if (lds(np, px, std::max(rows0, r)) > kLatticeLds) return -1.0;
+        if (px == 1 && py == 1) {
+            const long groups = (long)d.Lx * (d.Ly - 1) * ((d.Lz + 7) / 8);
+            if (groups <= kSmallGroups) return 3.0 + 0.0005 * groups;
+        }
+        return std::max(sweep(np, rows0, true, px > 1, py > 1), py > 1 ? sweep(np, r, false, px > 1, true) : 0.0);
     }
 };
+
+// A number of shares worth taking for a film: fewer are slower.
+struct ShareChoice {
+    int P, px, py;
+    double us;
+};
+
+// The useful cuts of a film into at most NW shares, by number of shares.
+static std::vector<ShareChoice> share_choices(const islf_replica_desc &d, int NW)
+{
+    const ShareCost k(d);
+    std::vector<ShareChoice> all, best;
+    const int H = (d.Lx + 1) / 2;
+    for (int px : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
+        if (px > H) break;
+        int last = 0;
+        for (int py = 1; px * py <= NW && py <= std::max(1, d.Ly - 2); ++py) {
+            const int rows = (int)ceil_div(d.Ly, py);
+            if (rows == last && py > 2) continue;   // as many rows as with one share fewer
+            last = rows;
+            const double t = k.time(px, py);
+            if (t >= 0) all.push_back({px * py, px, py, t});
+        }
+    }
+    std::stable_sort(all.begin(), all.end(), [](const ShareChoice &a, const ShareChoice &b) {
+        return a.P != b.P ? a.P < b.P : a.us < b.us;
+    });
+    for (const ShareChoice &c : all)
+        if (best.empty() || c.us < best.back().us) best.push_back(c);
+    return best;
+}
 
 static uint32_t magic_of(int d) { return d >= 2 ? (uint32_t)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d) : 0u; }
 
@@ -991,6 +1059,172 @@ static double chain_sweep_us(const islf_ctx *c, long long sites, int nreps)
     return std::max(20.0, 5.0 + 0.15 * nreps + work);
 }
 
+// The tables of a resident plan on the host.
+struct ResTablesHost {
+    std::vector<ResJob> jobs;
+    std::vector<int> first;
+    std::vector<ResPlane> planes;
+    std::vector<ResRow> rows;
+    std::vector<ResRep> reps;
+    size_t mbox_words = 0;
+};
+
+// The px x py shares of a film, appended to the tables; jobs go to `put`.
+template <class PUT>
+static void cut_film(const islf_replica_desc &d, int rep, int px, int py, bool small, int &id, ResTablesHost &h, PUT put)
+{
+    const ShareCost k(d);
+    const int P = px * py;
+    const uint32_t Wq = (uint32_t)k.Wq;
+    int rows0, rmax;
+    k.split(px, py, rows0, rmax);
+    std::vector<uint32_t> box(P), xface(P);   // a share's mailbox; its first x face in a slot
+    size_t slot = 0;                          // words of a slot, the same for all shares of the film
+    std::vector<int> R(py), y0(py);
+    const int before = py > 1 ? rows0 / 2 : 0;   // rows below row 0 in its shares
+    R[0] = rows0;
+    y0[0] = py > 1 ? d.Ly - before : 0;
+    long left = d.Ly - rows0;
+    for (int j = 1, y = rows0 - before; j < py; ++j) {
+        R[j] = (int)ceil_div(left, py - j);
+        y0[j] = y;
+        y += R[j];
+        left -= R[j];
+    }
+    std::vector<int> plane_off(px);
+    std::vector<int> np(px), ne(px), nh(px), nt(px);
+    for (int i = 0; i < px; ++i) {
+        int xa, n1, n2;
+        k.planes(px, i, xa, n1, n2);
+        np[i] = n1 + n2;
+        plane_off[i] = (int)h.planes.size();
+        std::vector<ResPlane> edge, mid, surf;
+        for (int q = 0; q < np[i]; ++q) {
+            ResPlane e{};
+            auto slot = [&](int v) { return (int16_t)(v < n1 ? v + 1 : v + 3); };
+            e.slot = slot(q);
+            e.mirror = slot(np[i] - 1 - q);
+            e.x = (int16_t)(q < n1 ? xa + q : d.Lx - xa - n2 + (q - n1));
+            e.flags = (int16_t)((e.x & 1) * PL_ODD + (e.x == 0 ? PL_X0 : 0) + (e.x == d.Lx - 1 ? PL_XL : 0));
+            // the outer share's inner face takes the first and the last plane, the inner share's outer face the two in the middle
+            if (i > 0) e.flags = (int16_t)(e.flags | (q == 0 ? 1 * PL_SEND : 0) | (q == np[i] - 1 ? 2 * PL_SEND : 0));
+            if (n2) e.flags = (int16_t)(e.flags | (q == n1 - 1 ? 4 * PL_SEND : 0) | (q == n1 ? 8 * PL_SEND : 0));
+            (e.flags >= PL_SEND ? edge : (e.flags & (PL_X0 | PL_XL)) ? surf : mid).push_back(e);
+        }
+        ne[i] = (int)edge.size();
+        nh[i] = 0;
+        for (int q = 0; q < ne[i]; ++q)
+            if (edge[q].flags & (PL_X0 | PL_XL)) nh[i] = q + 1;
+        nt[i] = (int)surf.size();
+        h.planes.insert(h.planes.end(), edge.begin(), edge.end());
+        h.planes.insert(h.planes.end(), mid.begin(), mid.end());
+        h.planes.insert(h.planes.end(), surf.begin(), surf.end());
+    }
+    for (int j = 0; j < py; ++j)
+        for (int i = 0; i < px; ++i) {
+            const size_t y = py > 1 ? 2 * (size_t)np[i] * Wq : 0;
+            const size_t x = (size_t)((i > 0 ? 2 : 0) + (i < px - 1 ? 2 : 0)) * R[j] * Wq;
+            xface[j * px + i] = (uint32_t)y;
+            slot = std::max(slot, y + x);
+        }
+    for (uint32_t &v : box) {
+        v = (uint32_t)h.mbox_words;
+        if (P > 1) h.mbox_words += 2 * slot;
+    }
+    for (int j = 0; j < py; ++j) {
+        // the block's rows by set
+        const int lr0 = j == 0 ? before + 1 : 0, ls = j == 0 ? (py > 1 ? before : d.Ly) : 0;
+        const int row_off = (int)h.rows.size();
+        ResRows set[4] = {};
+        // (chunk counts depend on the block's planes: filled in below)
+        auto add = [&](int k_, const std::vector<int> &lrs) {
+            set[k_].r0 = (int)h.rows.size() - row_off;
+            set[k_].n = (int)lrs.size();
+            set[k_].m = magic_of((int)lrs.size());
+            set[k_].m_w = magic_of((int)lrs.size() * k.Wf);
+            for (int lr : lrs) {
+                ResRow e{};
+                e.y = lr0 && lr >= lr0 ? lr - lr0 : y0[j] + lr - 1;
+                e.lr = (int16_t)lr;
+                e.flags = (int16_t)((e.y & 1) * RW_ODD + (lr == ls ? RW_LAST : 0) + (lr == lr0 ? RW_ROW0 : 0) +
+                                    (py > 1 && lr == 1 ? RW_DOWN : 0) + (py > 1 && lr == R[j] ? RW_UP : 0));
+                set[k_].seam |= (lr == ls || lr == lr0) ? 1 : 0;
+                h.rows.push_back(e);
+            }
+        };
+        std::vector<int> edge, last, inner;
+        for (int lr = 1; lr <= R[j]; ++lr) {
+            if (lr == lr0) continue;
+            if (py > 1 && (lr == 1 || lr == R[j])) edge.push_back(lr);
+            else if (lr0 && (lr == ls || lr == lr0 + 1) && !small) last.push_back(lr);
+            else inner.push_back(lr);
+        }
+        add(RES_EDGE, edge);
+        add(RES_SEAM, last);
+        add(RES_INNER, inner);
+        add(RES_ROW0, lr0 ? std::vector<int>(1, lr0) : std::vector<int>());
+        for (int i = 0; i < px; ++i) {
+            ResJob b{};
+            b.rep = rep;
+            b.P = P;
+            b.id = id++;
+            b.y0 = y0[j];
+            b.R = R[j];
+            b.ls = ls;
+            b.lr0 = lr0;
+            k.planes(px, i, b.xa, b.n1, b.n2);
+            b.has = (py > 1 ? HAS_Y : 0) | (i > 0 ? HAS_OUTER : 0) | (i < px - 1 ? HAS_INNER : 0);
+            b.planes = plane_off[i];
+            b.rows = row_off;
+            b.n_edge = ne[i];
+            b.n_head = nh[i];
+            b.n_tail = nt[i];
+            for (int q = 0; q < 4; ++q) {
+                b.set[q] = set[q];
+                b.set[q].whole = (int)ceil_div((long)np[i] * set[q].n * k.Wf, 64);
+                b.set[q].part = k.ng ? (int)ceil_div((long)np[i] * set[q].n, 64) : 0;
+            }
+            // Stages.  Row 0's phases 2 and 3 follow phase 1 of the rows beside it and precede their next
+            // phase 0; a share with row 0 does those rows first and splits the interior rows' phase 1 over
+            // the two stages of row 0, which hides their latency and that of row 0's own mail.
+            const bool two = px > 1;
+            auto part = [&](int set_, int phase, int c0 = 0, int c1 = -1) {
+                return ResPart{(int16_t)set_, (int16_t)phase, c0, c1 < 0 ? b.set[set_].whole + b.set[set_].part : c1};
+            };
+            auto stage = [&](std::vector<ResPart> v, int mail, int mail_row0) {
+                ResStage &t = b.stage[b.stages++];
+                for (int q = 0; q < 3; ++q) t.part[q] = q < (int)v.size() ? v[q] : ResPart{RES_INNER, 0, 0, 0};
+                t.mail = P > 1 ? mail : -1;
+                t.mail_row0 = two ? mail_row0 : -1;
+            };
+            const int inner_n = b.set[RES_INNER].whole + b.set[RES_INNER].part;
+            stage({part(RES_EDGE, 0), part(RES_SEAM, 0), part(RES_INNER, 0)}, 0, lr0 ? 3 : -1);
+            if (!lr0) {
+                stage({part(RES_EDGE, 1), part(RES_INNER, 1)}, 1, -1);
+            } else {
+                stage({part(RES_EDGE, 1), part(RES_SEAM, 1)}, -1, -1);
+                stage({part(RES_ROW0, 2), part(RES_INNER, 1, 0, inner_n / 2)}, -1, 2);
+                stage({part(RES_ROW0, 3), part(RES_INNER, 1, inner_n / 2, inner_n)}, 1, -1);
+            }
+            b.Wf = k.Wf;
+            b.ng = k.ng;
+            b.m_c = magic_of((d.Lz + 7) / 8);
+            b.m_q = magic_of(k.Wq);
+            b.m_f = magic_of(R[j] * k.Wq);
+            b.in = box[j * px + i];
+            b.slot = (uint32_t)slot;
+            if (py > 1) {
+                b.out_y[0] = box[(j + py - 1) % py * px + i] + (uint32_t)np[i] * Wq;   // the lower share's upper face
+                b.out_y[1] = box[(j + 1) % py * px + i];                               // the upper share's lower face
+            }
+            // the outer share's inner face (after its outer one, if any); the inner share's outer face
+            if (i > 0) b.out_x[0] = box[j * px + i - 1] + xface[j * px + i - 1] + (i > 1 ? 2u : 0u) * (uint32_t)R[j] * Wq;
+            if (i < px - 1) b.out_x[1] = box[j * px + i + 1] + xface[j * px + i + 1];
+            put(b, k.lds(np[i], px, R[j]));
+        }
+    }
+}
+
 // Shares of the listed replicas for one launch of at most num_cu workgroups
 // (one per CU: the kernel's registers allow no second one).  Replicas that
 // need several workgroups get a share each on workgroups of their own, the
@@ -998,19 +1232,29 @@ static double chain_sweep_us(const islf_ctx *c, long long sites, int nreps)
 // least work (they wait for nobody, so a workgroup may hold several).  The
 // target time per sweep that sets the shares is scanned for the shortest
 // launch.  Returns false if the replicas do not fit.
-static bool plan_resident(const islf_ctx *c, const std::vector<int> &reps, std::vector<ResJob> &jobs,
-                          std::vector<int> &first, std::vector<ResRep> &rr, ResPlan &p, size_t &mbox_words)
+static bool plan_resident(const islf_ctx *c, const std::vector<int> &reps, ResPlan &p, ResTablesHost &h)
 {
     const int n = (int)reps.size(), NW = c->num_cu;
-    std::vector<ShareCost> cost;
+    // replicas of one shape share their choices
+    std::vector<std::vector<ShareChoice>> shapes;
+    std::vector<int> shape(n), example;
+    std::unordered_map<unsigned long long, int> known;
     double total = 0.0;
-    for (int r : reps) {
-        cost.emplace_back(c->reps[r].desc);
-        const ShareCost &k = cost.back();
-        total += 2.0 * k.phase(k.d.Ly);
+    for (int i = 0; i < n; ++i) {
+        const islf_replica_desc &d = c->reps[reps[i]].desc;
+        if (d.Lx > 32000 || d.Ly > 32000) return false;   // 16-bit table entries
+        const unsigned long long key = ((unsigned long long)d.Lx << 48) ^ ((unsigned long long)d.Ly << 32) ^ (unsigned)d.Lz;
+        auto it = known.find(key);
+        if (it == known.end()) {
+            it = known.emplace(key, (int)shapes.size()).first;
+            shapes.push_back(share_choices(d, NW));
+            if (shapes.back().empty()) return false;
+        }
+        shape[i] = it->second;
+        const ShareChoice &f = shapes[shape[i]].front();
+        total += f.P * f.us;
     }
-    std::vector<int> P(n), bestP;
-    std::vector<double> tr(n);
+    std::vector<const ShareChoice *> pick(n), best_pick;
     double best = 1e300;
     auto pack = [&](std::vector<int> *where) -> double {
         // cluster workgroups first, then singles by LPT; returns the longest workgroup
@@ -1019,172 +1263,97 @@ static bool plan_resident(const islf_ctx *c, const std::vector<int> &reps, std::
         int w = 0;
         std::vector<int> single;
         for (int i = 0; i < n; ++i) {
-            if (P[i] == 1) {
+            if (pick[i]->P == 1) {
                 single.push_back(i);
                 continue;
             }
-            for (int k = 0; k < P[i]; ++k) heap.push_back({-tr[i], w++});
-            longest = std::max(longest, tr[i]);
+            for (int k = 0; k < pick[i]->P; ++k) heap.push_back({-pick[i]->us, w++});
+            longest = std::max(longest, pick[i]->us);
         }
         for (; w < NW; ++w) heap.push_back({0.0, w});
         std::make_heap(heap.begin(), heap.end());
-        std::stable_sort(single.begin(), single.end(), [&](int a, int b) { return tr[a] > tr[b]; });
+        std::stable_sort(single.begin(), single.end(), [&](int a, int b) { return pick[a]->us > pick[b]->us; });
         for (int i : single) {
             std::pop_heap(heap.begin(), heap.end());
-            heap.back().first -= tr[i];
+            heap.back().first -= pick[i]->us;
             longest = std::max(longest, -heap.back().first);
             if (where) (*where)[i] = heap.back().second;
             std::push_heap(heap.begin(), heap.end());
         }
         return longest;
     };
-    const double t0 = std::max(3.0, 0.7 * total / NW);
-    for (int step = 0; step < 48; ++step) {
-        const double T = t0 * pow(1.07, step);
+    const double t0 = std::max(2.0, 0.7 * total / NW);
+    for (int step = 0; step < 64; ++step) {
+        const double T = t0 * pow(1.04, step);
         long used = 0;
-        bool ok = true;
-        for (int i = 0; i < n && ok; ++i) {
-            int k = 1;
-            double t = cost[i].time(1);
-            if (t < 0 || t > T) {
-                // the fewest shares within T, else those with the shortest time
-                int bk = 0;
-                double bt = 1e300;
-                const int cap = std::min(NW, std::max(1, c->reps[reps[i]].desc.Ly - 2));
-                for (k = std::max(2, (int)(0.5 * 2.0 * cost[i].phase(cost[i].d.Ly) / T)); k <= cap; ++k) {
-                    const double tk = cost[i].time(k);
-                    if (tk < 0) continue;
-                    if (tk < bt) {
-                        bt = tk;
-                        bk = k;
-                    }
-                    if (tk <= T) break;
-                }
-                if (t >= 0 && (bk == 0 || t <= bt)) bk = 1;
-                else t = bt;
-                if (bk == 0) ok = false;
-                k = bk;
-            }
-            P[i] = k;
-            tr[i] = t;
-            if (k > 1) used += k;
-            if (used > NW) ok = false;
+        for (int i = 0; i < n; ++i) {
+            // the fewest shares within T, else the fastest cut
+            const std::vector<ShareChoice> &v = shapes[shape[i]];
+            size_t q = 0;
+            while (q + 1 < v.size() && v[q].us > T) ++q;
+            pick[i] = &v[q];
+            if (v[q].P > 1) used += v[q].P;
         }
-        if (!ok) continue;
+        if (used > NW) continue;
         const double m = pack(nullptr);
         if (m < best) {
             best = m;
-            bestP = P;
+            best_pick = pick;
         }
         if (m < T) break;
     }
-    if (bestP.empty()) return false;
-    P = bestP;
-    for (int i = 0; i < n; ++i) tr[i] = cost[i].time(P[i]);
+    if (best_pick.empty()) return false;
+    pick = best_pick;
     std::vector<int> where(n, -1);
     p.sweep_us = pack(&where);
     p.small = true;
     for (int i = 0; i < n; ++i) {
-        const islf_replica_desc &d = cost[i].d;
+        const islf_replica_desc &d = c->reps[reps[i]].desc;
         const long row = (long)d.Lx * ((d.Lz + 7) / 8);   // groups of a row
-        p.small = p.small && P[i] == 1 && row <= kResThreads && row * (d.Ly - 1) <= kSmallGroups;
+        p.small = p.small && pick[i]->P == 1 && row <= kResThreads && row * (d.Ly - 1) <= kSmallGroups;
     }
-    // jobs by workgroup
     std::vector<std::vector<ResJob>> wg(NW);
-    p.members = 0;
+    p.L.members = 0;
     p.lds = 0;
-    mbox_words = 0;
-    rr.clear();
     int id = 0;
     for (int i = 0; i < n; ++i) {
-        const ShareCost &k = cost[i];
-        rr.push_back(ResRep{reps[i], id, P[i], 0});
-        const islf_replica_desc &d = k.d;
-        const size_t box = (size_t)d.Lx * k.Wq;   // words of one mailbox slot
-        int rows0 = d.Ly, r = 0;
-        if (P[i] > 1) k.split(P[i], rows0, r);
-        const int before = P[i] > 1 ? rows0 / 2 : 0;   // share 0's rows below row 0
-        int y = P[i] > 1 ? rows0 - before : 0;          // first row of the next share
-        long left = d.Ly - rows0;
-        for (int q = 0; q < P[i]; ++q) {
-            ResJob j{};
-            j.rep = reps[i];
-            j.id = id++;
-            j.P = P[i];
-            j.p = q;
-            if (q == 0) {
-                j.R = rows0;
-                j.y0 = P[i] > 1 ? d.Ly - before : 0;
-                j.lr0 = P[i] > 1 ? before + 1 : 1;
-                j.ls = P[i] > 1 ? before : d.Ly;
-            } else {
-                j.R = (int)ceil_div(left, P[i] - q);
-                j.y0 = y;
-                y += j.R;
-                left -= j.R;
-            }
-            const bool cl = P[i] > 1;
-            auto rows = [](int base, int stride, int skip, int cnt, bool seam) {
-                return ResRows{base, stride, skip, std::max(0, cnt), magic_of(std::max(0, cnt)), seam ? 1 : 0};
-            };
-            if (cl) j.set[RES_EDGE] = rows(1, std::max(1, j.R - 1), 0, j.R == 1 ? 1 : 2, j.ls == 1);
-            if (j.lr0 == 0) {
-                j.set[RES_INNER] = rows(2, 1, 0, j.R - 2, false);
-            } else if (!cl) {
-                // row y = 0 first, y = Ly-1 last
-                j.set[RES_INNER] = p.small ? rows(2, 1, 0, j.R - 1, true) : rows(2, 1, 0, j.R - 2, false);
-                if (!p.small) j.set[RES_LAST] = rows(j.ls, 1, 0, 1, true);
-            } else if (j.ls == 1) {
-                j.set[RES_INNER] = rows(3, 1, 0, j.R - 3, false);
-            } else {
-                j.set[RES_INNER] = rows(2, 1, j.ls, j.R - 4, false);
-                j.set[RES_LAST] = rows(j.ls, 1, 0, 1, true);
-            }
-            if (j.lr0) j.set[RES_ROW0] = rows(j.lr0, 1, 0, 1, true);
-            j.Wf = k.Wf;
-            j.ng = k.ng;
-            j.m_w = magic_of(j.Wf);
-            j.m_c = magic_of((d.Lz + 7) / 8);
-            if (cl) {
-                auto inbox = [&](int s, int face) {
-                    const int t = (s + P[i]) % P[i];
-                    return (uint32_t)(mbox_words + ((size_t)t * 4 + 2 * (size_t)face) * box);
-                };
-                for (int f = 0; f < 2; ++f) j.in_off[f] = inbox(q, f);
-                j.out_off[0] = inbox(q - 1, 1);
-                j.out_off[1] = inbox(q + 1, 0);
-                wg[p.members++].push_back(j);
-            } else {
-                wg[where[i]].push_back(j);
-            }
-            p.lds = std::max(p.lds, k.lds(j.R));
-        }
-        if (P[i] > 1) mbox_words += (size_t)P[i] * 4 * box;
+        h.reps.push_back(ResRep{reps[i], id, pick[i]->P, 0});
+        cut_film(c->reps[reps[i]].desc, reps[i], pick[i]->px, pick[i]->py, p.small, id, h,
+                 [&](const ResJob &j, size_t lds) {
+                     wg[j.P > 1 ? p.L.members++ : where[i]].push_back(j);
+                     p.lds = std::max(p.lds, lds);
+                 });
+        if (h.mbox_words >= (1ull << 29)) return false;   // 32-bit byte offsets
     }
-    if (mbox_words >= (1ull << 32)) return false;
-    jobs.clear();
-    first.assign(1, 0);
+    // a workgroup's cluster share comes before its single films
+    h.first.assign(1, 0);
     for (int w = 0; w < NW; ++w) {
         if (wg[w].empty()) continue;
-        jobs.insert(jobs.end(), wg[w].begin(), wg[w].end());
-        first.push_back((int)jobs.size());
+        std::stable_sort(wg[w].begin(), wg[w].end(), [](const ResJob &a, const ResJob &b) { return (a.P > 1) > (b.P > 1); });
+        h.jobs.insert(h.jobs.end(), wg[w].begin(), wg[w].end());
+        h.first.push_back((int)h.jobs.size());
     }
-    p.grid = (int)first.size() - 1;
-    p.njobs = (int)jobs.size();
-    p.nreps = n;
+    p.L.grid = (int)h.first.size() - 1;
+    p.L.njobs = (int)h.jobs.size();
+    p.L.nreps = n;
     return true;
 }
 
-// Grows a device buffer of the plan to `bytes`.
+// Puts a host table into a device buffer of the plan, grown if needed.
 template <class T>
-static bool grow(islf_ctx *c, T *&ptr, size_t &have, size_t bytes)
+static bool put_table(islf_ctx *c, const T *&ptr, size_t &have, const std::vector<T> &v, hipError_t &e)
 {
-    if (bytes <= have) return true;
-    dev_free(c, ptr);
-    have = 0;
-    ptr = (T *)dev_alloc(c, bytes);
-    if (ptr) have = bytes;
-    return ptr != nullptr;
+    const size_t bytes = sizeof(T) * std::max<size_t>(1, v.size());
+    if (bytes > have) {
+        dev_free(c, (void *)ptr);
+        have = 0;
+        ptr = (const T *)dev_alloc(c, bytes);
+        if (!ptr) return false;
+        have = bytes;
+    }
+    if (!v.empty() && e == hipSuccess)
+        e = hipMemcpyAsync((void *)ptr, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice, c->stream);
+    return true;
 }
 
 // Builds the resident plan of some replicas (synchronises).  A plan that
@@ -1195,11 +1364,8 @@ static islf_status build_resident(islf_ctx *c, ResPlan &p, const std::vector<int
     p.usable = false;
     for (int4 *o : p.outgrown) dev_free(c, o);
     p.outgrown.clear();
-    std::vector<ResJob> jobs;
-    std::vector<int> first;
-    std::vector<ResRep> rr;
-    size_t mbox_words = 0;
-    if (reps.empty() || !plan_resident(c, reps, jobs, first, rr, p, mbox_words)) return ISLF_OK;
+    ResTablesHost h;
+    if (reps.empty() || !plan_resident(c, reps, p, h)) return ISLF_OK;
     long long sites = 0;
     size_t bytes = 0;
     for (int r : reps) {
@@ -1211,19 +1377,32 @@ static islf_status build_resident(islf_ctx *c, ResPlan &p, const std::vector<int
     p.fixed_us = 16.0 + 2.0 * (double)bytes / 2.0e6;
     if (p.sweep_us >= p.chain_us) return ISLF_OK;
     // per-sweep sums: 8 MiB at most (allocated by the longest run, see size_sums)
-    p.max_sweeps = (uint32_t)std::max<size_t>(1, std::min<size_t>(kResMaxSweeps, (8u << 20) / (16 * (size_t)p.njobs)));
-    if (!grow(c, p.jobs, p.jobs_b, sizeof(ResJob) * jobs.size()) ||
-        !grow(c, p.first, p.first_b, sizeof(int) * first.size()) ||
-        !grow(c, p.reps, p.reps_b, sizeof(ResRep) * rr.size()) ||
-        !grow(c, p.mbox, p.mbox_b, 8 * std::max<size_t>(1, mbox_words)))
+    p.max_sweeps = (uint32_t)std::max<size_t>(1, std::min<size_t>(kResMaxSweeps, (8u << 20) / (16 * (size_t)p.L.njobs)));
+    hipError_t e = hipSuccess;
+    if (!put_table(c, p.L.jobs, p.jobs_b, h.jobs, e) || !put_table(c, p.L.first, p.first_b, h.first, e) ||
+        !put_table(c, p.L.planes, p.planes_b, h.planes, e) || !put_table(c, p.L.rows, p.rows_b, h.rows, e) ||
+        !put_table(c, p.L.reps, p.reps_b, h.reps, e)) {
+        (void)hipStreamSynchronize(c->stream);   // no copy may outlive its source
         return ISLF_OK;
-    HIP_TRY(resident_lds_limit(c->fmt, kLatticeLds));
-    HIP_TRY(hipMemcpyAsync(p.jobs, jobs.data(), sizeof(ResJob) * jobs.size(), hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipMemcpyAsync(p.first, first.data(), sizeof(int) * first.size(), hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipMemcpyAsync(p.reps, rr.data(), sizeof(ResRep) * rr.size(), hipMemcpyHostToDevice, c->stream));
+    }
+    const size_t mb = 8 * std::max<size_t>(1, h.mbox_words);
+    if (mb > p.mbox_b) {
+        dev_free(c, p.L.mbox);
+        p.mbox_b = 0;
+        p.L.mbox = (unsigned long long *)dev_alloc(c, mb);
+        if (p.L.mbox) p.mbox_b = mb;
+    }
     // no mailbox word may carry an epoch still to come
-    HIP_TRY(launch_zero(p.mbox, (long)mbox_words, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
+    if (e == hipSuccess && p.L.mbox) e = launch_zero(p.L.mbox, (long)h.mbox_words, c->stream);
+    if (e == hipSuccess) e = resident_lds_limit(c->fmt, kLatticeLds);
+    const hipError_t es = hipStreamSynchronize(c->stream);
+    HIP_TRY(e);
+    HIP_TRY(es);
+    if (!p.L.mbox) return ISLF_OK;
+    p.L.descs = c->d_desc;
+    p.L.st = c->d_state;
+    p.L.rs = c->d_rsy;
+    p.L.sync = c->d_sync;
     p.usable = true;
     return ISLF_OK;
 }
@@ -1231,12 +1410,12 @@ static islf_status build_resident(islf_ctx *c, ResPlan &p, const std::vector<int
 // Room for the per-sweep sums of a run of n sweeps.
 static bool size_sums(islf_ctx *c, ResPlan &p, uint32_t n)
 {
-    const size_t bytes = sizeof(int4) * std::min(n, p.max_sweeps) * (size_t)p.njobs;
+    const size_t bytes = sizeof(int4) * std::min(n, p.max_sweeps) * (size_t)p.L.njobs;
     if (bytes <= p.part_b) return true;
     int4 *np = (int4 *)dev_alloc(c, bytes);
     if (!np) return false;
-    if (p.part) p.outgrown.push_back(p.part);
-    p.part = np;
+    if (p.L.part) p.outgrown.push_back(p.L.part);
+    p.L.part = np;
     p.part_b = bytes;
     return true;
 }
@@ -1284,14 +1463,13 @@ static islf_status resident_applies(islf_ctx *c, uint32_t n, bool *use)
 // Enqueues n sweeps in the resident form (plans built, no checks, no sync).
 static hipError_t enqueue_resident(islf_ctx *c, uint32_t n)
 {
-    const int check = c->exec == ISLF_EXEC_PERSISTENT;
     auto run = [&](const ResPlan &p) -> hipError_t {
+        ResLaunch L = p.L;
+        L.check_error = c->exec == ISLF_EXEC_PERSISTENT;
         hipError_t e = hipSuccess;
-        for (uint32_t done = 0; done < n && e == hipSuccess;) {
-            const uint32_t k = std::min(n - done, p.max_sweeps);
-            e = launch_resident(c->fmt, p.small, c->d_desc, c->d_state, p.jobs, p.first, p.reps, p.grid, p.njobs, p.members,
-                                p.nreps, p.lds, k, c->d_rsy, c->d_sync, p.part, p.mbox, check, c->stream);
-            done += k;
+        for (uint32_t done = 0; done < n && e == hipSuccess; done += L.n) {
+            L.n = std::min(n - done, p.max_sweeps);
+            e = launch_resident(c->fmt, p.small, L, p.lds, c->stream);
         }
         return e;
     };
@@ -2116,6 +2294,8 @@ extern "C" islf_status islf_batch_retire(islf_ctx *ctx, int32_t slot)
     R.mem_bytes = 0;
     R.main.clear();
     R.slab.clear();
+    free_resident(ctx, ctx->resident);
+    for (ResPlan &p : ctx->resident_plain) free_resident(ctx, p);
     ctx->dirty = true;
     return sync_tables(ctx);
 }

@@ -115,30 +115,71 @@ constexpr int kResMaxSweeps = 256;     // sweeps one launch may run
 constexpr int kResStaticLds = 10880;    // LDS bytes beside the lattice: pair tables, thresholds, control words
 constexpr int kSmallTasks = 2;         // four-site groups a lane of the small form may hold per phase
 
-// A set of local rows base + i * stride, i = 0 .. n-1, with two rows left out
-// from row `skip` on (0: none).
+// Tables of a share, as the host writes them: its planes in the order of
+// update (those sent to x neighbours first, free surfaces last) and its rows
+// (by row set).  Slots are positions in LDS: two runs of planes, each with a
+// halo plane on both sides (one run: the whole film or the middle).
+enum { PL_ODD = 1, PL_X0 = 2, PL_XL = 4, PL_SEND = 16 };   // x odd; x = 0; x = Lx-1; sent to outer j = 0, 1, inner j = 0, 1
+struct ResPlane {
+    int16_t slot, x, mirror, flags;   // mirror: slot of plane Lx-1-x
+};
+enum { RW_ODD = 1, RW_LAST = 2, RW_ROW0 = 4, RW_DOWN = 8, RW_UP = 16 };   // y odd; y = Ly-1; y = 0; sent down, up
+struct ResRow {
+    int32_t y;
+    int16_t lr, flags;
+};
+// A row set: entries r0 .. r0 + n - 1 of the row table.
 struct ResRows {
-    int32_t base, stride, skip, n;
-    uint32_t m;                   // ceil(2^32 / n), 0 for n = 1
+    int32_t r0, n;
+    uint32_t m, m_w;              // ceil(2^32 / d) of d = n and of d = n * whole words of a row
+    int32_t whole, part;          // chunks of 64 whole words, of 64 partial last words
     int32_t seam;                 // holds row y = 0 or Ly-1
 };
-enum { RES_EDGE = 0, RES_LAST = 1, RES_INNER = 2, RES_ROW0 = 3 };
+enum { RES_EDGE = 0, RES_SEAM = 1, RES_INNER = 2, RES_ROW0 = 3 };
+// A stage of a sweep ends with a workgroup barrier.  It updates chunks
+// [c0, c1) of up to three row sets (whole words are numbered before partial
+// ones) and takes in the neighbours' mail of one or two phases.
+struct ResPart {
+    int16_t set, phase;
+    int32_t c0, c1;
+};
+struct ResStage {
+    ResPart part[3];
+    int32_t mail, mail_row0;      // phase 0 or 1 of the main rows / phase 2 or 3 of row 0 taken in, -1 none
+};
+enum { HAS_Y = 1, HAS_OUTER = 2, HAS_INNER = 4 };   // neighbours of a share
 
-// One workgroup's share of one replica: `R` consecutive rows of the y ring
-// (all x, all z) starting at row y0.  A replica's P shares form a cluster;
-// share 0 holds rows Ly-1, 0 and 1, so that the y seam and the phases of row
-// 0 stay inside one workgroup.  Local rows are 1 .. R, rows 0 and R+1 are
-// copies of the neighbouring shares' edge rows (unused when P = 1).
+// One workgroup's share of one replica: R consecutive rows of the y ring
+// starting at row y0 (all z) in planes xa .. xa+n1-1 and their mirror images
+// (n2 = n1), or in the middle planes xa .. Lx-1-xa (n2 = 0; all planes when
+// xa = 0).  A replica's P shares form a cluster.  Planes come in mirrored
+// pairs and the shares that hold row 0 also hold rows Ly-1 and 1, so that the
+// y seam joins sites of one share whatever the boundary, and only row 0's own
+// x neighbours sit in other shares during phases 2 and 3.  Local rows are
+// 1 .. R; local rows 0 and R+1 and the halo planes are copies of the
+// neighbouring shares' edges, or 0 beyond a free surface.
 struct ResJob {
-    int32_t rep, P, p;
+    int32_t rep, P;
     int32_t id;                   // its slot in the per-sweep sums (a replica's shares are consecutive)
     int32_t y0, R;
     int32_t ls, lr0;              // local rows of y = Ly-1 and y = 0 (0: not in this share)
-    ResRows set[4];               // edge rows (updated first, sent to the neighbours), row Ly-1 (where it is no
-                                  // edge row), interior rows, and row 0 (phases 2 and 3)
+    int32_t xa, n1, n2;
+    int32_t has;                  // HAS_*
+    int32_t planes, rows;         // offsets of its tables
+    int32_t n_edge, n_head, n_tail;   // planes sent to x neighbours; surface planes among the first / at the end
+    ResRows set[4];               // edge rows (sent to the y neighbours), rows Ly-1 and 1 beside row 0 (where they
+                                  // are no edge rows), interior rows, and row 0 (phases 2 and 3)
+    int32_t stages;               // 2, or 4 in a share with row 0
+    ResStage stage[4];
     int32_t Wf, ng;               // whole words of a sublattice row; 4-site groups of a partial last word
-    uint32_t m_w, m_c;            // ceil(2^32 / d) of d = Wf and of d = 4-site groups of a row
-    uint32_t in_off[2], out_off[2];   // mailboxes (64-bit words): [0] lower, [1] upper neighbour
+    uint32_t m_c;                 // ceil(2^32 / d) of d = 4-site groups of a row,
+    uint32_t m_q, m_f;            // of d = words of a row, of d = R * words of a row
+    // mailboxes (64-bit words).  This share's: two slots (by phase & 1) of
+    // `slot` words, the faces it has one after the other: y from below and
+    // from above (plane, word), x from the outer share (run of lower x, of
+    // upper x) and from the inner one (local row - 1, word).  The neighbours'
+    // faces that it fills: out_y below, above; out_x outer, inner.
+    uint32_t in, slot, out_y[2], out_x[2];
 };
 // A replica of a resident launch and its jobs job0 .. job0 + P - 1.
 struct ResRep {
@@ -156,5 +197,22 @@ struct ResSync {
     unsigned int pad2_[30];
 };
 enum { RES_WAIT = 0, RES_GO = 1, RES_ABORT = 2 };
+// Arguments of a resident launch and its closing kernel.
+struct ResLaunch {
+    const RepDesc *descs;
+    RepState *st;
+    const ResJob *jobs;          // workgroup b runs jobs first[b] .. first[b+1]-1
+    const int *first;
+    const ResPlane *planes;
+    const ResRow *rows;
+    const ResRep *reps;
+    int grid, njobs, members, nreps;   // members: cluster workgroups of the grid
+    uint32_t n;                  // sweeps
+    int check_error;             // leave at once if the context's error word is raised (persistent form)
+    ResSync *rs;
+    GridSync *sync;
+    int4 *part;                  // n x njobs sums
+    unsigned long long *mbox;
+};
 
 }  // namespace islf

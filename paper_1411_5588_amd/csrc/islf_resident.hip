@@ -4,16 +4,20 @@
 // sites; between two sweeps nothing travels but the edge rows of the shares.
 //
 // A replica that fits one workgroup is swept by it alone (barriers inside the
-// workgroup only).  A larger one is cut along y into shares of whole rows
-// (ResJob), one workgroup each, which exchange their edge rows after phases 0
-// and 1 through mailboxes in device memory: every 64-bit mailbox word carries
-// 32 spins and the step's epoch and is written and polled with relaxed
-// device-scope atomics, so a word's arrival is its own flag: no fence and no
-// counter stands between an edge word and its reader.  The edge rows are
-// updated first in a phase and the interior rows cover the transfer.
-//  - Two mailbox slots (by phase) are enough: a share writes step k+2 only
-//    after it has read its neighbour's step k+1, which the neighbour wrote
-//    after it had read step k.
+// workgroup only).  A larger one is cut along y and along x (mirrored plane
+// pairs) into shares (ResJob), one workgroup each, which exchange the edges of
+// their shares after phases 0 and 1 through mailboxes in device memory: every
+// 64-bit mailbox word carries 32 spins and the step's epoch and is written and
+// polled with relaxed device-scope atomics, so a word's arrival is its own
+// flag: no fence and no counter stands between an edge word and its reader.
+// Edge rows and planes are updated first in a phase; one wave takes in the
+// mail while the others compute the rest.
+//  - Two mailbox slots (by phase) are enough: a share writes a word of step
+//    k+2 only after it has read its neighbour's step k+1, which the neighbour
+//    wrote after it had read step k (row 0's words in phases 2 and 3 are other
+//    words than the main rows' and follow the same rule).
+//  - No word that arrives in a phase is read in it: an update reads its
+//    neighbours' sublattice that the phase leaves alone.
 //  - The shares of a cluster wait for each other, so they must all be
 //    resident.  Each first reports to a counter and waits (bounded) until all
 //    of the launch's cluster workgroups have; only then does the first sweep
@@ -37,16 +41,31 @@ struct DrawKey {
     uint32_t t, replica, key0, key1;
 };
 
-// A share as the update loop sees it (uniform over the workgroup).  Its
-// lattice in LDS: planes x = -1 .. Lx of R + 2 local rows of 2 Wq words; the
-// planes -1 and Lx stay 0 (a free surface adds nothing to a neighbour count).
+// A column: one word position of one local row, what an update needs of it
+// worked out once per launch.  The table is an array per field (consecutive
+// lanes read consecutive columns: no bank conflicts).
+struct Column {
+    uint32_t at, gy;         // byte offset in its plane (even z); Philox counter part y * gy + 16 w
+    uint32_t flags;          // RW_*, the z edge shift (see share_gather) from bit 8, the local row from bit 16 on
+    uint32_t up, dn;         // steps to the next word round the row, each way
+};
+constexpr int kColumnFields = 7;   // and the column's parts of its mailbox addresses: y (edge rows), x
+
+// A share as the update loop sees it (uniform over the workgroup): its
+// lattice in LDS, planes (slots) of R + 2 local rows of 2 Wq words, followed
+// by the plane, column and mail tables.
 struct Share {
     int Lx, Wq, rem;         // words of a sublattice row, sites of a partial last word (32: none)
-    uint32_t SB, RB, PB;     // LDS bytes of a sublattice row, a local row, an x plane
-    int R, ls, lr0, y0;
+    uint32_t SB, RB, PB;     // LDS bytes of a sublattice row, a local row, a plane
+    int R, ls, lr0, y0, np;
     uint32_t inv;            // seam inversion mask
     bool refl, never, sym;
     uint32_t gx, gy;         // Philox counter steps of x and y
+    const uint4 *pt;         // plane table: slot * PB, x * gx, mirror slot * PB, flags
+    const uint2 *pm;         // mailbox addresses of the planes sent to x neighbours (a second one or ~0)
+    const uint32_t *ct;      // column table: whole words by row, then the rows' partial words
+    int nc;                  // columns
+    const uint32_t *mt;      // mail table: where word k of a slot goes in phase 0 (see mail_target)
 };
 
 // Sums over one thread's flips of a sweep (see bp_march).
@@ -65,6 +84,7 @@ struct ResCtl {
     int acc[2][4];
     unsigned int bad;      // 1 + the first sweep in which a wait ran out, else ~0
     unsigned int state;    // the census' answer; error word at the start
+    int ticket[4];         // next chunk of a phase, by phase number mod 4
 };
 
 __device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c)
@@ -100,33 +120,28 @@ struct Word {
     uint32_t S, b0, b1, b2, own, gq;
 };
 
-// SEAM: the row may be y = 0 or Ly-1.  KIND: all 32 sites of the word exist, w
-// is the partial last word, or either.  All selects are arithmetic (no
-// divergent branches, so that the loads are issued together).
-enum { WORD_WHOLE, WORD_PART, WORD_ANY };
-template <bool SEAM, int KIND>
-__device__ __forceinline__ Word share_gather(const Share &g, const char *lat, int x, int lr, int w, int phase)
+// SEAM: the row may be y = 0 or Ly-1.  WHOLE: all 32 sites of the word exist,
+// else it is the partial last word.  All selects are arithmetic (no divergent
+// branches, so that the loads are issued together).
+template <bool SEAM, bool WHOLE>
+__device__ __forceinline__ Word share_gather(const Share &g, const char *lat, const uint4 &pl, const Column &cl,
+                                             int phase)
 {
-    const int y = SEAM ? share_row_y(g, lr) : lr + (lr > g.ls && g.ls ? -g.lr0 : g.y0 - 1);
-    const uint32_t q = (uint32_t)(phase + x + y) & 1u, qm = 0u - q;
-    const uint32_t row = __umul24((uint32_t)x, g.PB) + (__umul24((uint32_t)lr, g.RB) + g.PB);   // plane -1 comes first
-    const uint32_t at = row + 4u * (uint32_t)w;
+    const uint32_t q = (pl.w ^ cl.flags ^ (uint32_t)phase) & 1u, qm = 0u - q;
+    const uint32_t at = pl.x + cl.at;
     Word o;
     o.own = at + (qm & g.SB);
-    const uint32_t oth = at + (~qm & g.SB);
+    const uint32_t oth = at + (g.SB - (qm & g.SB));
     // the other sublattice one word on: up for odd z, down for even z, round the row's ends
-    const uint32_t last = (uint32_t)g.Wq - 1u;
-    const uint32_t up = (uint32_t)w == last ? 0u - 4u * last : 4u, dn = w == 0 ? 4u * last : 0u - 4u;
-    const uint32_t O = lds32(lat, oth), E = lds32(lat, oth + pick(qm, up, dn));
+    const uint32_t O = lds32(lat, oth), E = lds32(lat, oth + pick(qm, cl.up, cl.dn));
     o.S = lds32(lat, o.own);
     uint32_t ua = o.own + g.RB, da = o.own - g.RB, um = 0u, dm = 0u;
     if (SEAM) {
-        // the seam joins local rows ls (y = Ly-1) and lr0 (y = 0) of planes x and xs
-        const uint32_t xs = g.refl ? (uint32_t)(g.Lx - 1 - x) : (uint32_t)x;
-        const uint32_t col = o.own - row, sx = __umul24(xs, g.PB) + (g.PB + col);
-        const bool su = lr == g.ls, sd = lr == g.lr0;
-        ua = su ? sx + __umul24((uint32_t)g.lr0, g.RB) : ua;
-        da = sd ? sx + __umul24((uint32_t)g.ls, g.RB) : da;
+        // the seam joins local rows ls (y = Ly-1) and lr0 (y = 0) of planes x and, reflected, Lx-1-x
+        const uint32_t sx = o.own - pl.x - (cl.flags >> 16) * g.RB + (g.refl ? pl.z : pl.x);
+        const bool su = (cl.flags & RW_LAST) != 0, sd = (cl.flags & RW_ROW0) != 0;
+        ua = su ? sx + (uint32_t)g.lr0 * g.RB : ua;
+        da = sd ? sx + (uint32_t)g.ls * g.RB : da;
         um = su ? g.inv : 0u;
         dm = sd ? g.inv : 0u;
     }
@@ -134,10 +149,8 @@ __device__ __forceinline__ Word share_gather(const Share &g, const char *lat, in
     const uint32_t xm = lds32(lat, o.own - g.PB), xp = lds32(lat, o.own + g.PB);
     // z neighbour beyond the word: the previous word's top site (the row's
     // last site for w = 0), or the next word's first one
-    const uint32_t Et = E << (w == 0 ? 32 - g.rem : 0);
-    const uint32_t zd = __builtin_amdgcn_alignbit(O, Et, 31);
-    const int top = KIND == WORD_ANY && (uint32_t)w != last ? 31 : g.rem - 1;
-    const uint32_t zu = KIND == WORD_WHOLE ? __builtin_amdgcn_alignbit(E, O, 1) : (O >> 1) | ((E & 1u) << top);
+    const uint32_t zd = __builtin_amdgcn_alignbit(O, E << ((cl.flags >> 8) & 31u), 31);
+    const uint32_t zu = WHOLE ? __builtin_amdgcn_alignbit(E, O, 1) : (O >> 1) | ((E & 1u) << (g.rem - 1));
     const uint32_t Z = pick(qm, zu, zd);
     const uint32_t s1 = xor3(O, Z, ym), c1 = maj3(O, Z, ym);
     const uint32_t s2 = xor3(yp, xm, xp), c2 = maj3(yp, xm, xp);
@@ -145,7 +158,7 @@ __device__ __forceinline__ Word share_gather(const Share &g, const char *lat, in
     o.b0 = s1 ^ s2;
     o.b1 = xor3(c1, c2, k0);
     o.b2 = maj3(c1, c2, k0);
-    o.gq = (uint32_t)x * g.gx + (uint32_t)y * g.gy + 16u * (uint32_t)w + q;
+    o.gq = pl.y + cl.gy + q;
     return o;
 }
 
@@ -265,65 +278,65 @@ __device__ __forceinline__ uint32_t few_flips(const Word &o, int ng, const DrawK
     return F;
 }
 
-// Updates a row set in one phase.  Tasks (words) run x slowest, then row,
-// then word; 64 consecutive tasks are a chunk, chunks go to the waves in turn
-// (`turn` carries the turn from set to set), so that the SIMDs get equal
-// numbers of chunks.  send: the new words of edge rows go to the neighbours'
-// mailboxes.
-template <bool SEAM>
-__device__ __forceinline__ void share_rows(const Share &g, const ResJob &jb, char *lat, const uint4 *quad,
-                                           const uint2 *pair, const uint64_t *thr, const DrawKey &key,
-                                           const ResRows &rs, int phase, bool send, unsigned long long *mbox, uint32_t epoch, int &turn, Sums &a)
+// (a mailbox is below 4 GiB: a uniform base and a 32-bit offset)
+__device__ __forceinline__ void mail_put(unsigned long long *mbox, uint32_t at, unsigned long long v)
 {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    constexpr int W = kResThreads / 64;
-    auto each = [&](auto whole_t) {
-        constexpr bool WHOLE = decltype(whole_t)::value;
-        const int inner = WHOLE ? jb.Wf : 1;
-        const int plane = rs.n * inner;
-        const int T = g.Lx * plane;
-        const int chunks = (T + 63) >> 6;
-        int c = wave - turn;
-        if (c < 0) c += W;
-        for (; c < chunks; c += W) {
-            const int tk = c * 64 + lane;
-            const bool ok = tk < T;
-            const uint32_t tau = (uint32_t)min(tk, T - 1);
-            const uint32_t rest = WHOLE ? div_m(tau, (uint32_t)inner, jb.m_w) : tau;
-            const int w = WHOLE ? (int)(tau - __umul24(rest, (uint32_t)inner)) : jb.Wf;
-            const int x = (int)div_m(rest, (uint32_t)rs.n, rs.m);
-            int lr = rs.base + __mul24((int)rest - __mul24(x, rs.n), rs.stride);
-            if (rs.skip) lr += lr >= rs.skip ? 2 : 0;
-            const Word o = share_gather<SEAM, WHOLE ? WORD_WHOLE : WORD_PART>(g, lat, x, lr, w, phase);
-            // chunks of bulk planes read the bulk table at a fixed base
-            const bool surf = c * 64 < plane || c * 64 + 63 >= T - plane;
-            const bool x0 = x == 0, xl = x == g.Lx - 1;
-            uint32_t F;
-            if (g.sym && !surf) {
-                if (WHOLE) F = bp_flips_quads(o.S, o.b2, o.b1, o.b0, o.gq, key, quad);
-                else F = few_flips<true>(o, jb.ng, key, quad, pair, thr, false);
-            } else {
-                F = few_flips<false>(o, WHOLE ? 8 : jb.ng, key, quad, pair + (x0 ? 256 : xl ? 512 : 0),
-                                     thr + kThrPerClass * ((x0 ? 1 : 0) + (xl ? 2 : 0)), g.never);
-            }
-            if (!WHOLE) F &= (1u << g.rem) - 1u;
-            F = ok ? F : 0u;
-            const uint32_t V = o.S ^ F;
-            if (ok) *(uint32_t *)(lat + o.own) = V;
-            share_sums(o, F, surf, x0, xl, a);
-            if (send && ok) {
-                const unsigned long long v = ((unsigned long long)epoch << 32) | V;
-                const uint32_t at = (uint32_t)(phase * g.Lx + x) * (uint32_t)g.Wq + (uint32_t)w;
-                if (lr == 1)
-                    __hip_atomic_store(mbox + jb.out_off[0] + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (lr == g.R)
-                    __hip_atomic_store(mbox + jb.out_off[1] + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+    gu64 *p = (gu64 *)((gu8 *)mbox + 8u * at);
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Updates chunk c of a row set in one phase: words run planes slowest, then
+// rows, then words of a row, 64 to a chunk.  send: new words of edge rows and
+// edge planes go to the neighbours' mailboxes.
+template <bool SEAM, bool WHOLE>
+__device__ __forceinline__ void share_chunk(const Share &g, const ResJob &jb, char *lat, const ResTables &tb,
+                                            const DrawKey &key, const ResRows &rs, int c, int phase, bool send,
+                                            bool edge_rows, unsigned long long *mbox, uint32_t epoch, Sums &a)
+{
+    const int lane = threadIdx.x & 63;
+    const int plane = WHOLE ? rs.n * jb.Wf : rs.n;
+    const uint32_t m = WHOLE ? rs.m_w : rs.m;
+    const uint32_t *ct = g.ct + (WHOLE ? rs.r0 * jb.Wf : g.R * jb.Wf + rs.r0);
+    const int T = g.np * plane;
+    const int tk = c * 64 + lane;
+    const bool ok = tk < T;
+    const uint32_t tau = (uint32_t)min(tk, T - 1);
+    const uint32_t pi = div_m(tau, (uint32_t)plane, m);
+    const uint32_t *cp = ct + (tau - __umul24(pi, (uint32_t)plane));
+    const Column cl{cp[0], cp[g.nc], cp[2 * g.nc], cp[3 * g.nc], cp[4 * g.nc]};
+    const uint4 pl = g.pt[pi];
+    const Word o = share_gather<SEAM, WHOLE>(g, lat, pl, cl, phase);
+    // chunks of bulk planes read the bulk table at a fixed base
+    const bool surf = c * 64 < jb.n_head * plane || c * 64 + 63 >= T - jb.n_tail * plane;
+    const bool x0 = (pl.w & PL_X0) != 0, xl = (pl.w & PL_XL) != 0;
+    uint32_t F;
+    if (g.sym && !surf) {
+        if (WHOLE) F = bp_flips_quads(o.S, o.b2, o.b1, o.b0, o.gq, key, tb.quad);
+        else F = few_flips<true>(o, jb.ng, key, tb.quad, tb.pair, tb.thr, false);
+    } else {
+        F = few_flips<false>(o, WHOLE ? 8 : jb.ng, key, tb.quad, tb.pair + (x0 ? 256 : xl ? 512 : 0),
+                             tb.thr + kThrPerClass * ((x0 ? 1 : 0) + (xl ? 2 : 0)), g.never);
+    }
+    if (!WHOLE) F &= (1u << g.rem) - 1u;
+    F = ok ? F : 0u;
+    const uint32_t V = o.S ^ F;
+    if (ok) *(uint32_t *)(lat + o.own) = V;
+    share_sums(o, F, surf, x0, xl, a);
+    if (send) {
+        const unsigned long long v = ((unsigned long long)epoch << 32) | V;
+        const uint32_t sl = (phase & 1) ? jb.slot : 0u;
+        if (edge_rows && ok) {
+            const uint32_t ay = cp[5 * g.nc] + __umul24(pi, (uint32_t)g.Wq) + sl;
+            mail_put(mbox, ay, v);
+            if (g.R == 1) mail_put(mbox, ay + (jb.out_y[1] - jb.out_y[0]), v);   // one row is both edges
         }
-        turn = (turn + chunks) & (W - 1);
-    };
-    if (jb.Wf) each(std::true_type{});
-    if (jb.ng) each(std::false_type{});
+        if (c * 64 < jb.n_edge * plane && ok && (int)pi < jb.n_edge) {
+            const uint2 px = g.pm[pi];
+            const uint32_t ax = cp[6 * g.nc] + sl;
+            mail_put(mbox, px.x + ax, v);
+            if (px.y != ~0u) mail_put(mbox, px.y + ax, v);
+        }
+    }
 }
 
 // Small films: one lane per four-site group, so that a phase spreads over all
@@ -343,7 +356,7 @@ struct GroupTask {
     bool on, x0, xl;
 };
 
-__device__ __forceinline__ GroupTask group_task(const Share &g, uint32_t m_c, const ResRows &rs, int tk)
+__device__ __forceinline__ GroupTask group_task(const Share &g, uint32_t m_c, int lr0, const ResRows &rs, int tk)
 {
     const int C = (int)(g.gy >> 1);
     GroupTask t;
@@ -351,7 +364,7 @@ __device__ __forceinline__ GroupTask group_task(const Share &g, uint32_t m_c, co
     const uint32_t k = t.on ? (uint32_t)tk : 0u;
     const uint32_t rest = div_m(k, (uint32_t)C, m_c), gr = k - rest * (uint32_t)C;
     const int x = (int)div_m(rest, (uint32_t)rs.n, rs.m);
-    const int lr = rs.base + ((int)rest - x * rs.n) * rs.stride;
+    const int lr = lr0 + ((int)rest - x * rs.n);
     const int w = (int)(gr >> 3), y = share_row_y(g, lr);
     const int xs = g.refl ? g.Lx - 1 - x : x;
     const bool su = lr == g.ls, sd = lr == g.lr0, lastw = w == g.Wq - 1;
@@ -411,74 +424,121 @@ __device__ __forceinline__ void group_update(const Share &g, const GroupTask &t,
     share_sums(o, F, t.x0 || t.xl, t.x0, t.xl, a);
 }
 
-// Mailbox word k of a phase: words 0 .. n-1 of the lower neighbour's edge row
-// (local row 0 here), then the upper neighbour's (row R+1).
-__device__ __forceinline__ unsigned long long mail(const Share &g, const ResJob &jb, const unsigned long long *mbox,
-                                                   uint32_t epoch, int phase, int k)
+// Halo plane j of a face (0 outer, 1 inner): its slot and its x.
+__device__ __forceinline__ int halo_slot(const ResJob &jb, int face, int j)
 {
-    const int n = g.Lx * g.Wq;
-    const int face = k >= n ? 1 : 0;
-    if (k >= 2 * n) return (unsigned long long)epoch << 32;   // nothing to wait for
-    return __hip_atomic_load(mbox + jb.in_off[face] + (uint32_t)(phase * n + k - face * n), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
+    if (face == 0) return j == 0 ? 0 : jb.n2 ? jb.n1 + jb.n2 + 3 : jb.n1 + 1;
+    return jb.n1 + 1 + j;
+}
+__device__ __forceinline__ int halo_x(const Share &g, const ResJob &jb, int face, int j)
+{
+    if (face == 0) return j == 0 ? jb.xa - 1 : g.Lx - jb.xa;
+    return j == 0 ? jb.xa + jb.n1 : g.Lx - jb.xa - jb.n2 - 1;
 }
 
-// Receives the edge words that both neighbours updated in a phase into local
-// rows 0 and R+1.  Returns false if a wait ran out.
+// Words of a mailbox slot: y faces, then x faces.
+__device__ __forceinline__ int mail_y(const Share &g, const ResJob &jb)
+{
+    return (jb.has & HAS_Y) ? 2 * g.np * g.Wq : 0;
+}
+__device__ __forceinline__ int mail_x(const Share &g, const ResJob &jb)
+{
+    return (((jb.has & HAS_OUTER) ? 2 : 0) + ((jb.has & HAS_INNER) ? 2 : 0)) * g.R * g.Wq;
+}
+
+// Where word k of a slot goes: its byte offset in LDS in the even-z
+// sublattice, bit 0 the parity of x + y (the sublattice that a phase updates
+// is that parity + phase), bit 1 set for row 0 (sent in phases 2 and 3).
+__device__ __forceinline__ uint32_t mail_target(const Share &g, const ResJob &jb, int k)
+{
+    const int n = g.np * g.Wq, RW = g.R * g.Wq, KY = mail_y(g, jb);
+    if (k < KY) {
+        const int face = k >= n ? 1 : 0;
+        const uint32_t kk = (uint32_t)(k - face * n), pi = div_m(kk, (uint32_t)g.Wq, jb.m_q), w = kk - pi * g.Wq;
+        const uint4 pl = g.pt[pi];
+        // the neighbour's row is a main row one below local row 1 or one above local row R
+        const int y = face ? share_row_y(g, g.R) + 1 : g.y0 - 1;
+        return pl.x + (face ? (uint32_t)(g.R + 1) * g.RB : 0u) + 4u * w + ((pl.w ^ (uint32_t)y) & 1u);
+    }
+    uint32_t kk = (uint32_t)(k - KY);
+    const uint32_t f = div_m(kk, (uint32_t)RW, jb.m_f);
+    kk -= f * RW;
+    const uint32_t row = div_m(kk, (uint32_t)g.Wq, jb.m_q);
+    kk -= row * g.Wq;
+    const int face = (jb.has & HAS_OUTER) ? (int)(f >> 1) : 1, j = (int)(f & 1u);
+    const uint32_t par = (uint32_t)(halo_x(g, jb, face, j) + share_row_y(g, (int)row + 1)) & 1u;
+    return (uint32_t)halo_slot(jb, face, j) * g.PB + (row + 1u) * g.RB + 4u * kk + par +
+           ((int)row + 1 == g.lr0 ? 2u : 0u);
+}
+
+// One wave receives the words that the neighbours updated in phase 0 or 1 into
+// the halo rows and planes, or in phases 2 and 3 row 0's words, while the
+// other waves compute (no word that arrives in a phase is read in it).
+// Returns false if a wait ran out.
 __device__ __forceinline__ bool share_receive(const Share &g, const ResJob &jb, char *lat, GridSync *sync,
                                               const unsigned long long *mbox, uint32_t epoch, int phase)
 {
-    const int n = g.Lx * g.Wq;
-    constexpr int B = 4;   // words polled together by a thread
+    const unsigned long long *box = mbox + jb.in + ((phase & 1) ? jb.slot : 0u);
+    const int KY = mail_y(g, jb), K = KY + mail_x(g, jb), lane = threadIdx.x & 63;
+    constexpr int B = 8;   // words a lane polls together
     unsigned spins = 0;
-    for (int k0 = threadIdx.x; k0 < 2 * n; k0 += B * kResThreads) {
-        unsigned long long v[B];
+    for (int k0 = phase < 2 ? 0 : KY; k0 < K; k0 += 64 * B) {
+        uint32_t to[B];
+        bool some = false;
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+            const int k = k0 + 64 * i + lane;
+            to[i] = k < K ? g.mt[k] : ~0u;
+            // row 0 comes in phases 2 and 3, alone
+            if (((to[i] & 2u) != 0) != (phase >= 2)) to[i] = ~0u;
+            some = some || to[i] != ~0u;
+        }
+        if (!__any(some)) continue;
         while (true) {
+            unsigned long long v[B];
             bool all = true;
 #pragma unroll
-            for (int i = 0; i < B; ++i) v[i] = mail(g, jb, mbox, epoch, phase, k0 + i * kResThreads);
+            for (int i = 0; i < B; ++i)
+                v[i] = __hip_atomic_load(box + min(k0 + 64 * i + lane, K - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-            for (int i = 0; i < B; ++i) all = all && (uint32_t)(v[i] >> 32) == epoch;
-            if (all) break;
-            __builtin_amdgcn_s_sleep(1);
+            for (int i = 0; i < B; ++i) {
+                if (to[i] == ~0u) continue;
+                if ((uint32_t)(v[i] >> 32) == epoch) {
+                    *(uint32_t *)(lat + (to[i] & ~3u) + (((to[i] ^ (uint32_t)phase) & 1u) ? g.SB : 0u)) = (uint32_t)v[i];
+                    to[i] = ~0u;
+                } else {
+                    all = false;
+                }
+            }
+            if (__all(all)) break;
+            __builtin_amdgcn_s_sleep(2);
             if ((++spins & 1023u) == 0) {
                 if (__hip_atomic_load(&sync->error.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return false;
                 if (spins > (1u << 21)) {
-                    atomicAdd(&sync->error.v, 1ull);
+                    if (lane == 0) atomicAdd(&sync->error.v, 1ull);
                     return false;
                 }
             }
-        }
-#pragma unroll
-        for (int i = 0; i < B; ++i) {
-            const int k = k0 + i * kResThreads;
-            if (k >= 2 * n) break;
-            const int face = k >= n ? 1 : 0;
-            const int kk = k - face * n;
-            const int x = kk / g.Wq, w = kk - x * g.Wq;
-            const int lr = face ? g.R + 1 : 0;
-            // the neighbour's row is a main row one below local row 1 or one above local row R
-            const int y = face ? share_row_y(g, g.R) + 1 : g.y0 - 1;
-            const int q = (phase + x + y) & 1;
-            *(uint32_t *)(lat + ((uint32_t)(x + 1) * g.PB + (uint32_t)lr * g.RB + (q ? g.SB : 0u) + 4u * (uint32_t)w)) =
-                (uint32_t)v[i];
         }
     }
     return true;
 }
 
-// Moves a share's rows between the replica's spin array and LDS: local rows
-// lo .. hi, LDS word (x, local row, sublattice, word).
+// Moves words between the replica's spin array and LDS: local rows lo .. hi of
+// planes 0 .. np-1 of the plane table (or of the one halo plane given by slot
+// and x), LDS word (plane, local row, sublattice, word).
 template <int FMT, bool LOAD>
-__device__ __forceinline__ void share_move(const Share &g, const RepDesc &d, char *lat, int lo, int hi)
+__device__ __forceinline__ void share_move(const Share &g, const RepDesc &d, const ResPlane *planes, char *lat, int lo,
+                                           int hi, int np, int slot = 0, int hx = 0)
 {
     const int nr = hi - lo + 1, RW = 2 * g.Wq;
-    const int n = g.Lx * nr * RW;
+    const int n = np * nr * RW;
     for (int k = threadIdx.x; k < n; k += kResThreads) {
         const int r = k / RW, c = k - r * RW;
-        const int x = r / nr, lr = lo + (r - x * nr);
+        const int pi = r / nr, lr = lo + (r - pi * nr);
         const int y = share_row_y(g, lr);
-        uint32_t *l = (uint32_t *)(lat + ((uint32_t)(x + 1) * g.PB + (uint32_t)lr * g.RB)) + c;
+        const int x = planes ? planes[pi].x : hx, sl = planes ? planes[pi].slot : slot;
+        uint32_t *l = (uint32_t *)(lat + ((uint32_t)sl * g.PB + (uint32_t)lr * g.RB)) + c;
         const size_t row = (size_t)x * d.Ly + y;
         if (FMT == ISLF_SPIN_BITPACK) {
             uint32_t *p = (uint32_t *)d.spins + row * (size_t)RW + c;
@@ -529,41 +589,45 @@ __device__ __forceinline__ unsigned int res_census(ResSync *rs, unsigned int mem
 // What bounds it: VALU issue (the Philox word and the threshold lookups, as
 // in bp_march).  16 waves per workgroup and one workgroup per CU: a CU's
 // whole LDS is one share, which keeps the edge rows few against the interior
-// (two workgroups of 8 waves per CU: 64 x 40x120x120 25.7 against 23.8 us per
-// sweep, 3 x 160x480x600 97 against 73).  Per sweep, before (launch chain, or
-// persistent kernel) and now: 12x24x24 14 and 3.7 us, 168 ladder films 37 and
-// 3.0 us, 64 x 40x120x120 31 and 23.8 us, 96 uneven films int8 85 and 70 us,
-// 3 x 160x480x600 int8 95 and 75 us, persistent 78 and 74 us.
+// (two workgroups of 8 waves per CU measured 24.3 against 23.4 us per sweep on
+// 64 x 40x120x120 and 85 against 66 on 3 x 160x480x600).  Counters, 3 x
+// 160x480x600: 15.8 VALU lane-ops per update (the launch chain's march 16.2,
+// padding of its 300-bit rows included), VALU issue 89% of the time; without
+// the exchange the same launch takes 57.6 us per sweep instead of 62.0.
+// Per sweep, before (launch chain, or persistent kernel) and now: 12x24x24 14
+// and 3.6 us, 168 ladder films 37 and 3.0 us, 64 x 40x120x120 31 and 22.1 us,
+// 96 uneven films int8 85 and 60 us, 184x504x504 39 and 25.7 us, 3 x
+// 160x480x600 int8 95 and 62 us, persistent 78 and 62 us.
 // SMALL: no clusters, and films of few words, updated one four-site group per
 // lane (share_groups).
 template <int FMT, bool SMALL>
 __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restrict__ descs,
                                                           const RepState *__restrict__ st,
                                                           const ResJob *__restrict__ jobs,
-                                                          const int *__restrict__ first, int njobs, int members,
-                                                          uint32_t n, ResSync *rs, GridSync *sync, int4 *part,
-                                                          unsigned long long *mbox, int check_error)
+                                                          const int *__restrict__ first,
+                                                          const ResPlane *__restrict__ plane_tables,
+                                                          const ResRow *__restrict__ row_tables, const ResLaunch L)
 {
     extern __shared__ uint32_t smem[];
     __shared__ ResTables tb;
     __shared__ ResCtl ctl_s;
     static_assert(sizeof(ResTables) + sizeof(ResCtl) <= kResStaticLds, "the host's LDS budget counts on it");
-    uint2 *pair = tb.pair;
-    uint64_t *thr = tb.thr;
     ResCtl *ctl = &ctl_s;
     char *lat = (char *)smem;
     const int tid = threadIdx.x;
-    if (check_error) {
+    const uint32_t n = L.n;
+    if (L.check_error) {
         if (tid == 0)
-            ctl->state = __hip_atomic_load(&sync->error.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 1u : 0u;
+            ctl->state = __hip_atomic_load(&L.sync->error.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? 1u : 0u;
         __syncthreads();
         if (ctl->state) return;
         __syncthreads();
     }
-    const uint32_t epoch0 = rs->epoch;
+    const uint32_t epoch0 = L.rs->epoch;
     for (int j = first[blockIdx.x]; j < first[blockIdx.x + 1]; ++j) {
         const ResJob &jb = jobs[j];   // uniform: scalar loads where used
         const RepDesc &d = descs[jb.rep];
+        const ResPlane *planes = plane_tables + jb.planes;
         Share g;
         g.Lx = d.Lx; g.Wq = d.Wq;
         g.rem = (d.Lz >> 1) - 32 * (d.Wq - 1);
@@ -571,32 +635,85 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
         g.RB = 2u * g.SB;
         g.PB = (uint32_t)(jb.R + 2) * g.RB;
         g.R = jb.R; g.ls = jb.ls; g.lr0 = jb.lr0; g.y0 = jb.y0;
+        g.np = jb.n1 + jb.n2;
         g.inv = d.seam_invert ? ~0u : 0u;
         g.refl = d.seam_reflect != 0;
         g.never = d.never_mask != 0;
         g.sym = d.sym != 0 && !g.never;
         g.gy = 2u * (uint32_t)d.C;
         g.gx = g.gy * (uint32_t)d.Ly;
+        const int slots = g.np + (jb.n2 ? 4 : 2);
+        uint4 *pt = (uint4 *)(lat + ((uint32_t)slots * g.PB + 15u & ~15u));
+        uint2 *pm = (uint2 *)(pt + g.np);
+        uint32_t *ct = (uint32_t *)(pm + g.np);
+        g.pm = pm;
+        g.nc = g.R * g.Wq;
+        uint32_t *mt = ct + kColumnFields * g.nc;
+        g.pt = pt;
+        g.ct = ct;
+        g.mt = mt;
         DrawKey key{st[jb.rep].t, d.replica, d.key0, d.key1};
-        // tables: three classes' pair tables (a one-layer film has one class), all thresholds
+        // tables: three classes' pair tables (a one-layer film has one class), all thresholds, planes, rows
         for (int k = tid; k < 768; k += kResThreads) {
             const int e = k & 255, cls = g.Lx == 1 ? 3 : k >> 8;
             const int ev = (e & 1) | ((e >> 1) & 2) | ((e >> 2) & 4) | ((e >> 3) & 8);
             const int od = ((e >> 1) & 1) | ((e >> 2) & 2) | ((e >> 3) & 4) | ((e >> 4) & 8);
-            pair[k] = make_uint2(d.thr_m1[cls * kThrPerClass + ev], d.thr_m1[cls * kThrPerClass + od]);
+            tb.pair[k] = make_uint2(d.thr_m1[cls * kThrPerClass + ev], d.thr_m1[cls * kThrPerClass + od]);
         }
         for (int k = tid; k < 256 && g.sym; k += kResThreads) tb.quad[k] = quad_entry(d, k);
-        if (tid < kThrEntries) thr[tid] = d.thr[tid];
+        if (tid < kThrEntries) tb.thr[tid] = d.thr[tid];
         if (tid < 8) (&ctl->acc[0][0])[tid] = 0;
         if (tid == 8) ctl->bad = ~0u;
-        // the planes beyond the free surfaces
-        for (uint32_t k = tid; k < g.PB / 4; k += kResThreads) {
-            ((uint32_t *)lat)[k] = 0u;
-            ((uint32_t *)(lat + (uint32_t)(g.Lx + 1) * g.PB))[k] = 0u;
+        if (tid >= 12 && tid < 16) ctl->ticket[tid - 12] = 0;
+        if (!SMALL) {
+            for (int k = tid; k < g.np; k += kResThreads) {
+                const ResPlane e = planes[k];
+                pt[k] = make_uint4((uint32_t)e.slot * g.PB, (uint32_t)e.x * g.gx, (uint32_t)e.mirror * g.PB,
+                                   (uint32_t)e.flags);
+                // faces it is sent to: outer j = 0, 1, inner j = 0, 1
+                uint32_t to[2] = {~0u, ~0u};
+                int m = 0;
+                for (int f = 0; f < 4; ++f)
+                    if (e.flags & (PL_SEND << f)) {
+                        const uint32_t v = jb.out_x[f >> 1] + (uint32_t)((f & 1) * g.R * g.Wq);
+                        if (m == 0) to[0] = v;
+                        else to[1] = v;
+                        ++m;
+                    }
+                pm[k] = make_uint2(to[0], to[1]);
+            }
+            for (int k = tid; k < g.R * g.Wq; k += kResThreads) {
+                const int ri = k / g.Wq, w = k - ri * g.Wq;
+                const ResRow e = row_tables[jb.rows + ri];
+                uint32_t *c = ct + (w < jb.Wf ? ri * jb.Wf + w : g.R * jb.Wf + ri);
+                c[0] = (uint32_t)e.lr * g.RB + 4u * (uint32_t)w;
+                c[g.nc] = (uint32_t)e.y * g.gy + 16u * (uint32_t)w;
+                c[2 * g.nc] = (uint32_t)e.flags | (w == 0 ? 32u - (uint32_t)g.rem : 0u) << 8 | (uint32_t)e.lr << 16;
+                c[3 * g.nc] = w == g.Wq - 1 ? 0u - 4u * (uint32_t)w : 4u;
+                c[4 * g.nc] = w == 0 ? 4u * (uint32_t)(g.Wq - 1) : 0u - 4u;
+                c[5 * g.nc] = jb.out_y[e.lr == 1 ? 0 : 1] + (uint32_t)w;
+                c[6 * g.nc] = (uint32_t)((e.lr - 1) * g.Wq + w);
+            }
         }
+        // the planes beyond the free surfaces stay 0
+        if (!(jb.has & HAS_OUTER))
+            for (uint32_t k = tid; k < g.PB / 4; k += kResThreads) {
+                ((uint32_t *)lat)[k] = 0u;
+                ((uint32_t *)(lat + (uint32_t)(slots - 1) * g.PB))[k] = 0u;
+            }
         const bool cluster = !SMALL && jb.P > 1;
-        share_move<FMT, true>(g, d, lat, cluster ? 0 : 1, cluster ? g.R + 1 : g.R);
-        if (cluster && tid == 0) ctl->state = res_census(rs, (unsigned)members);
+        const bool has_x = (jb.has & (HAS_OUTER | HAS_INNER)) != 0, has_y = (jb.has & HAS_Y) != 0;
+        share_move<FMT, true>(g, d, planes, lat, has_y ? 0 : 1, has_y ? g.R + 1 : g.R, g.np);
+        if (!SMALL && has_x)
+            for (int f = 0; f < 4; ++f)
+                if (jb.has & ((f >> 1) ? HAS_INNER : HAS_OUTER))
+                    share_move<FMT, true>(g, d, nullptr, lat, 1, g.R, 1, halo_slot(jb, f >> 1, f & 1),
+                                          halo_x(g, jb, f >> 1, f & 1));
+        if (cluster) {
+            __syncthreads();   // the plane table
+            for (int k = tid; k < mail_y(g, jb) + mail_x(g, jb); k += kResThreads) mt[k] = mail_target(g, jb, k);
+        }
+        if (cluster && tid == 0) ctl->state = res_census(L.rs, (unsigned)L.members);
         __syncthreads();
         if (cluster && ctl->state != RES_GO) {
             __syncthreads();
@@ -607,40 +724,74 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
         int main_tasks = 0, row0_tasks = 0;
         if (SMALL) {
             const ResRows &m = jb.set[RES_INNER], &z = jb.set[RES_ROW0];
-            for (int k = 0; k < kSmallTasks; ++k) gt[k] = group_task(g, jb.m_c, m, tid + k * kResThreads);
-            gt0 = group_task(g, jb.m_c, z, tid);
+            for (int k = 0; k < kSmallTasks; ++k) gt[k] = group_task(g, jb.m_c, 2, m, tid + k * kResThreads);
+            gt0 = group_task(g, jb.m_c, 1, z, tid);
             // whole waves without a group skip the phase
             main_tasks = g.Lx * m.n * d.C - (tid & ~63);
             row0_tasks = g.Lx * d.C;
         }
         bool good = true;
-        const int phases = g.lr0 ? 4 : 2;
+        int turn = 0;   // phases so far
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         for (uint32_t s = 0; s < n && good; ++s, ++key.t) {
             Sums a = {0, 0, 0, 0, 0, 0, 0, 0};
-            int turn = 0;
+            if (SMALL) {
 #pragma unroll 1
-            for (int phase = 0; phase < phases; ++phase) {
-                const bool xch = cluster && (phase == 0 || (phase == 1 && s + 1 < n));
-                const uint32_t ep = epoch0 + 2u * s + (uint32_t)phase + 1u;
-                if (SMALL) {
+                for (int phase = 0; phase < 4; ++phase) {
                     if (phase < 2) {
                         for (int k = 0; k < kSmallTasks; ++k)
-                            if (k * kResThreads < main_tasks) group_update(g, gt[k], lat, pair, thr, key, phase, a);
+                            if (k * kResThreads < main_tasks) group_update(g, gt[k], lat, tb.pair, tb.thr, key, phase, a);
                     } else if ((int)(tid & ~63) < row0_tasks) {
-                        group_update(g, gt0, lat, pair, thr, key, phase, a);
+                        group_update(g, gt0, lat, tb.pair, tb.thr, key, phase, a);
                     }
-                } else {
-#pragma unroll 1
-                    for (int k = phase < 2 ? RES_EDGE : RES_ROW0; k <= (phase < 2 ? RES_INNER : RES_ROW0); ++k) {
-                        const ResRows &rs = jb.set[k];
-                        if (rs.n == 0) continue;
-                        const bool send = xch && k == RES_EDGE;
-                        if (rs.seam) share_rows<true>(g, jb, lat, tb.quad, pair, thr, key, rs, phase, send, mbox, ep, turn, a);
-                        else share_rows<false>(g, jb, lat, tb.quad, pair, thr, key, rs, phase, send, mbox, ep, turn, a);
-                    }
-                    if (xch && !share_receive(g, jb, lat, sync, mbox, ep, phase)) atomicMin(&ctl->bad, s + 1u);
+                    if (phase < 3) __syncthreads();
                 }
-                if (phase + 1 < phases) __syncthreads();
+            } else {
+#pragma unroll 1
+                for (int i = 0; i < jb.stages; ++i) {
+                    const ResStage &sg = jb.stage[i];
+                    const uint32_t ep = epoch0 + 4u * s + 1u;   // + phase
+                    // the last wave takes in the mail first (nobody's input after the last sweep: phases 1 and 3)
+                    if (cluster && wave == kResThreads / 64 - 1) {
+                        bool ok = true;
+                        if (sg.mail == 0 || (sg.mail == 1 && s + 1 < n))
+                            ok = share_receive(g, jb, lat, L.sync, L.mbox, ep + (uint32_t)sg.mail, sg.mail);
+                        if (sg.mail_row0 == 2 || (sg.mail_row0 == 3 && s > 0))   // (phase 3's comes a sweep later)
+                            ok = share_receive(g, jb, lat, L.sync, L.mbox, ep + (sg.mail_row0 == 2 ? 2u : 3u - 4u),
+                                               sg.mail_row0) && ok;
+                        if (!ok) atomicMin(&ctl->bad, s + 1u);
+                    }
+                    // chunks go to the waves as they come free
+                    int *ticket = &ctl->ticket[turn & 3];
+                    if (tid == 0) ctl->ticket[(turn + 2) & 3] = 0;   // last used two barriers ago
+                    ++turn;
+                    while (true) {
+                        int c = 0;
+                        if ((tid & 63) == 0) c = atomicAdd(ticket, 1);
+                        c = __builtin_amdgcn_readfirstlane(c);
+                        int k = 0;
+                        while (k < 3 && c >= sg.part[k].c1 - sg.part[k].c0) {
+                            c -= sg.part[k].c1 - sg.part[k].c0;
+                            ++k;
+                        }
+                        if (k == 3) break;
+                        c += sg.part[k].c0;
+                        const int set = sg.part[k].set, phase = sg.part[k].phase;
+                        const ResRows &rs = jb.set[set];
+                        const bool edge = set == RES_EDGE;
+                        const bool send = cluster && (!(phase & 1) || s + 1 < n);
+                        const uint32_t e = ep + (uint32_t)phase;
+                        if (c < rs.whole) {
+                            if (rs.seam) share_chunk<true, true>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
+                            else share_chunk<false, true>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
+                        } else {
+                            c -= rs.whole;
+                            if (rs.seam) share_chunk<true, false>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
+                            else share_chunk<false, false>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
+                        }
+                    }
+                    if (i + 1 < jb.stages) __syncthreads();
+                }
             }
             // the sweep's changes (see bp_march), one LDS add per wave and quantity
             const int dB = -4 * (a.A0 + 2 * a.A1 + 4 * a.A2) + 16 * a.NF - 4 * a.NFU + a.KDM;
@@ -661,13 +812,13 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
             __syncthreads();
             // the other half serves the next sweep, whose barriers order this clear before its reuse
             if (tid == 0) {
-                part[(size_t)s * njobs + jb.id] = make_int4(acc[0], acc[1], acc[2], acc[3]);
+                L.part[(size_t)s * L.njobs + jb.id] = make_int4(acc[0], acc[1], acc[2], acc[3]);
                 acc[0] = acc[1] = acc[2] = acc[3] = 0;
             }
             // (a faster wave may be in sweep s+1 already: its failure counts there)
             good = ctl->bad > s + 1u;
         }
-        if (good) share_move<FMT, false>(g, d, lat, 1, g.R);
+        if (good) share_move<FMT, false>(g, d, planes, lat, 1, g.R, g.np);
         __syncthreads();
     }
 }
@@ -676,19 +827,19 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
 // shares' changes, stores the records and advances the replica; if the launch
 // was aborted, sweeps the cluster replicas here first.
 template <int FMT>
-__global__ __launch_bounds__(kResThreads) void k_resident_close(const RepDesc *__restrict__ descs, RepState *st,
-                                                                const ResRep *__restrict__ reps, int njobs,
-                                                                uint32_t n, ResSync *rs, GridSync *sync, int4 *part,
-                                                                int check_error)
+__global__ __launch_bounds__(kResThreads) void k_resident_close(const ResLaunch L)
 {
     __shared__ long long sum[kResMaxSweeps][4];
     __shared__ uint64_t thr[kThrEntries];
     __shared__ int run;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const ResRep rr = reps[blockIdx.x];
-    const RepDesc &d = descs[rr.rep];
+    const uint32_t n = L.n;
+    ResSync *rs = L.rs;
+    RepState *st = L.st;
+    const ResRep rr = L.reps[blockIdx.x];
+    const RepDesc &d = L.descs[rr.rep];
     if (tid == 0) {
-        const bool err = check_error && __hip_atomic_load(&sync->error.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool err = L.check_error && __hip_atomic_load(&L.sync->error.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         run = err ? 0 : rr.P > 1 && rs->state != RES_GO ? 2 : 1;
     }
     if (tid < kThrEntries) thr[tid] = d.thr[tid];
@@ -734,7 +885,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident_close(const RepDesc *_
         for (uint32_t s = wave; s < n; s += kResThreads / 64) {
             long long v[4] = {0, 0, 0, 0};
             for (int p = lane; p < rr.P; p += 64) {
-                const int4 w = part[(size_t)s * njobs + rr.job0 + p];
+                const int4 w = L.part[(size_t)s * L.njobs + rr.job0 + p];
                 v[0] += w.x; v[1] += w.y; v[2] += w.z; v[3] += w.w;
             }
 #pragma unroll
@@ -787,7 +938,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident_close(const RepDesc *_
             rs->count = 0;
             rs->state = RES_WAIT;
             rs->done = 0;
-            rs->epoch += 2u * n + 2u;
+            rs->epoch += 4u * n + 4u;
         }
     }
 }
@@ -795,19 +946,6 @@ __global__ __launch_bounds__(kResThreads) void k_resident_close(const RepDesc *_
 // ---------------------------------------------------------------------------
 // Host-callable launchers
 // ---------------------------------------------------------------------------
-template <int FMT, bool SMALL>
-static hipError_t launch_resident_as(const RepDesc *descs, RepState *st, const ResJob *jobs, const int *first,
-                                     const ResRep *reps, int grid, int njobs, int members, int nreps, size_t lds,
-                                     uint32_t n, ResSync *rs, GridSync *sync, int4 *part, unsigned long long *mbox,
-                                     int check_error, hipStream_t s)
-{
-    hipLaunchKernelGGL((k_resident<FMT, SMALL>), dim3(grid), dim3(kResThreads), lds, s, descs, st, jobs, first, njobs,
-                       members, n, rs, sync, part, mbox, check_error);
-    hipLaunchKernelGGL(k_resident_close<FMT>, dim3(nreps), dim3(kResThreads), 0, s, descs, st, reps, njobs, n, rs,
-                       sync, part, check_error);
-    return hipGetLastError();
-}
-
 // Lets the kernels use `bytes` of dynamic LDS.
 hipError_t resident_lds_limit(int fmt, size_t bytes)
 {
@@ -821,15 +959,19 @@ hipError_t resident_lds_limit(int fmt, size_t bytes)
     return e;
 }
 
-hipError_t launch_resident(int fmt, bool small, const RepDesc *descs, RepState *st, const ResJob *jobs,
-                           const int *first, const ResRep *reps, int grid, int njobs, int members, int nreps,
-                           size_t lds, uint32_t n, ResSync *rs, GridSync *sync, int4 *part, unsigned long long *mbox,
-                           int check_error, hipStream_t s)
+hipError_t launch_resident(int fmt, bool small, const ResLaunch &L, size_t lds, hipStream_t s)
 {
-    auto f = fmt == ISLF_SPIN_INT8
-                 ? (small ? launch_resident_as<ISLF_SPIN_INT8, true> : launch_resident_as<ISLF_SPIN_INT8, false>)
-                 : (small ? launch_resident_as<ISLF_SPIN_BITPACK, true> : launch_resident_as<ISLF_SPIN_BITPACK, false>);
-    return f(descs, st, jobs, first, reps, grid, njobs, members, nreps, lds, n, rs, sync, part, mbox, check_error, s);
+    const dim3 g(L.grid), gr(L.nreps), b(kResThreads);
+    if (fmt == ISLF_SPIN_INT8) {
+        if (small) hipLaunchKernelGGL((k_resident<ISLF_SPIN_INT8, true>), g, b, lds, s, L.descs, L.st, L.jobs, L.first, L.planes, L.rows, L);
+        else hipLaunchKernelGGL((k_resident<ISLF_SPIN_INT8, false>), g, b, lds, s, L.descs, L.st, L.jobs, L.first, L.planes, L.rows, L);
+        hipLaunchKernelGGL(k_resident_close<ISLF_SPIN_INT8>, gr, b, 0, s, L);
+    } else {
+        if (small) hipLaunchKernelGGL((k_resident<ISLF_SPIN_BITPACK, true>), g, b, lds, s, L.descs, L.st, L.jobs, L.first, L.planes, L.rows, L);
+        else hipLaunchKernelGGL((k_resident<ISLF_SPIN_BITPACK, false>), g, b, lds, s, L.descs, L.st, L.jobs, L.first, L.planes, L.rows, L);
+        hipLaunchKernelGGL(k_resident_close<ISLF_SPIN_BITPACK>, gr, b, 0, s, L);
+    }
+    return hipGetLastError();
 }
 
 }  // namespace islf

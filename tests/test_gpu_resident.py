@@ -34,7 +34,8 @@ SHAPES = [
     (1, 2, 2), (2, 2, 4), (1, 3, 64), (3, 4, 66), (5, 7, 62),            # tiny: one row beside the seam, one layer
     (12, 24, 24), (8, 12, 12), (16, 16, 64), (7, 43, 58),                # one lane per group, up to the last lane
     (30, 40, 64), (30, 41, 62), (9, 60, 128), (13, 33, 130),             # words, one workgroup
-    (20, 64, 76), (16, 150, 130), (40, 120, 120), (21, 333, 66),         # shares
+    (20, 64, 76), (16, 150, 130), (40, 120, 120), (21, 333, 66),         # shares along y
+    (61, 50, 70), (80, 200, 160), (37, 24, 190), (90, 9, 250),           # and along x
 ]
 
 
