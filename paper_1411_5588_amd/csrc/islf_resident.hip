@@ -753,6 +753,10 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
                     const uint32_t ep = epoch0 + 4u * s + 1u;   // + phase
                     // the last wave takes in the mail first (nobody's input after the last sweep: phases 1 and 3)
                     if (cluster && wave == kResThreads / 64 - 1) {
+                        // Ahead of the computing waves of its SIMD: its few instructions stand between one load latency
+                        // and the next, and at their priority it waited for three waves of Philox in between. The
+                        // 3.6 M site film, 1,720 words a sweep: 62.8 -> 61.7 us a sweep; 0.9 M sites 25.8 -> 24.7.
+                        __builtin_amdgcn_s_setprio(3);
                         bool ok = true;
                         if (sg.mail == 0 || (sg.mail == 1 && s + 1 < n))
                             ok = share_receive(g, jb, lat, L.sync, L.mbox, ep + (uint32_t)sg.mail, sg.mail);
@@ -760,6 +764,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
                             ok = share_receive(g, jb, lat, L.sync, L.mbox, ep + (sg.mail_row0 == 2 ? 2u : 3u - 4u),
                                                sg.mail_row0) && ok;
                         if (!ok) atomicMin(&ctl->bad, s + 1u);
+                        __builtin_amdgcn_s_setprio(0);
                     }
                     // chunks go to the waves as they come free
                     int *ticket = &ctl->ticket[turn & 3];
