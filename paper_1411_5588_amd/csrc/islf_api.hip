@@ -31,11 +31,12 @@ hipError_t launch_persistent(int fmt, const RepDesc *descs, RepState *st, const 
 hipError_t launch_persistent_teams(int fmt, const RepDesc *descs, RepState *st, const Entry *items, const int *first,
                                    const TeamInfo *teams, uint32_t nsweeps, GridSync *sync, SyncLine *rsync,
                                    int n_rsync, int grid, hipStream_t s);
-hipError_t launch_init(int fmt, const RepDesc *descs, int rep, int mode, const int8_t *host, hipStream_t s);
-hipError_t launch_export(const RepDesc *descs, int rep, long rows, int8_t *out, hipStream_t s);
-hipError_t launch_recompute(const RepDesc *descs, int rep, long rows, const int8_t *spins, unsigned long long *out,
+hipError_t launch_init(int fmt, const RepDesc *descs, RepState *st, int rep, int mode, long n, hipStream_t s);
+hipError_t launch_import(int fmt, const RepDesc *descs, RepState *st, int rep, int Lz, long n, const int8_t *host,
+                         hipStream_t s);
+hipError_t launch_export(int fmt, const RepDesc *descs, int rep, int Lz, long n, int8_t *out, hipStream_t s);
+hipError_t launch_recompute(int fmt, const RepDesc *descs, RepState *st, int rep, long n, unsigned long long *out,
                             hipStream_t s);
-hipError_t launch_set_state(RepState *st, int rep, const unsigned long long *obs, uint32_t t, hipStream_t s);
 hipError_t launch_layer_profile(const RepDesc *descs, int rep, long rows, long words_per_row, int32_t *out,
                                 long long *acc, hipStream_t s);
 hipError_t launch_zero(unsigned long long *p, long n, hipStream_t s);
@@ -1479,22 +1480,22 @@ static hipError_t enqueue_resident(islf_ctx *c, uint32_t n)
     return e;
 }
 
-// init spins + initial observables of slot i (synchronises)
+// Rows times 16-site columns: what the kernels over all spins of a replica are sized by.
+static long host_columns(const islf_replica_desc &d)
+{
+    return (long)d.Lx * d.Ly * ((d.Lz + 15) / 16);
+}
+
+// Spins of slot i (host_staged, or by init mode) and their observables (synchronises).
 static islf_status init_replica(islf_ctx *c, int i, int mode, const int8_t *host_staged)
 {
     Replica &R = c->reps[i];
+    const long n = host_columns(R.desc);
     HIP_TRY(hipMemcpyAsync(c->d_desc + i, &R.d, sizeof(RepDesc), hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(launch_zero((unsigned long long *)R.d.acc, 2 * kAccSlots * 4, c->stream));
-    HIP_TRY(launch_init(c->fmt, c->d_desc, i, mode, host_staged, c->stream));
-    const size_t N = (size_t)R.desc.Lx * R.desc.Ly * R.desc.Lz;
-    int8_t *tmp = (int8_t *)dev_alloc(c, N);
-    if (!tmp) return fail(ISLF_ENOMEM, "cannot allocate %zu bytes of staging", N);
-    hipError_t e = launch_export(c->d_desc, i, (long)R.desc.Lx * R.desc.Ly, tmp, c->stream);
-    if (e == hipSuccess)
-        e = launch_recompute(c->d_desc, i, (long)R.desc.Lx * R.desc.Ly, tmp, c->d_scratch, c->stream);
-    if (e == hipSuccess) e = launch_set_state(c->d_state, i, c->d_scratch, 0u, c->stream);
+    if (host_staged) HIP_TRY(launch_import(c->fmt, c->d_desc, c->d_state, i, R.desc.Lz, n, host_staged, c->stream));
+    else HIP_TRY(launch_init(c->fmt, c->d_desc, c->d_state, i, mode, n, c->stream));
+    hipError_t e = launch_recompute(c->fmt, c->d_desc, c->d_state, i, n, nullptr, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    dev_free(c, tmp);
     if (e != hipSuccess) return fail(ISLF_EDEVICE, "replica init failed: %s", hipGetErrorString(e));
     R.t_host = 0;
     return ISLF_OK;
@@ -1748,7 +1749,7 @@ extern "C" islf_status islf_set_spins(islf_ctx *ctx, int32_t rep, const int8_t *
         dev_free(ctx, staged);
         return fail(ISLF_EDEVICE, "copy of host spins failed: %s", hipGetErrorString(e));
     }
-    st = init_replica(ctx, rep, 3, staged);
+    st = init_replica(ctx, rep, ISLF_INIT_HOST, staged);
     dev_free(ctx, staged);
     if (st == ISLF_OK && R.failed) {
         R.failed = false;
@@ -1768,7 +1769,7 @@ extern "C" islf_status islf_get_spins(islf_ctx *ctx, int32_t rep, int8_t *host, 
     if (st != ISLF_OK) return st;
     int8_t *tmp = (int8_t *)dev_alloc(ctx, N);
     if (!tmp) return fail(ISLF_ENOMEM, "cannot allocate staging");
-    hipError_t e = launch_export(ctx->d_desc, rep, (long)R.desc.Lx * R.desc.Ly, tmp, ctx->stream);
+    hipError_t e = launch_export(ctx->fmt, ctx->d_desc, rep, R.desc.Lz, host_columns(R.desc), tmp, ctx->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(host, tmp, N, hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     dev_free(ctx, tmp);
@@ -2036,16 +2037,11 @@ extern "C" islf_status islf_recompute(islf_ctx *ctx, int32_t rep, islf_obs *out)
     st = check_intact(ctx, rep);
     if (st != ISLF_OK) return st;
     const Replica &R = ctx->reps[rep];
-    const size_t N = (size_t)R.desc.Lx * R.desc.Ly * R.desc.Lz;
-    int8_t *tmp = (int8_t *)dev_alloc(ctx, N);
-    if (!tmp) return fail(ISLF_ENOMEM, "cannot allocate staging");
     unsigned long long h[4];
-    hipError_t e = launch_export(ctx->d_desc, rep, (long)R.desc.Lx * R.desc.Ly, tmp, ctx->stream);
-    if (e == hipSuccess)
-        e = launch_recompute(ctx->d_desc, rep, (long)R.desc.Lx * R.desc.Ly, tmp, ctx->d_scratch, ctx->stream);
+    hipError_t e = launch_recompute(ctx->fmt, ctx->d_desc, ctx->d_state, rep, host_columns(R.desc), ctx->d_scratch,
+                                    ctx->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(h, ctx->d_scratch, sizeof h, hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    dev_free(ctx, tmp);
     if (e != hipSuccess) return fail(ISLF_EDEVICE, "recompute failed: %s", hipGetErrorString(e));
     out->B = (int64_t)h[0];
     out->M = (int64_t)h[1];

@@ -244,11 +244,6 @@ __device__ __forceinline__ void i8_update_col(const RepView &v, int x, int y, in
 // bit-packed format: update one 32-bit word (32 same-phase sites).
 // Row layout: words [0, Wq) hold even z (z = 2i), words [Wq, 2Wq) odd z.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t bp_bit(const uint32_t *sub, int i)
-{
-    return (sub[i >> 5] >> (i & 31)) & 1u;
-}
-
 template <bool COH>
 __device__ __forceinline__ void bp_update_word(const RepView &v, int x, int y, int w, int parity,
                                                const uint64_t *sthr, Acc &a)

@@ -21,6 +21,7 @@
 // Both formats draw the same Philox word for the same site, so they give the
 // same Markov chain.
 #include <mutex>
+#include <type_traits>
 
 #include "islf_device.h"
 
@@ -870,11 +871,26 @@ __global__ __launch_bounds__(kBlock, persistent_min_blocks(FMT)) void k_persiste
 // ---------------------------------------------------------------------------
 // Initial states and format conversion.
 // mode 0: random (Philox domain 1, t = 0; +1 iff the word's top bit is 0),
-// mode 1: all up, 2: all down, 3: from staged host spins (int8 +-1, host layout).
+// mode 1: all up, 2: all down.  Every kernel that sets spins also starts the
+// replica's state anew: sums, sweep count and observables, to which the
+// recompute that follows adds.
 // ---------------------------------------------------------------------------
-__global__ void k_init_i8(const RepDesc *__restrict__ descs, int rep, int mode, const int8_t *__restrict__ host)
+__device__ __forceinline__ void start_state(const RepDesc &d, RepState &st)
+{
+    if (blockIdx.x != 0) return;
+    unsigned long long *acc = (unsigned long long *)d.acc;
+    for (int i = threadIdx.x; i < 2 * kAccSlots * 4; i += blockDim.x) acc[i] = 0;
+    if (threadIdx.x == 0) {
+        for (int k = 0; k < 4; ++k) st.cur[k] = 0;
+        st.t = 0;
+        st.live = 1;
+    }
+}
+
+__global__ void k_init_i8(const RepDesc *__restrict__ descs, RepState *__restrict__ st, int rep, int mode)
 {
     const RepDesc &d = descs[rep];
+    start_state(d, st[rep]);
     const int Lzh = d.Lz >> 1;
     // one 8-byte column (row, sublattice q, column k) per step: sites z = 2i + q, i = 8k .. 8k+7
     const long ncol = (long)d.Lx * d.Ly * 2 * d.K;
@@ -896,17 +912,15 @@ __global__ void k_init_i8(const RepDesc *__restrict__ descs, int rep, int mode, 
             }
         } else if (mode == 1) {
             for (int b = 0; b < nv; ++b) W |= 1ull << (8 * b);
-        } else if (mode == 3) {
-            const int8_t *src = host + row * d.Lz + q;
-            for (int b = 0; b < nv; ++b) W |= (uint64_t)(src[2 * (8 * k + b)] > 0 ? 1u : 0u) << (8 * b);
         }
         *(uint64_t *)(d.spins + (size_t)row * d.RB + (size_t)q * d.Hp + 8 * k) = W;
     }
 }
 
-__global__ void k_init_bp(const RepDesc *__restrict__ descs, int rep, int mode, const int8_t *__restrict__ host)
+__global__ void k_init_bp(const RepDesc *__restrict__ descs, RepState *__restrict__ st, int rep, int mode)
 {
     const RepDesc &d = descs[rep];
+    start_state(d, st[rep]);
     const int nbits = d.Lz >> 1;
     const long nw = (long)d.Lx * d.Ly * 2 * d.Wq;
     uint32_t *words = (uint32_t *)d.spins;
@@ -916,103 +930,181 @@ __global__ void k_init_bp(const RepDesc *__restrict__ descs, int rep, int mode, 
         const int q = rem / d.Wq, w = rem - q * d.Wq;
         const int nb_here = min(32, nbits - 32 * w);
         uint32_t S = 0;
-        for (int b = 0; b < nb_here; ++b) {
-            const int i = 32 * w + b;
-            uint32_t u;
-            if (mode == 0) {
-                uint32_t rnd[4];
-                const uint32_t g = (((uint32_t)(row * d.C + (i >> 2))) << 1) | (uint32_t)q;
-                philox10(g, 0u, d.replica, 1u, d.key0, d.key1, rnd);
-                u = 1u - (rnd[i & 3] >> 31);
-            } else if (mode == 1) {
-                u = 1;
-            } else if (mode == 2) {
-                u = 0;
-            } else {
-                u = host[row * d.Lz + 2 * i + q] > 0 ? 1u : 0u;
-            }
-            S |= u << b;
+        if (mode == 1) S = ~0u >> (32 - nb_here);
+        for (int b = 0; mode == 0 && b < nb_here; b += 4) {   // a group: four sites (22 M sites: 47 -> 17 us)
+            uint32_t rnd[4];
+            const uint32_t g = (((uint32_t)(row * d.C + ((32 * w + b) >> 2))) << 1) | (uint32_t)q;
+            philox10(g, 0u, d.replica, 1u, d.key0, d.key1, rnd);
+            for (int l = 0; l < 4; ++l)
+                if (b + l < nb_here) S |= (1u - (rnd[l] >> 31)) << (b + l);
         }
         words[k] = S;
     }
 }
 
-// Internal format -> host layout int8 +-1.
-__global__ void k_export(const RepDesc *__restrict__ descs, int rep, int8_t *__restrict__ out)
+// ---------------------------------------------------------------------------
+// Host layout (int8 +-1, z fastest) <-> internal format.  A lane moves 16 sites
+// of a row: one 8-site column of either sublattice, so that the host side is
+// one run of 16 bytes.  A = the width every row's start is aligned to (1, 2, 4
+// or 16 bytes: Lz need only be even); the copy is made in pieces of A bytes.
+// ---------------------------------------------------------------------------
+typedef uint32_t HostVec __attribute__((ext_vector_type(4)));
+
+template <int A>
+struct HostRun {
+    using T = typename std::conditional<A == 16, HostVec, typename std::conditional<
+        A == 4, uint32_t, typename std::conditional<A == 2, uint16_t, uint8_t>::type>::type>::type;
+    union {
+        T part[16 / A];
+        uint32_t w[4];
+    };
+    __device__ __forceinline__ void load(const int8_t *p, int n)
+    {
+#pragma unroll
+        for (int i = 0; i < 16 / A; ++i)
+            if (A == 16 || i * A < n) part[i] = ((const T *)p)[i];
+    }
+    __device__ __forceinline__ void store(int8_t *p, int n) const
+    {
+#pragma unroll
+        for (int i = 0; i < 16 / A; ++i)
+            if (A == 16 || i * A < n) ((T *)p)[i] = part[i];
+    }
+};
+
+// 8-site columns of a sublattice row that are stored (whole 32-bit words of the bit-packed format)
+__device__ __forceinline__ int stored_columns(const RepDesc &d)
+{
+    return d.fmt == ISLF_SPIN_INT8 ? d.K : 4 * d.Wq;
+}
+
+// Internal format -> host layout.  Memory: 1 + 1 (or 1 + 1/8) bytes a site.
+// 88 x 504 x 504 int8 (22 M sites): 13 us, 3.4 TB/s; one lane a site took 28 us.
+template <int FMT, int A>
+__global__ __launch_bounds__(kBlock) void k_export(const RepDesc *__restrict__ descs, int rep,
+                                                   int8_t *__restrict__ out)
 {
     const RepDesc &d = descs[rep];
-    const int Lz = d.Lz;
-    // a workgroup takes whole rows (x, y); the lanes run along z
-    for (int r = blockIdx.x; r < d.Lx * d.Ly; r += gridDim.x) {
-        int8_t *o = out + (size_t)r * (size_t)Lz;
-        if (d.fmt == ISLF_SPIN_INT8) {
-            const uint8_t *src = d.spins + (size_t)r * d.RB;
-            for (int z = threadIdx.x; z < Lz; z += blockDim.x)
-                o[z] = src[(z & 1) * d.Hp + (z >> 1)] ? (int8_t)1 : (int8_t)-1;
+    const uint32_t nh = (uint32_t)d.Lz >> 1, nk = (nh + 7) >> 3, n = (uint32_t)d.Lx * (uint32_t)d.Ly * nk;
+    for (uint32_t c = blockIdx.x * kBlock + threadIdx.x; c < n; c += gridDim.x * kBlock) {
+        const uint32_t row = c / nk, k = c - row * nk;
+        HostRun<A> r;
+        if (FMT == ISLF_SPIN_INT8) {
+            const uint8_t *p = d.spins + (size_t)row * d.RB + 8 * k;
+            const uint2 e = *(const uint2 *)p, o = *(const uint2 *)(p + d.Hp);
+            r.w[0] = __builtin_amdgcn_perm(o.x, e.x, 0x05010400u);
+            r.w[1] = __builtin_amdgcn_perm(o.x, e.x, 0x07030602u);
+            r.w[2] = __builtin_amdgcn_perm(o.y, e.y, 0x05010400u);
+            r.w[3] = __builtin_amdgcn_perm(o.y, e.y, 0x07030602u);
         } else {
-            const uint32_t *row = (const uint32_t *)d.spins + (size_t)r * 2 * d.Wq;
-            for (int z = threadIdx.x; z < Lz; z += blockDim.x)
-                o[z] = bp_bit(row + (size_t)(z & 1) * d.Wq, z >> 1) ? (int8_t)1 : (int8_t)-1;
+            const uint8_t *p = d.spins + (size_t)row * 8 * d.Wq + k;
+            const uint32_t e = p[0], o = p[4 * d.Wq];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                // bits 2i, 2i+1 of either, one to a byte, even sublattice first
+                const uint32_t e2 = (e >> (2 * i)) & 3u, o2 = (o >> (2 * i)) & 3u;
+                r.w[i] = ((e2 | e2 << 15) | (o2 << 8 | o2 << 23)) & 0x01010101u;
+            }
+        }
+        // 1 -> +1, 0 -> -1
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t down = r.w[i] ^ 0x01010101u;
+            r.w[i] |= (down << 8) - down;
+        }
+        r.store(out + (size_t)row * (uint32_t)d.Lz + 16 * k, (int)min(16u, (uint32_t)d.Lz - 16 * k));
+    }
+}
+
+// Host layout -> internal format (the values are known to be +-1); starts the
+// state.  22 M int8 sites: 12 us; one byte load a site took 30 us.
+template <int FMT, int A>
+__global__ __launch_bounds__(kBlock) void k_import(const RepDesc *__restrict__ descs, RepState *__restrict__ st,
+                                                   int rep, const int8_t *__restrict__ host)
+{
+    const RepDesc &d = descs[rep];
+    start_state(d, st[rep]);
+    const uint32_t nk = (uint32_t)stored_columns(d), n = (uint32_t)d.Lx * (uint32_t)d.Ly * nk;
+    for (uint32_t c = blockIdx.x * kBlock + threadIdx.x; c < n; c += gridDim.x * kBlock) {
+        const uint32_t row = c / nk, k = c - row * nk;
+        HostRun<A> r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r.w[i] = 0xFFFFFFFFu;   // past the row's end: no spin
+        const int left = d.Lz - 16 * (int)k;
+        if (left > 0) r.load(host + (size_t)row * (uint32_t)d.Lz + 16 * k, min(16, left));
+        uint2 e, o;
+        e.x = __builtin_amdgcn_perm(r.w[1], r.w[0], 0x06040200u);
+        e.y = __builtin_amdgcn_perm(r.w[3], r.w[2], 0x06040200u);
+        o.x = __builtin_amdgcn_perm(r.w[1], r.w[0], 0x07050301u);
+        o.y = __builtin_amdgcn_perm(r.w[3], r.w[2], 0x07050301u);
+        e.x = ~(e.x >> 7) & 0x01010101u;
+        e.y = ~(e.y >> 7) & 0x01010101u;
+        o.x = ~(o.x >> 7) & 0x01010101u;
+        o.y = ~(o.y >> 7) & 0x01010101u;
+        if (FMT == ISLF_SPIN_INT8) {
+            uint8_t *p = d.spins + (size_t)row * d.RB + 8 * k;
+            *(uint2 *)p = e;
+            *(uint2 *)(p + d.Hp) = o;
+        } else {
+            // byte b of a word to bit b: the bits meet in the top byte
+            uint8_t *p = d.spins + (size_t)row * 8 * d.Wq + k;
+            p[0] = (uint8_t)((e.x * 0x01020408u) >> 24 | ((e.y * 0x01020408u) >> 24) << 4);
+            p[4 * d.Wq] = (uint8_t)((o.x * 0x01020408u) >> 24 | ((o.y * 0x01020408u) >> 24) << 4);
         }
     }
 }
 
 // ---------------------------------------------------------------------------
 // Full recompute of (B, M, M1, Mn): each site counts its three forward slots.
-// Works on the host-layout export so that it is one code for both formats.
+// A lane takes a word of either sublattice of a row (2 x 32 sites bit-packed,
+// 2 x 8 int8) with the words one row and one plane on, and counts the unlike
+// pairs: of n bonds, u unlike, the sum is n - 2u.  Reads the spins three times,
+// two of them from L2.  88 x 504 x 504 int8 (22 M sites): 13 us (bit-packed
+// 8 us); by way of a host-layout copy, one lane a site, export and sums took 93 us.
+// Adds to out (the replica's observables in st if out is null).
 // ---------------------------------------------------------------------------
-__global__ void k_recompute(const RepDesc *__restrict__ descs, int rep, const int8_t *__restrict__ s,
-                            unsigned long long *__restrict__ out)
+constexpr int kSumBlock = 1024;
+
+template <int FMT>
+__global__ __launch_bounds__(kSumBlock) void k_recompute(const RepDesc *__restrict__ descs, RepState *__restrict__ st,
+                                                      int rep, unsigned long long *__restrict__ out)
 {
+    using W = typename std::conditional<FMT == ISLF_SPIN_INT8, uint64_t, uint32_t>::type;
+    constexpr int SITES = FMT == ISLF_SPIN_INT8 ? 8 : 32;      // sites of a word
+    constexpr int STEP = FMT == ISLF_SPIN_INT8 ? 8 : 1;        // bits of a site
     const RepDesc &d = descs[rep];
-    const int Lx = d.Lx, Ly = d.Ly, Lz = d.Lz;
-    const uint32_t plane = (uint32_t)Ly * (uint32_t)Lz;
+    const uint32_t Lx = d.Lx, Ly = d.Ly, nh = (uint32_t)d.Lz >> 1, nw = (nh + SITES - 1) / SITES;
+    const uint32_t n = Lx * Ly * nw;
+    const size_t row_b = FMT == ISLF_SPIN_INT8 ? (size_t)d.RB : (size_t)8 * d.Wq;
+    const size_t half_b = FMT == ISLF_SPIN_INT8 ? (size_t)d.Hp : (size_t)4 * d.Wq;
     const int sg = d.seam_invert ? -1 : 1;
-    // a workgroup takes whole rows (x, y), four at a time so that each lane
-    // has the loads of four rows in flight: x and y are uniform, the lanes
-    // run along z (coalesced), and offsets fit 32 bits (a replica is below
-    // 4 GiB)
-    int B = 0, M = 0, M1 = 0, Mn = 0;
-    const int rows = Lx * Ly;
-    for (int r0 = 4 * (int)blockIdx.x; r0 < rows; r0 += 4 * (int)gridDim.x) {
-        // per row (uniform): offset, y-neighbour row offset and sign, x+1 plane
-        uint32_t ro[4], yo[4];
-        int ys[4], xp[4], ok[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int r = min(r0 + k, rows - 1);
-            const int x = r / Ly, y = r - x * Ly;
-            ok[k] = r0 + k < rows;
-            ro[k] = (uint32_t)r * (uint32_t)Lz;
-            yo[k] = y < Ly - 1 ? ro[k] + (uint32_t)Lz : (uint32_t)((d.seam_reflect ? Lx - 1 - x : x) * Ly) * Lz;
-            ys[k] = y < Ly - 1 ? 1 : sg;
-            xp[k] = x < Lx - 1;
-        }
-        int b[4] = {0, 0, 0, 0}, m[4] = {0, 0, 0, 0};
-        for (int z = threadIdx.x; z < Lz; z += blockDim.x) {
-            const int zn = z + 1 == Lz ? 0 : z + 1;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                if (!ok[k]) break;
-                const int si = s[ro[k] + z];
-                int bb = si * s[ro[k] + zn] + ys[k] * si * s[yo[k] + z];
-                if (xp[k]) bb += si * s[ro[k] + plane + z];
-                b[k] += bb;
-                m[k] += si;
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (!ok[k]) break;
-            const int x = (r0 + k) / Ly;
-            B += b[k];
-            M += m[k];
-            if (x == 0) M1 += m[k];
-            if (x == Lx - 1) Mn += m[k];
-        }
+    long long B = 0, M = 0, M1 = 0, Mn = 0;
+    for (uint32_t c = blockIdx.x * kSumBlock + threadIdx.x; c < n; c += gridDim.x * kSumBlock) {
+        const uint32_t row = c / nw, w = c - row * nw;
+        const uint32_t x = row / Ly, y = row - x * Ly;
+        const bool seam = y + 1 == Ly;
+        const uint32_t yrow = !seam ? row + 1 : (d.seam_reflect ? Lx - 1 - x : x) * Ly;
+        const uint8_t *p = d.spins + row * row_b, *py = d.spins + yrow * row_b;
+        const uint8_t *px = x + 1 < Lx ? p + Ly * row_b : p;   // no bond past the last plane: no pair is unlike
+        const int ns = min(SITES, (int)(nh - SITES * w));
+        const W ones = FMT == ISLF_SPIN_INT8 ? (W)0x0101010101010101ull : (W)~(W)0;
+        const W mask = ones >> (STEP * (SITES - ns));
+        auto word = [&](const uint8_t *r, uint32_t i) { return ((const W *)r)[i]; };
+        auto count = [&](W v) { return FMT == ISLF_SPIN_INT8 ? __popcll(v & mask) : __popc((uint32_t)(v & mask)); };
+        const W s0 = word(p, w) & mask, s1 = word(p + half_b, w) & mask;
+        const W nx = word(p, w + 1 < nw ? w + 1 : 0u) & 1u;
+        const W s0n = (s0 >> STEP) | (nx << (STEP * (ns - 1)));
+        const int uz = count(s0 ^ s1) + count(s1 ^ s0n);
+        const int uy = count(s0 ^ word(py, w)) + count(s1 ^ word(py + half_b, w));
+        const int ux = count(s0 ^ word(px, w)) + count(s1 ^ word(px + half_b, w));
+        const int m = 2 * (count(s0) + count(s1) - ns);
+        B += 2 * (ns - uz) + (seam ? sg : 1) * 2 * (ns - uy) + (x + 1 < Lx ? 2 * (ns - ux) : 0);
+        M += m;
+        if (x == 0) M1 += m;
+        if (x + 1 == Lx) Mn += m;
     }
     long long v[4] = {B, M, M1, Mn};
-    __shared__ long long red[4][kBlock / 64];
+    __shared__ long long red[4][kSumBlock / 64];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
 #pragma unroll
@@ -1024,12 +1116,11 @@ __global__ void k_recompute(const RepDesc *__restrict__ descs, int rep, const in
     __syncthreads();
     if (threadIdx.x < 4) {
         long long acc = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) acc += red[threadIdx.x][w];
-        atomicAdd(&out[threadIdx.x], (unsigned long long)acc);
+        for (int w = 0; w < kSumBlock / 64; ++w) acc += red[threadIdx.x][w];
+        atomicAdd((out ? out : (unsigned long long *)st[rep].cur) + threadIdx.x, (unsigned long long)acc);
     }
 }
 
-// Sets the running observables of a replica (after init / set_spins).
 // Layer profile (Sec. II.B, Eq. 17): for every row (x, y) of replica rep,
 // P = sum over z of its spins, written to out (int32) or, if out is NULL,
 // added to acc (int64).  A workgroup owns R whole rows (R * words per row <=
@@ -1081,15 +1172,6 @@ __global__ __launch_bounds__(256) void k_layer_profile(const RepDesc *__restrict
         const int32_t P = 2 * (int32_t)cnt[k] - Lz;
         if (out) out[r0 + k] = P;
         else acc[r0 + k] += P;
-    }
-}
-
-__global__ void k_set_state(RepState *st, int rep, const unsigned long long *obs, uint32_t t)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        for (int k = 0; k < 4; ++k) st[rep].cur[k] = (long long)obs[k];
-        st[rep].t = t;
-        st[rep].live = 1;
     }
 }
 
@@ -1304,30 +1386,76 @@ hipError_t launch_persistent_teams(int fmt, const RepDesc *descs, RepState *st, 
     return hipLaunchCooperativeKernel(persistent_teams_kernel(fmt), dim3(grid), dim3(kBlock), args, 0, s);
 }
 
-hipError_t launch_init(int fmt, const RepDesc *descs, int rep, int mode, const int8_t *host, hipStream_t s)
+// Workgroups for n lanes, at most `most` (the kernels stride over the rest).
+static unsigned lanes_grid(long n, long most)
 {
+    return (unsigned)std::max(1L, std::min((n + kBlock - 1) / kBlock, most));
+}
+
+// The width in bytes that every row of the host layout at p is aligned to.
+static int host_align(const void *p, int Lz)
+{
+    const uintptr_t v = (uintptr_t)p | (uintptr_t)Lz;
+    return !(v & 15) ? 16 : !(v & 3) ? 4 : !(v & 1) ? 2 : 1;
+}
+
+// mode 0, 1, 2: as k_init; starts the state.  n = rows times 16-site columns, here
+// and below.
+hipError_t launch_init(int fmt, const RepDesc *descs, RepState *st, int rep, int mode, long n, hipStream_t s)
+{
+    const dim3 grid(lanes_grid(2 * n, 1024)), block(kBlock);
+    if (fmt == ISLF_SPIN_INT8) hipLaunchKernelGGL(k_init_i8, grid, block, 0, s, descs, st, rep, mode);
+    else hipLaunchKernelGGL(k_init_bp, grid, block, 0, s, descs, st, rep, mode);
+    return hipGetLastError();
+}
+
+template <int FMT>
+static void import_export(const RepDesc *descs, RepState *st, int rep, int align, bool in, int8_t *host, unsigned grid,
+                          hipStream_t s)
+{
+    auto go = [&](auto a) {
+        constexpr int A = decltype(a)::value;
+        if (in) hipLaunchKernelGGL((k_import<FMT, A>), dim3(grid), dim3(kBlock), 0, s, descs, st, rep, host);
+        else hipLaunchKernelGGL((k_export<FMT, A>), dim3(grid), dim3(kBlock), 0, s, descs, rep, host);
+    };
+    if (align == 16) go(std::integral_constant<int, 16>());
+    else if (align == 4) go(std::integral_constant<int, 4>());
+    else if (align == 2) go(std::integral_constant<int, 2>());
+    else go(std::integral_constant<int, 1>());
+}
+
+hipError_t launch_import(int fmt, const RepDesc *descs, RepState *st, int rep, int Lz, long n, const int8_t *host,
+                         hipStream_t s)
+{
+    const int a = host_align(host, Lz);
     if (fmt == ISLF_SPIN_INT8)
-        hipLaunchKernelGGL(k_init_i8, dim3(1024), dim3(kBlock), 0, s, descs, rep, mode, host);
+        import_export<ISLF_SPIN_INT8>(descs, st, rep, a, true, (int8_t *)host, lanes_grid(n, 1L << 16), s);
+    else import_export<ISLF_SPIN_BITPACK>(descs, st, rep, a, true, (int8_t *)host, lanes_grid(n, 1L << 16), s);
+    return hipGetLastError();
+}
+
+hipError_t launch_export(int fmt, const RepDesc *descs, int rep, int Lz, long n, int8_t *out, hipStream_t s)
+{
+    const int a = host_align(out, Lz);
+    if (fmt == ISLF_SPIN_INT8)
+        import_export<ISLF_SPIN_INT8>(descs, nullptr, rep, a, false, out, lanes_grid(n, 1L << 16), s);
+    else import_export<ISLF_SPIN_BITPACK>(descs, nullptr, rep, a, false, out, lanes_grid(n, 1L << 16), s);
+    return hipGetLastError();
+}
+
+// out = the observables, or added to the replica's freshly started state if
+// null.  At most 256 workgroups of 1024: each ends with four atomics on the
+// same four words, which serialise (1,024 workgroups of 256: 21 us for 22 M int8 sites, 13 us so).
+hipError_t launch_recompute(int fmt, const RepDesc *descs, RepState *st, int rep, long n, unsigned long long *out,
+                            hipStream_t s)
+{
+    if (out) hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, out, 4L);
+    const long lanes = fmt == ISLF_SPIN_INT8 ? n : (n + 3) / 4;
+    const dim3 grid((unsigned)std::max(1L, std::min((lanes + kSumBlock - 1) / kSumBlock, 256L))), block(kSumBlock);
+    if (fmt == ISLF_SPIN_INT8)
+        hipLaunchKernelGGL((k_recompute<ISLF_SPIN_INT8>), grid, block, 0, s, descs, st, rep, out);
     else
-        hipLaunchKernelGGL(k_init_bp, dim3(1024), dim3(kBlock), 0, s, descs, rep, mode, host);
-    return hipGetLastError();
-}
-
-hipError_t launch_export(const RepDesc *descs, int rep, long rows, int8_t *out, hipStream_t s)
-{
-    const unsigned grid = (unsigned)std::max(1L, std::min(rows, 1L << 20));
-    hipLaunchKernelGGL(k_export, dim3(grid), dim3(kBlock), 0, s, descs, rep, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_recompute(const RepDesc *descs, int rep, long rows, const int8_t *spins,
-                            unsigned long long *out, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, s, out, 4L);
-    // at most 1024 workgroups: each ends with four atomics on the same four
-    // words, which serialise when there are many more
-    const unsigned grid = (unsigned)std::max(1L, std::min((rows + 3) / 4, 1024L));
-    hipLaunchKernelGGL(k_recompute, dim3(grid), dim3(kBlock), 0, s, descs, rep, spins, out);
+        hipLaunchKernelGGL((k_recompute<ISLF_SPIN_BITPACK>), grid, block, 0, s, descs, st, rep, out);
     return hipGetLastError();
 }
 
@@ -1340,12 +1468,6 @@ hipError_t launch_layer_profile(const RepDesc *descs, int rep, long rows, long w
     const long R = rw >= kProfileWords ? 1 : kProfileWords / rw;
     const long grid = (rows + R - 1) / R;
     hipLaunchKernelGGL(k_layer_profile, dim3((unsigned int)grid), dim3(256), 0, s, descs, rep, out, acc);
-    return hipGetLastError();
-}
-
-hipError_t launch_set_state(RepState *st, int rep, const unsigned long long *obs, uint32_t t, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_set_state, dim3(1), dim3(64), 0, s, st, rep, obs, t);
     return hipGetLastError();
 }
 
