@@ -754,8 +754,8 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
                     // the last wave takes in the mail first (nobody's input after the last sweep: phases 1 and 3)
                     if (cluster && wave == kResThreads / 64 - 1) {
                         // Ahead of the computing waves of its SIMD: its few instructions stand between one load latency
-                        // and the next, and at their priority it waited for three waves of Philox in between. The
-                        // 3.6 M site film, 1,720 words a sweep: 62.8 -> 61.7 us a sweep; 0.9 M sites 25.8 -> 24.7.
+                        // and the next, and at their priority it waited for three waves of Philox in between.
+                        // Three films of 46 M sites, 1,720 words a sweep: 62.8 -> 61.7 us a sweep; one 25.8 -> 24.7.
                         __builtin_amdgcn_s_setprio(3);
                         bool ok = true;
                         if (sg.mail == 0 || (sg.mail == 1 && s + 1 < n))
