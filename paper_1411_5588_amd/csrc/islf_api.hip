@@ -11,7 +11,11 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
+#include <atomic>
+#include <map>
 #include <string>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -32,9 +36,12 @@ hipError_t launch_persistent_teams(int fmt, const RepDesc *descs, RepState *st, 
                                    const TeamInfo *teams, uint32_t nsweeps, GridSync *sync, SyncLine *rsync,
                                    int n_rsync, int grid, hipStream_t s);
 hipError_t launch_init(int fmt, const RepDesc *descs, RepState *st, int rep, int mode, long n, hipStream_t s);
-hipError_t launch_import(int fmt, const RepDesc *descs, RepState *st, int rep, int Lz, long n, const int8_t *host,
-                         hipStream_t s);
-hipError_t launch_export(int fmt, const RepDesc *descs, int rep, int Lz, long n, int8_t *out, hipStream_t s);
+hipError_t launch_import(int fmt, const RepDesc *descs, RepState *st, int rep, int Lz, uint32_t c0, uint32_t c1,
+                         size_t h0, const int8_t *host, hipStream_t s);
+hipError_t launch_export(int fmt, const RepDesc *descs, int rep, int Lz, uint32_t c0, uint32_t c1, size_t h0,
+                         int8_t *out, hipStream_t s);
+hipError_t launch_fetch(const unsigned long long *error, const void *ring, long first, long n, long size,
+                        unsigned long long *host, hipStream_t s);
 hipError_t launch_recompute(int fmt, const RepDesc *descs, RepState *st, int rep, long n, unsigned long long *out,
                             hipStream_t s);
 hipError_t launch_layer_profile(const RepDesc *descs, int rep, long rows, long words_per_row, int32_t *out,
@@ -237,6 +244,16 @@ struct ResPlan {
     double sweep_us = 0.0, fixed_us = 0.0, chain_us = 0.0;   // expected: per sweep, per launch; a sweep of the launch chain
 };
 
+// A number of shares worth taking for a film: fewer are slower.
+struct ShareChoice {
+    int P, px, py;
+    double us;
+};
+
+constexpr size_t kMaxShapes = 256;
+constexpr long kResultWords = 8192;            // 64 KiB of results
+constexpr size_t kWindow = 2u << 20;           // bytes of spins per window
+
 struct islf_ctx {
     int fmt = 0;
     uint32_t cap = 0;
@@ -268,6 +285,12 @@ struct islf_ctx {
     int rsync_cap = 0;
     int team_mode = -1;        // 1: team barriers when every live replica can have a workgroup; 0: grid; -1: automatic
     unsigned long long *d_scratch = nullptr;   // 64 x u64
+    // what calls bring back, in pinned memory: word 0 the error word, results
+    // from word 8 on; and two windows for spins too many for it (made by the
+    // first call with such spins)
+    unsigned long long *h_res = nullptr;
+    int8_t *h_win = nullptr;
+    hipEvent_t win_event[2] = {};
     int *d_live = nullptr;                      // live replica ids
     int live_capacity = 0;
     Plan batched, persistent;
@@ -296,12 +319,14 @@ struct islf_ctx {
     uint32_t graph_sweeps = 0;
     bool graph_valid = false;
 
+    // the cuts of the shapes planned so far (kMaxShapes at most)
+    std::map<std::array<int, 3>, std::vector<ShareChoice>> choices;
+
     // device bytes the context holds, by allocation
     std::unordered_map<void *, size_t> alloc_bytes;
     size_t dev_bytes = 0;
 };
 
-static islf_status check_intact(islf_ctx *c, int rep);
 static islf_status check_none_failed(const islf_ctx *c);
 
 static void *dev_alloc(islf_ctx *c, size_t bytes)
@@ -444,6 +469,17 @@ static void build_work(Replica &R, int rep_id, int fmt)
     for (int p0 = 0; p0 < P; p0 += sl.np)
         for (int j0 = 0; j0 < J; j0 += sl.nj)
             R.slab.push_back(Entry{rep_id, p0, std::min(sl.np, P - p0), j0, std::min(sl.nj, J - j0), ITEM_SLAB});
+}
+
+// The number of entries that build_work makes.
+static size_t work_entries(const islf_replica_desc &d, const I8Shape &s, int fmt)
+{
+    const int J = (int)columns_of(d, fmt), rows = std::max(0, d.Ly - 3);
+    const SlabShape sl = slab_shape(d, fmt);
+    const size_t main = (size_t)ceil_div(d.Lx, s.mx) *
+                        (s.tj == 0 ? (size_t)ceil_div((long)rows * J, kBlock)
+                                   : (size_t)ceil_div(rows, s.ty) * (size_t)ceil_div(J, s.tj));
+    return main + (size_t)ceil_div((d.Lx + 1) / 2, sl.np) * (size_t)ceil_div(J, sl.nj);
 }
 
 static void fill_desc(Replica &R, int fmt, uint32_t cap)
@@ -672,8 +708,9 @@ static islf_status sync_tables(islf_ctx *c)
     }
     if (!c->live.empty())
         HIP_TRY(hipMemcpyAsync(c->d_live, c->live.data(), sizeof(int) * c->live.size(), hipMemcpyHostToDevice, c->stream));
-    for (int i : c->live)
-        HIP_TRY(hipMemcpyAsync(c->d_desc + i, &c->reps[i].d, sizeof(RepDesc), hipMemcpyHostToDevice, c->stream));
+    std::vector<RepDesc> all(n);
+    for (int i = 0; i < n; ++i) all[i] = c->reps[i].d;
+    if (n) HIP_TRY(hipMemcpyAsync(c->d_desc, all.data(), sizeof(RepDesc) * n, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     c->batched.valid = false;
     c->persistent.valid = false;
@@ -1015,12 +1052,6 @@ struct ShareCost {
     }
 };
 
-// A number of shares worth taking for a film: fewer are slower.
-struct ShareChoice {
-    int P, px, py;
-    double us;
-};
-
 // The useful cuts of a film into at most NW shares, by number of shares.  A cut
 // into more has to be 3% faster: below that the films of 100,000 to 350,000
 // sites, whose stages cost much the same at 4 shares as at 24, were cut fine
@@ -1237,26 +1268,22 @@ static void cut_film(const islf_replica_desc &d, int rep, int px, int py, bool s
 // least work (they wait for nobody, so a workgroup may hold several).  The
 // target time per sweep that sets the shares is scanned for the shortest
 // launch.  Returns false if the replicas do not fit.
-static bool plan_resident(const islf_ctx *c, const std::vector<int> &reps, ResPlan &p, ResTablesHost &h)
+static bool plan_resident(islf_ctx *c, const std::vector<int> &reps, ResPlan &p, ResTablesHost &h)
 {
     const int n = (int)reps.size(), NW = c->num_cu;
     // replicas of one shape share their choices
-    std::vector<std::vector<ShareChoice>> shapes;
-    std::vector<int> shape(n), example;
-    std::unordered_map<unsigned long long, int> known;
+    if (c->choices.size() > kMaxShapes) c->choices.clear();
+    std::vector<const std::vector<ShareChoice> *> shape(n);
     double total = 0.0;
     for (int i = 0; i < n; ++i) {
         const islf_replica_desc &d = c->reps[reps[i]].desc;
         if (d.Lx > 32000 || d.Ly > 32000) return false;   // 16-bit table entries
-        const unsigned long long key = ((unsigned long long)d.Lx << 48) ^ ((unsigned long long)d.Ly << 32) ^ (unsigned)d.Lz;
-        auto it = known.find(key);
-        if (it == known.end()) {
-            it = known.emplace(key, (int)shapes.size()).first;
-            shapes.push_back(share_choices(d, NW));
-            if (shapes.back().empty()) return false;
-        }
-        shape[i] = it->second;
-        const ShareChoice &f = shapes[shape[i]].front();
+        const std::array<int, 3> key = {d.Lx, d.Ly, d.Lz};
+        auto it = c->choices.find(key);
+        if (it == c->choices.end()) it = c->choices.emplace(key, share_choices(d, NW)).first;
+        if (it->second.empty()) return false;
+        shape[i] = &it->second;
+        const ShareChoice &f = shape[i]->front();
         total += f.P * f.us;
     }
     std::vector<const ShareChoice *> pick(n), best_pick;
@@ -1293,7 +1320,7 @@ static bool plan_resident(const islf_ctx *c, const std::vector<int> &reps, ResPl
         long used = 0;
         for (int i = 0; i < n; ++i) {
             // the fewest shares within T, else the fastest cut
-            const std::vector<ShareChoice> &v = shapes[shape[i]];
+            const std::vector<ShareChoice> &v = *shape[i];
             size_t q = 0;
             while (q + 1 < v.size() && v[q].us > T) ++q;
             pick[i] = &v[q];
@@ -1484,27 +1511,63 @@ static hipError_t enqueue_resident(islf_ctx *c, uint32_t n)
     return e;
 }
 
+// Acts on the persistent kernel's error word, fetched to h_res.  A raised word
+// means a launch gave up at a grid barrier and left its sweeps half done, so
+// every live replica is marked failed (its calls return ESTATE until
+// islf_set_spins restarts it or it is retired); the word is then cleared so
+// that later launches can run.  With rep >= 0, that replica's chain has to be
+// intact too.
+static islf_status take_error(islf_ctx *c, int rep)
+{
+    if (c->h_res[0]) {
+        for (int r : c->live) c->reps[r].failed = true;
+        c->graph_valid = false;
+        HIP_TRY(launch_zero((unsigned long long *)&c->d_sync->error, 16, c->stream));
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        return fail(ISLF_EDEVICE, "a persistent-kernel grid barrier gave up (its workgroups were not all resident at "
+                                  "once, or the wait was cut short); every live replica is marked failed");
+    }
+    if (rep >= 0 && c->reps[rep].failed)
+        return fail(ISLF_ESTATE, "replica %d was cut short by a failed persistent launch (restart it with "
+                                 "islf_set_spins or retire it)", rep);
+    return ISLF_OK;
+}
+
+// The error word, and with it n 64-bit words of the ring of `size` at `ring`
+// from word `first` on (n <= kResultWords; to h_res + 8), by one kernel and one
+// wait: each copy from device memory to pageable memory took 15 us, and a
+// second wait came with the error word (one record: 41 us, 12 us so).
+static islf_status fetch(islf_ctx *c, int rep, const void *ring = nullptr, long first = 0, long n = 0, long size = 1)
+{
+    HIP_TRY(launch_fetch(&c->d_sync->error.v, ring, first, n, size, c->h_res, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    return take_error(c, rep);
+}
+
+static islf_status check_device_error(islf_ctx *c) { return fetch(c, -1); }
+
+// A live replica whose chain is intact: checks the device error word, then
+// the replica's failed mark.
+static islf_status check_intact(islf_ctx *c, int rep) { return fetch(c, rep); }
+
 // Rows times 16-site columns: what the kernels over all spins of a replica are sized by.
 static long host_columns(const islf_replica_desc &d)
 {
     return (long)d.Lx * d.Ly * ((d.Lz + 15) / 16);
 }
 
-// Spins of slot i (host_staged, or by init mode) and their observables (synchronises).
-static islf_status init_replica(islf_ctx *c, int i, int mode, const int8_t *host_staged)
+// Spins of slot i by its init mode, and their observables (its descriptor is on the device).
+static hipError_t start_replica(islf_ctx *c, int i)
 {
     Replica &R = c->reps[i];
     const long n = host_columns(R.desc);
-    HIP_TRY(hipMemcpyAsync(c->d_desc + i, &R.d, sizeof(RepDesc), hipMemcpyHostToDevice, c->stream));
-    if (host_staged) HIP_TRY(launch_import(c->fmt, c->d_desc, c->d_state, i, R.desc.Lz, n, host_staged, c->stream));
-    else HIP_TRY(launch_init(c->fmt, c->d_desc, c->d_state, i, mode, n, c->stream));
-    hipError_t e = launch_recompute(c->fmt, c->d_desc, c->d_state, i, n, nullptr, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) return fail(ISLF_EDEVICE, "replica init failed: %s", hipGetErrorString(e));
+    const int mode = R.desc.init == ISLF_INIT_HOST ? ISLF_INIT_UP : R.desc.init;
     R.t_host = 0;
-    return ISLF_OK;
+    const hipError_t e = launch_init(c->fmt, c->d_desc, c->d_state, i, mode, n, c->stream);
+    return e != hipSuccess ? e : launch_recompute(c->fmt, c->d_desc, c->d_state, i, n, nullptr, c->stream);
 }
 
+// A slot with memory and tables for a replica; start_replica sets its spins.
 static islf_status add_replica(islf_ctx *c, const islf_replica_desc *desc, int *slot_out)
 {
     islf_status st = validate(desc);
@@ -1537,9 +1600,6 @@ static islf_status add_replica(islf_ctx *c, const islf_replica_desc *desc, int *
     R.tile_set = false;
     fill_desc(R, c->fmt, c->cap);
     build_work(R, slot, c->fmt);
-    const int mode = desc->init == ISLF_INIT_HOST ? ISLF_INIT_UP : desc->init;
-    st = init_replica(c, slot, mode, nullptr);
-    if (st != ISLF_OK) return st;
     R.live = true;
     c->dirty = true;
     *slot_out = slot;
@@ -1570,6 +1630,10 @@ static void destroy_ctx(islf_ctx *c)
     dev_free(c, c->d_teams);
     dev_free(c, c->d_rsync);
     dev_free(c, c->d_scratch);
+    if (c->h_res) (void)hipHostFree(c->h_res);
+    if (c->h_win) (void)hipHostFree(c->h_win);
+    for (hipEvent_t ev : c->win_event)
+        if (ev) (void)hipEventDestroy(ev);
     dev_free(c, c->d_live);
     free_plan(c, c->batched);
     free_plan(c, c->persistent);
@@ -1659,7 +1723,8 @@ extern "C" islf_status islf_create_with_allocator(const islf_replica_desc *reps,
     c->d_sync = (GridSync *)dev_alloc(c, sizeof(GridSync));
     c->d_scratch = (unsigned long long *)dev_alloc(c, 64 * sizeof(unsigned long long));
     c->d_rsy = (ResSync *)dev_alloc(c, sizeof(ResSync));
-    if (!c->d_sync || !c->d_scratch || !c->d_rsy) {
+    if (hipHostMalloc((void **)&c->h_res, 8 * (8 + kResultWords), hipHostMallocCoherent) != hipSuccess) c->h_res = nullptr;
+    if (!c->d_sync || !c->d_scratch || !c->d_rsy || !c->h_res) {
         destroy_ctx(c);
         return fail(ISLF_ENOMEM, "cannot allocate context buffers");
     }
@@ -1668,17 +1733,16 @@ extern "C" islf_status islf_create_with_allocator(const islf_replica_desc *reps,
         destroy_ctx(c);
         return fail(ISLF_EDEVICE, "cannot clear sync words");
     }
-    for (int i = 0; i < n_reps; ++i) {
+    islf_status st = ensure_slots(c, n_reps);
+    for (int i = 0; i < n_reps && st == ISLF_OK; ++i) {
         int slot;
-        islf_status st = add_replica(c, &reps[i], &slot);
-        if (st != ISLF_OK) {
-            std::string keep = g_err;
-            destroy_ctx(c);
-            g_err = keep;
-            return st;
-        }
+        st = add_replica(c, &reps[i], &slot);
     }
-    islf_status st = sync_tables(c);
+    if (st == ISLF_OK) st = sync_tables(c);
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < n_reps && st == ISLF_OK && e == hipSuccess; ++i) e = start_replica(c, i);
+    if (st == ISLF_OK && e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess) st = fail(ISLF_EDEVICE, "replica init failed: %s", hipGetErrorString(e));
     if (st != ISLF_OK) {
         std::string keep = g_err;
         destroy_ctx(c);
@@ -1727,6 +1791,160 @@ extern "C" islf_status islf_get_desc(const islf_ctx *ctx, int32_t rep, islf_repl
     return ISLF_OK;
 }
 
+// Threads that copy or check host spins with the calling one, for the length of
+// a call.  One thread copies 16 to 27 GB/s here, the link carries 57: 22 M sites
+// set in 1050 and read in 1270 us by pageable copies, 890 and 740 us so.
+class Crew {
+public:
+    explicit Crew(size_t bytes)
+    {
+        const int most = (int)std::min(4u, std::thread::hardware_concurrency() / 2);
+        if (bytes < 2 * kWindow) return;   // starting threads costs as much as they would save
+        try {
+            for (int i = 1; i < most; ++i) threads_.emplace_back([this, i] { work(i); });
+        } catch (...) {
+            // those that started do it
+        }
+    }
+    ~Crew()
+    {
+        stop_ = true;
+        turn_.fetch_add(1, std::memory_order_release);
+        for (std::thread &t : threads_) t.join();
+    }
+    Crew(const Crew &) = delete;
+    Crew &operator=(const Crew &) = delete;
+    // copies n bytes (dst may be null), or with check_ looks for bytes that are
+    // neither +1 nor -1; true if there are any
+    bool run(int8_t *dst, const int8_t *src, size_t n, bool check)
+    {
+        dst_ = dst;
+        src_ = src;
+        n_ = n;
+        check_ = check;
+        parts_ = (int)threads_.size() + 1;
+        bad_.store(0, std::memory_order_relaxed);
+        left_.store((int)threads_.size(), std::memory_order_relaxed);
+        turn_.fetch_add(1, std::memory_order_release);
+        part(0);
+        while (left_.load(std::memory_order_acquire)) std::this_thread::yield();
+        return bad_.load(std::memory_order_relaxed) != 0;
+    }
+
+private:
+    void part(int i)
+    {
+        const size_t step = round_up((n_ + parts_ - 1) / parts_, 4096), a = std::min(n_, i * step);
+        const size_t m = std::min(n_ - a, step);
+        if (!check_) {
+            memcpy(dst_ + a, src_ + a, m);
+            return;
+        }
+        // +1 and -1 are the bytes 0x01 and 0xFF: (byte + 1) & 0xFD is 0 exactly
+        // for them (a branch-free pass the compiler vectorises)
+        uint8_t bad = 0;
+        const uint8_t *p = (const uint8_t *)src_ + a;
+        for (size_t k = 0; k < m; ++k) bad |= (uint8_t)(p[k] + 1u) & 0xFDu;
+        if (bad) bad_.store(1, std::memory_order_relaxed);
+    }
+    void work(int i)
+    {
+        for (unsigned seen = 0;;) {
+            for (int spins = 0; turn_.load(std::memory_order_acquire) == seen;)
+                if (++spins > 256) std::this_thread::yield();
+            ++seen;
+            if (stop_) return;
+            part(i);
+            left_.fetch_sub(1, std::memory_order_release);
+        }
+    }
+    std::vector<std::thread> threads_;
+    std::atomic<unsigned> turn_{0};
+    std::atomic<int> left_{0}, bad_{0};
+    int8_t *dst_ = nullptr;
+    const int8_t *src_ = nullptr;
+    size_t n_ = 0;
+    int parts_ = 1;
+    bool check_ = false, stop_ = false;
+};
+
+// Moves the host layout of a replica through pinned memory: by way of h_res
+// where it fits, else window by window, the threads' copy of one beside the
+// transfer and kernel of the other.  With `out`, the error word comes first and
+// nothing is written to host when it is raised.
+static islf_status move_spins(islf_ctx *c, int rep, int8_t *host, bool out, Crew &crew)
+{
+    const Replica &R = c->reps[rep];
+    const int Lz = R.desc.Lz, K = (Lz + 15) / 16;
+    const long n = host_columns(R.desc);
+    const size_t N = (size_t)R.desc.Lx * R.desc.Ly * Lz;
+    auto at = [&](long col) { return (size_t)(col / K) * Lz + (size_t)(16 * (col % K)); };   // host byte of a column
+    if (out) HIP_TRY(launch_fetch(&c->d_sync->error.v, nullptr, 0, 0, 1, c->h_res, c->stream));
+    if (N <= 8 * (size_t)kResultWords) {
+        int8_t *p = (int8_t *)(c->h_res + 8);
+        if (!out) {
+            memcpy(p, host, N);
+            HIP_TRY(launch_import(c->fmt, c->d_desc, c->d_state, rep, Lz, 0, (uint32_t)n, 0, p, c->stream));
+            return ISLF_OK;
+        }
+        HIP_TRY(launch_export(c->fmt, c->d_desc, rep, Lz, 0, (uint32_t)n, 0, p, c->stream));
+        HIP_TRY(hipStreamSynchronize(c->stream));
+        const islf_status st = take_error(c, rep);
+        if (st == ISLF_OK) memcpy(host, p, N);
+        return st;
+    }
+    for (hipEvent_t &ev : c->win_event)
+        if (!ev) HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    if (!c->h_win && hipHostMalloc((void **)&c->h_win, 2 * kWindow, hipHostMallocDefault) != hipSuccess) {
+        c->h_win = nullptr;
+        return fail(ISLF_ENOMEM, "cannot allocate staging");
+    }
+    int8_t *dev = (int8_t *)dev_alloc(c, 2 * kWindow);
+    if (!dev) return fail(ISLF_ENOMEM, "cannot allocate staging");
+    const long per = (long)(kWindow / 16), wins = (n + per - 1) / per;
+    hipError_t e = hipSuccess;
+    islf_status st = ISLF_OK;
+    auto start = [&](long w) {   // device side of window w
+        const long c0 = w * per, c1 = std::min(n, c0 + per);
+        const size_t h0 = at(c0), bytes = (c1 == n ? N : at(c1)) - h0;
+        int8_t *d = dev + (w & 1) * kWindow, *p = c->h_win + (w & 1) * kWindow;
+        if (out) {
+            e = launch_export(c->fmt, c->d_desc, rep, Lz, (uint32_t)c0, (uint32_t)c1, h0, d, c->stream);
+            if (e == hipSuccess) e = hipMemcpyAsync(p, d, bytes, hipMemcpyDeviceToHost, c->stream);
+        } else {
+            e = hipMemcpyAsync(d, p, bytes, hipMemcpyHostToDevice, c->stream);
+            if (e == hipSuccess)
+                e = launch_import(c->fmt, c->d_desc, c->d_state, rep, Lz, (uint32_t)c0, (uint32_t)c1, h0, d, c->stream);
+        }
+        if (e == hipSuccess) e = hipEventRecord(c->win_event[w & 1], c->stream);
+    };
+    auto copy = [&](long w) {    // host side of window w
+        const size_t h0 = at(w * per), bytes = (w + 1 == wins ? N : at((w + 1) * per)) - h0;
+        int8_t *p = c->h_win + (w & 1) * kWindow;
+        if (out) crew.run(host + h0, p, bytes, false);
+        else crew.run(p, host + h0, bytes, false);
+    };
+    if (out) start(0);
+    for (long w = 0; w < wins && e == hipSuccess && st == ISLF_OK; ++w) {
+        if (out) {
+            if (w + 1 < wins) start(w + 1);
+            if (e == hipSuccess) e = hipEventSynchronize(c->win_event[w & 1]);
+            if (e == hipSuccess && w == 0) st = take_error(c, rep);
+            if (e == hipSuccess && st == ISLF_OK) copy(w);
+        } else {
+            if (w >= 2) e = hipEventSynchronize(c->win_event[w & 1]);
+            if (e != hipSuccess) break;
+            copy(w);
+            start(w);
+        }
+    }
+    const hipError_t es = hipStreamSynchronize(c->stream);
+    dev_free(c, dev);
+    if (e == hipSuccess) e = es;
+    if (e != hipSuccess) return fail(ISLF_EDEVICE, "copy of spins failed: %s", hipGetErrorString(e));
+    return st;
+}
+
 extern "C" islf_status islf_set_spins(islf_ctx *ctx, int32_t rep, const int8_t *host, size_t n)
 {
     islf_status st = check_rep(ctx, rep);
@@ -1736,49 +1954,33 @@ extern "C" islf_status islf_set_spins(islf_ctx *ctx, int32_t rep, const int8_t *
     if (!host || n != N) return fail(ISLF_EINVAL, "expected %zu spins, got %zu", N, n);
     if (R.t_host != 0 && !R.failed)
         return fail(ISLF_ESTATE, "set_spins is only valid before the first sweep (or after a failed launch)");
-    // +1 and -1 are the bytes 0x01 and 0xFF: (byte + 1) & 0xFD is 0 exactly for
-    // them (a branch-free pass the compiler vectorises; the index of a bad
-    // value is looked up only when there is one)
-    uint8_t bad = 0;
-    const uint8_t *hb = (const uint8_t *)host;
-    for (size_t i = 0; i < n; ++i) bad |= (uint8_t)(hb[i] + 1u) & 0xFDu;
-    if (bad)
+    Crew crew(N);
+    if (crew.run(nullptr, host, N, true))
         for (size_t i = 0; i < n; ++i)
             if (host[i] != 1 && host[i] != -1) return fail(ISLF_EINVAL, "spin %zu is %d, not +-1", i, (int)host[i]);
-    int8_t *staged = (int8_t *)dev_alloc(ctx, N);
-    if (!staged) return fail(ISLF_ENOMEM, "cannot allocate staging");
-    hipError_t e = hipMemcpyAsync(staged, host, N, hipMemcpyHostToDevice, ctx->stream);
+    HIP_TRY(hipMemcpyAsync(ctx->d_desc + rep, &R.d, sizeof(RepDesc), hipMemcpyHostToDevice, ctx->stream));
+    st = move_spins(ctx, rep, (int8_t *)host, false, crew);
+    if (st != ISLF_OK) return st;
+    hipError_t e = launch_recompute(ctx->fmt, ctx->d_desc, ctx->d_state, rep, host_columns(R.desc), nullptr, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    if (e != hipSuccess) {
-        dev_free(ctx, staged);
-        return fail(ISLF_EDEVICE, "copy of host spins failed: %s", hipGetErrorString(e));
-    }
-    st = init_replica(ctx, rep, ISLF_INIT_HOST, staged);
-    dev_free(ctx, staged);
-    if (st == ISLF_OK && R.failed) {
+    if (e != hipSuccess) return fail(ISLF_EDEVICE, "replica init failed: %s", hipGetErrorString(e));
+    R.t_host = 0;
+    if (R.failed) {
         R.failed = false;
         ctx->graph_valid = false;
     }
-    return st;
+    return ISLF_OK;
 }
 
 extern "C" islf_status islf_get_spins(islf_ctx *ctx, int32_t rep, int8_t *host, size_t n)
 {
     islf_status st = check_rep(ctx, rep);
     if (st != ISLF_OK) return st;
-    Replica &R = ctx->reps[rep];
+    const Replica &R = ctx->reps[rep];
     const size_t N = (size_t)R.desc.Lx * R.desc.Ly * R.desc.Lz;
     if (!host || n != N) return fail(ISLF_EINVAL, "expected %zu spins, got %zu", N, n);
-    st = check_intact(ctx, rep);
-    if (st != ISLF_OK) return st;
-    int8_t *tmp = (int8_t *)dev_alloc(ctx, N);
-    if (!tmp) return fail(ISLF_ENOMEM, "cannot allocate staging");
-    hipError_t e = launch_export(ctx->fmt, ctx->d_desc, rep, R.desc.Lz, host_columns(R.desc), tmp, ctx->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(host, tmp, N, hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    dev_free(ctx, tmp);
-    if (e != hipSuccess) return fail(ISLF_EDEVICE, "get_spins failed: %s", hipGetErrorString(e));
-    return ISLF_OK;
+    Crew crew(N);
+    return move_spins(ctx, rep, host, true, crew);
 }
 
 extern "C" islf_status islf_set_exec(islf_ctx *ctx, int32_t mode)
@@ -1918,39 +2120,6 @@ static islf_status enqueue_form(islf_ctx *c, uint32_t n, bool resident)
     return ISLF_OK;
 }
 
-// Reads the persistent kernel's error word (synchronises).  A raised word
-// means a launch gave up at a grid barrier and left its sweeps half done, so
-// every live replica is marked failed (its calls return ESTATE until
-// islf_set_spins restarts it or it is retired); the word is then cleared so
-// that later launches can run.
-static islf_status check_device_error(islf_ctx *c)
-{
-    unsigned long long err = 0;
-    HIP_TRY(hipMemcpyAsync(&err, &c->d_sync->error.v, sizeof err, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    if (err) {
-        for (int r : c->live) c->reps[r].failed = true;
-        c->graph_valid = false;
-        HIP_TRY(launch_zero((unsigned long long *)&c->d_sync->error, 16, c->stream));
-        HIP_TRY(hipStreamSynchronize(c->stream));
-        return fail(ISLF_EDEVICE, "a persistent-kernel grid barrier gave up (its workgroups were not all resident at "
-                                  "once, or the wait was cut short); every live replica is marked failed");
-    }
-    return ISLF_OK;
-}
-
-// A live replica whose chain is intact: checks the device error word, then
-// the replica's failed mark.
-static islf_status check_intact(islf_ctx *c, int rep)
-{
-    islf_status st = check_device_error(c);
-    if (st != ISLF_OK) return st;
-    if (c->reps[rep].failed)
-        return fail(ISLF_ESTATE, "replica %d was cut short by a failed persistent launch (restart it with "
-                                 "islf_set_spins or retire it)", rep);
-    return ISLF_OK;
-}
-
 static islf_status check_none_failed(const islf_ctx *c)
 {
     for (int r : c->live)
@@ -1989,11 +2158,10 @@ extern "C" islf_status islf_sweep_count(islf_ctx *ctx, int32_t rep, uint64_t *t)
     islf_status st = check_rep(ctx, rep);
     if (st != ISLF_OK) return st;
     if (!t) return fail(ISLF_EINVAL, "NULL output");
-    st = check_intact(ctx, rep);
-    if (st != ISLF_OK) return st;
     RepState s;
-    HIP_TRY(hipMemcpyAsync(&s, ctx->d_state + rep, sizeof s, hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
+    st = fetch(ctx, rep, ctx->d_state + rep, 0, sizeof s / 8, sizeof s / 8);
+    if (st != ISLF_OK) return st;
+    memcpy(&s, ctx->h_res + 8, sizeof s);
     if (s.t != (uint32_t)ctx->reps[rep].t_host)
         return fail(ISLF_EDEVICE, "device sweep counter %u != issued %llu", s.t,
                     (unsigned long long)ctx->reps[rep].t_host);
@@ -2019,9 +2187,15 @@ extern "C" islf_status islf_measure(islf_ctx *ctx, int32_t rep, uint64_t first, 
     if (!out) return fail(ISLF_EINVAL, "NULL output");
     st = check_records(ctx, rep, first, count);
     if (st != ISLF_OK) return st;
+    const Replica &R = ctx->reps[rep];
+    constexpr long W = sizeof(islf_obs) / 8;
+    if (count <= kResultWords / W && count <= ctx->cap) {
+        st = fetch(ctx, rep, R.d.rec, (long)(first % ctx->cap) * W, (long)count * W, (long)ctx->cap * W);
+        if (st == ISLF_OK) memcpy(out, ctx->h_res + 8, count * sizeof(islf_obs));
+        return st;
+    }
     st = check_intact(ctx, rep);
     if (st != ISLF_OK) return st;
-    const Replica &R = ctx->reps[rep];
     uint32_t done = 0;
     while (done < count) {
         const uint32_t slot = (uint32_t)((first + done) % ctx->cap);
@@ -2038,15 +2212,13 @@ extern "C" islf_status islf_recompute(islf_ctx *ctx, int32_t rep, islf_obs *out)
     islf_status st = check_rep(ctx, rep);
     if (st != ISLF_OK) return st;
     if (!out) return fail(ISLF_EINVAL, "NULL output");
-    st = check_intact(ctx, rep);
-    if (st != ISLF_OK) return st;
     const Replica &R = ctx->reps[rep];
-    unsigned long long h[4];
-    hipError_t e = launch_recompute(ctx->fmt, ctx->d_desc, ctx->d_state, rep, host_columns(R.desc), ctx->d_scratch,
-                                    ctx->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(h, ctx->d_scratch, sizeof h, hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    const hipError_t e = launch_recompute(ctx->fmt, ctx->d_desc, ctx->d_state, rep, host_columns(R.desc), ctx->d_scratch,
+                                          ctx->stream);
     if (e != hipSuccess) return fail(ISLF_EDEVICE, "recompute failed: %s", hipGetErrorString(e));
+    st = fetch(ctx, rep, ctx->d_scratch, 0, 4, 4);
+    if (st != ISLF_OK) return st;
+    const unsigned long long *h = ctx->h_res + 8;
     out->B = (int64_t)h[0];
     out->M = (int64_t)h[1];
     out->M1 = (int64_t)h[2];
@@ -2062,9 +2234,16 @@ extern "C" islf_status islf_record_energy(islf_ctx *ctx, int32_t rep, uint64_t f
     if (!out) return fail(ISLF_EINVAL, "NULL output");
     st = check_records(ctx, rep, first, count);
     if (st != ISLF_OK) return st;
+    const Replica &R = ctx->reps[rep];
+    if ((long)count <= kResultWords) {
+        HIP_TRY(launch_energy(R.d.rec, ctx->cap, first, count, R.desc.J, R.desc.H, R.desc.h1, R.desc.hn,
+                              (double *)(ctx->h_res + 8), ctx->stream));
+        st = fetch(ctx, rep);
+        if (st == ISLF_OK) memcpy(out, ctx->h_res + 8, sizeof(double) * count);
+        return st;
+    }
     st = check_intact(ctx, rep);
     if (st != ISLF_OK) return st;
-    const Replica &R = ctx->reps[rep];
     double *tmp = (double *)dev_alloc(ctx, sizeof(double) * count);
     if (!tmp) return fail(ISLF_ENOMEM, "cannot allocate staging");
     hipError_t e = launch_energy(R.d.rec, ctx->cap, first, count, R.desc.J, R.desc.H, R.desc.h1, R.desc.hn, tmp,
@@ -2087,26 +2266,30 @@ extern "C" islf_status islf_means(islf_ctx *ctx, uint64_t first, uint32_t count,
         st = check_records(ctx, r, first, count);
         if (st != ISLF_OK) return st;
     }
+    // live replicas only; dead slots report NaN
+    const int nl = (int)ctx->live.size();
+    const bool fits = 5l * nl <= kResultWords;
+    std::vector<double> tmp_h(fits ? 0 : 5 * (size_t)nl);
+    double *tmp = (double *)(ctx->h_res + 8);
+    if (fits && nl > 0) HIP_TRY(launch_means(ctx->d_desc, ctx->d_live, nl, first, count, tmp, ctx->stream));
     st = check_device_error(ctx);
     if (st != ISLF_OK) return st;
     st = check_none_failed(ctx);
     if (st != ISLF_OK) return st;
-    // live replicas only; dead slots report NaN
-    const int nl = (int)ctx->live.size();
-    std::vector<double> tmp_h(5 * (size_t)std::max(nl, 1));
-    double *tmp = (double *)dev_alloc(ctx, sizeof(double) * 5 * std::max(nl, 1));
-    if (!tmp) return fail(ISLF_ENOMEM, "cannot allocate staging");
-    hipError_t e = hipSuccess;
-    if (nl > 0) e = launch_means(ctx->d_desc, ctx->d_live, nl, first, count, tmp, ctx->stream);
-    if (e == hipSuccess && nl > 0)
-        e = hipMemcpyAsync(tmp_h.data(), tmp, sizeof(double) * 5 * nl, hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    dev_free(ctx, tmp);
-    if (e != hipSuccess) return fail(ISLF_EDEVICE, "means failed: %s", hipGetErrorString(e));
+    if (!fits) {
+        double *dev = (double *)dev_alloc(ctx, sizeof(double) * 5 * nl);
+        if (!dev) return fail(ISLF_ENOMEM, "cannot allocate staging");
+        hipError_t e = launch_means(ctx->d_desc, ctx->d_live, nl, first, count, dev, ctx->stream);
+        tmp = tmp_h.data();
+        if (e == hipSuccess) e = hipMemcpyAsync(tmp, dev, sizeof(double) * 5 * nl, hipMemcpyDeviceToHost, ctx->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+        dev_free(ctx, dev);
+        if (e != hipSuccess) return fail(ISLF_EDEVICE, "means failed: %s", hipGetErrorString(e));
+    }
     for (int r = 0; r < n; ++r)
         for (int k = 0; k < 5; ++k) out[5 * r + k] = NAN;
     for (int i = 0; i < nl; ++i)
-        for (int k = 0; k < 5; ++k) out[5 * ctx->live[i] + k] = tmp_h[5 * i + k];
+        for (int k = 0; k < 5; ++k) out[5 * ctx->live[i] + k] = tmp[5 * i + k];
     return ISLF_OK;
 }
 
@@ -2212,11 +2395,8 @@ extern "C" islf_status islf_footprint_bytes(const islf_replica_desc *desc, int32
     if (st != ISLF_OK) return st;
     if (spin_format != ISLF_SPIN_INT8 && spin_format != ISLF_SPIN_BITPACK)
         return fail(ISLF_EINVAL, "invalid spin format %d", spin_format);
-    Replica R;
-    R.desc = *desc;
-    R.tile = default_tile(desc, spin_format);
-    build_work(R, 0, spin_format);
-    *bytes = replica_bytes(desc, spin_format, obs_capacity) + sizeof(Entry) * (R.main.size() + R.slab.size()) +
+    *bytes = replica_bytes(desc, spin_format, obs_capacity) +
+             sizeof(Entry) * work_entries(*desc, i8_shape(*desc, default_tile(desc, spin_format), spin_format), spin_format) +
              sizeof(RepDesc) + sizeof(RepState);
     return ISLF_OK;
 }
@@ -2274,8 +2454,17 @@ extern "C" islf_status islf_batch_add(islf_ctx *ctx, const islf_replica_desc *de
     int s = -1;
     islf_status st = add_replica(ctx, desc, &s);
     if (st != ISLF_OK) return st;
+    st = sync_tables(ctx);
+    hipError_t e = st == ISLF_OK ? start_replica(ctx, s) : hipSuccess;
+    if (st == ISLF_OK && e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess) st = fail(ISLF_EDEVICE, "replica init failed: %s", hipGetErrorString(e));
+    if (st != ISLF_OK) {
+        ctx->reps[s].live = false;
+        ctx->dirty = true;
+        return st;
+    }
     *slot = s;
-    return sync_tables(ctx);
+    return ISLF_OK;
 }
 
 extern "C" islf_status islf_batch_retire(islf_ctx *ctx, int32_t slot)
@@ -2786,19 +2975,12 @@ extern "C" islf_status islf_replica_means(islf_ctx *ctx, int32_t rep, uint64_t f
     if (!out) return fail(ISLF_EINVAL, "NULL output");
     st = check_records(ctx, rep, first, count);
     if (st != ISLF_OK) return st;
-    st = check_intact(ctx, rep);
-    if (st != ISLF_OK) return st;
-    int *dl = (int *)dev_alloc(ctx, sizeof(int));
-    double *tmp = (double *)dev_alloc(ctx, sizeof(double) * 5);
-    hipError_t e = (dl && tmp) ? hipSuccess : hipErrorOutOfMemory;
-    if (e == hipSuccess) e = hipMemcpyAsync(dl, &rep, sizeof(int), hipMemcpyHostToDevice, ctx->stream);
-    if (e == hipSuccess) e = launch_means(ctx->d_desc, dl, 1, first, count, tmp, ctx->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(out, tmp, sizeof(double) * 5, hipMemcpyDeviceToHost, ctx->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-    dev_free(ctx, dl);
-    dev_free(ctx, tmp);
-    if (e != hipSuccess) return fail(ISLF_EDEVICE, "replica means failed: %s", hipGetErrorString(e));
-    return ISLF_OK;
+    // its entry in the list of live replicas (which only an addition or a retirement changes)
+    const long i = std::lower_bound(ctx->live.begin(), ctx->live.end(), (int)rep) - ctx->live.begin();
+    HIP_TRY(launch_means(ctx->d_desc, ctx->d_live + i, 1, first, count, (double *)(ctx->h_res + 8), ctx->stream));
+    st = fetch(ctx, rep);
+    if (st == ISLF_OK) memcpy(out, ctx->h_res + 8, 5 * sizeof(double));
+    return st;
 }
 
 extern "C" islf_status islf_device_bytes(const islf_ctx *ctx, uint64_t *total, uint64_t *replica_bytes)

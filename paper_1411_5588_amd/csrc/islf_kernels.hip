@@ -972,21 +972,15 @@ struct HostRun {
     }
 };
 
-// 8-site columns of a sublattice row that are stored (whole 32-bit words of the bit-packed format)
-__device__ __forceinline__ int stored_columns(const RepDesc &d)
-{
-    return d.fmt == ISLF_SPIN_INT8 ? d.K : 4 * d.Wq;
-}
-
 // Internal format -> host layout.  Memory: 1 + 1 (or 1 + 1/8) bytes a site.
 // 88 x 504 x 504 int8 (22 M sites): 13 us, 3.4 TB/s; one lane a site took 28 us.
 template <int FMT, int A>
-__global__ __launch_bounds__(kBlock) void k_export(const RepDesc *__restrict__ descs, int rep,
-                                                   int8_t *__restrict__ out)
+__global__ __launch_bounds__(kBlock) void k_export(const RepDesc *__restrict__ descs, int rep, uint32_t c0,
+                                                   uint32_t c1, size_t h0, int8_t *__restrict__ out)
 {
     const RepDesc &d = descs[rep];
-    const uint32_t nh = (uint32_t)d.Lz >> 1, nk = (nh + 7) >> 3, n = (uint32_t)d.Lx * (uint32_t)d.Ly * nk;
-    for (uint32_t c = blockIdx.x * kBlock + threadIdx.x; c < n; c += gridDim.x * kBlock) {
+    const uint32_t nk = (uint32_t)d.K;
+    for (uint32_t c = c0 + blockIdx.x * kBlock + threadIdx.x; c < c1; c += gridDim.x * kBlock) {
         const uint32_t row = c / nk, k = c - row * nk;
         HostRun<A> r;
         if (FMT == ISLF_SPIN_INT8) {
@@ -1012,7 +1006,7 @@ __global__ __launch_bounds__(kBlock) void k_export(const RepDesc *__restrict__ d
             const uint32_t down = r.w[i] ^ 0x01010101u;
             r.w[i] |= (down << 8) - down;
         }
-        r.store(out + (size_t)row * (uint32_t)d.Lz + 16 * k, (int)min(16u, (uint32_t)d.Lz - 16 * k));
+        r.store(out + ((size_t)row * (uint32_t)d.Lz + 16 * k - h0), (int)min(16u, (uint32_t)d.Lz - 16 * k));
     }
 }
 
@@ -1020,18 +1014,18 @@ __global__ __launch_bounds__(kBlock) void k_export(const RepDesc *__restrict__ d
 // state.  22 M int8 sites: 12 us; one byte load a site took 30 us.
 template <int FMT, int A>
 __global__ __launch_bounds__(kBlock) void k_import(const RepDesc *__restrict__ descs, RepState *__restrict__ st,
-                                                   int rep, const int8_t *__restrict__ host)
+                                                   int rep, uint32_t c0, uint32_t c1, size_t h0,
+                                                   const int8_t *__restrict__ host)
 {
     const RepDesc &d = descs[rep];
     start_state(d, st[rep]);
-    const uint32_t nk = (uint32_t)stored_columns(d), n = (uint32_t)d.Lx * (uint32_t)d.Ly * nk;
-    for (uint32_t c = blockIdx.x * kBlock + threadIdx.x; c < n; c += gridDim.x * kBlock) {
+    const uint32_t nk = (uint32_t)d.K;
+    for (uint32_t c = c0 + blockIdx.x * kBlock + threadIdx.x; c < c1; c += gridDim.x * kBlock) {
         const uint32_t row = c / nk, k = c - row * nk;
         HostRun<A> r;
 #pragma unroll
         for (int i = 0; i < 4; ++i) r.w[i] = 0xFFFFFFFFu;   // past the row's end: no spin
-        const int left = d.Lz - 16 * (int)k;
-        if (left > 0) r.load(host + (size_t)row * (uint32_t)d.Lz + 16 * k, min(16, left));
+        r.load(host + ((size_t)row * (uint32_t)d.Lz + 16 * k - h0), min(16, d.Lz - 16 * (int)k));
         uint2 e, o;
         e.x = __builtin_amdgcn_perm(r.w[1], r.w[0], 0x06040200u);
         e.y = __builtin_amdgcn_perm(r.w[3], r.w[2], 0x06040200u);
@@ -1050,6 +1044,8 @@ __global__ __launch_bounds__(kBlock) void k_import(const RepDesc *__restrict__ d
             uint8_t *p = d.spins + (size_t)row * 8 * d.Wq + k;
             p[0] = (uint8_t)((e.x * 0x01020408u) >> 24 | ((e.y * 0x01020408u) >> 24) << 4);
             p[4 * d.Wq] = (uint8_t)((o.x * 0x01020408u) >> 24 | ((o.y * 0x01020408u) >> 24) << 4);
+            if (k + 1 == nk)   // the rest of the last word
+                for (int i = 1; i < 4 * d.Wq - (int)k; ++i) p[i] = p[4 * d.Wq + i] = 0;
         }
     }
 }
@@ -1178,6 +1174,18 @@ __global__ __launch_bounds__(256) void k_layer_profile(const RepDesc *__restrict
 __global__ void k_zero_u64(unsigned long long *p, long n)
 {
     for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) p[i] = 0;
+}
+
+// The error word and n 64-bit words of a ring into host memory, words 8 on.
+__global__ void k_fetch(const unsigned long long *__restrict__ error, const unsigned long long *__restrict__ ring,
+                        long first, long n, long size, unsigned long long *__restrict__ host)
+{
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) host[0] = *error;
+    for (long k = i; k < n; k += (long)gridDim.x * blockDim.x) {
+        const long j = first + k;
+        host[8 + k] = ring[j < size ? j : j - size];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1410,13 +1418,14 @@ hipError_t launch_init(int fmt, const RepDesc *descs, RepState *st, int rep, int
 }
 
 template <int FMT>
-static void import_export(const RepDesc *descs, RepState *st, int rep, int align, bool in, int8_t *host, unsigned grid,
-                          hipStream_t s)
+static void import_export(const RepDesc *descs, RepState *st, int rep, int align, bool in, uint32_t c0, uint32_t c1,
+                          size_t h0, int8_t *host, hipStream_t s)
 {
+    const dim3 grid(lanes_grid((long)c1 - c0, 1L << 16)), block(kBlock);
     auto go = [&](auto a) {
         constexpr int A = decltype(a)::value;
-        if (in) hipLaunchKernelGGL((k_import<FMT, A>), dim3(grid), dim3(kBlock), 0, s, descs, st, rep, host);
-        else hipLaunchKernelGGL((k_export<FMT, A>), dim3(grid), dim3(kBlock), 0, s, descs, rep, host);
+        if (in) hipLaunchKernelGGL((k_import<FMT, A>), grid, block, 0, s, descs, st, rep, c0, c1, h0, host);
+        else hipLaunchKernelGGL((k_export<FMT, A>), grid, block, 0, s, descs, rep, c0, c1, h0, host);
     };
     if (align == 16) go(std::integral_constant<int, 16>());
     else if (align == 4) go(std::integral_constant<int, 4>());
@@ -1424,22 +1433,21 @@ static void import_export(const RepDesc *descs, RepState *st, int rep, int align
     else go(std::integral_constant<int, 1>());
 }
 
-hipError_t launch_import(int fmt, const RepDesc *descs, RepState *st, int rep, int Lz, long n, const int8_t *host,
-                         hipStream_t s)
+hipError_t launch_import(int fmt, const RepDesc *descs, RepState *st, int rep, int Lz, uint32_t c0, uint32_t c1,
+                         size_t h0, const int8_t *host, hipStream_t s)
 {
     const int a = host_align(host, Lz);
-    if (fmt == ISLF_SPIN_INT8)
-        import_export<ISLF_SPIN_INT8>(descs, st, rep, a, true, (int8_t *)host, lanes_grid(n, 1L << 16), s);
-    else import_export<ISLF_SPIN_BITPACK>(descs, st, rep, a, true, (int8_t *)host, lanes_grid(n, 1L << 16), s);
+    if (fmt == ISLF_SPIN_INT8) import_export<ISLF_SPIN_INT8>(descs, st, rep, a, true, c0, c1, h0, (int8_t *)host, s);
+    else import_export<ISLF_SPIN_BITPACK>(descs, st, rep, a, true, c0, c1, h0, (int8_t *)host, s);
     return hipGetLastError();
 }
 
-hipError_t launch_export(int fmt, const RepDesc *descs, int rep, int Lz, long n, int8_t *out, hipStream_t s)
+hipError_t launch_export(int fmt, const RepDesc *descs, int rep, int Lz, uint32_t c0, uint32_t c1, size_t h0,
+                         int8_t *out, hipStream_t s)
 {
     const int a = host_align(out, Lz);
-    if (fmt == ISLF_SPIN_INT8)
-        import_export<ISLF_SPIN_INT8>(descs, nullptr, rep, a, false, out, lanes_grid(n, 1L << 16), s);
-    else import_export<ISLF_SPIN_BITPACK>(descs, nullptr, rep, a, false, out, lanes_grid(n, 1L << 16), s);
+    if (fmt == ISLF_SPIN_INT8) import_export<ISLF_SPIN_INT8>(descs, nullptr, rep, a, false, c0, c1, h0, out, s);
+    else import_export<ISLF_SPIN_BITPACK>(descs, nullptr, rep, a, false, c0, c1, h0, out, s);
     return hipGetLastError();
 }
 
@@ -1475,6 +1483,14 @@ hipError_t launch_zero(unsigned long long *p, long n, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_zero_u64, dim3(256), dim3(kBlock), 0, s, p, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_fetch(const unsigned long long *error, const void *ring, long first, long n, long size,
+                        unsigned long long *host, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_fetch, dim3(lanes_grid(n, 64)), dim3(kBlock), 0, s, error, (const unsigned long long *)ring,
+                       first, n, size, host);
     return hipGetLastError();
 }
 

@@ -49,3 +49,42 @@ def test_spins_and_observables_round_trip(fmt, ybc):
         ctx.sweep(1)
         for r in range(len(SHAPES)):
             assert tuple(ctx.measure(r, 0, 1)[0]) == tuple(ctx.recompute(r)), SHAPES[r]
+
+
+@pytest.mark.parametrize("shape", [(2, 8, 4096), (2, 8, 4098), (37, 251, 226), (3, 2, 700002), (44, 252, 504)])
+@pytest.mark.parametrize("fmt", [islf.INT8, islf.BITPACK])
+def test_spins_in_windows(fmt, shape):
+    """64 KiB (one piece), just over it, and several windows with rows across their ends, with and without helpers."""
+    rng = np.random.default_rng(SEED + 32)
+    a, b = [(2 * rng.integers(0, 2, size=shape) - 1).astype(np.int8) for _ in range(2)]
+    p = config1(Lx=shape[0], Ly=shape[1], Lz=shape[2], seed=SEED, replica=0, ybc=GAPBC)
+    with islf.Context([islf.Replica(**p)], spin_format=fmt, obs_capacity=4) as ctx:
+        ctx.set_spins(0, a)
+        b[-1, -1, -1] = 0
+        with pytest.raises(islf.IslfError) as e:   # refused whole: the last byte is no spin
+            ctx.set_spins(0, b)
+        assert e.value.status == islf.EINVAL
+        assert np.array_equal(ctx.get_spins(0).reshape(shape), a)
+        assert tuple(ctx.recompute(0)) == sums(a, GAPBC)
+        b[-1, -1, -1] = 1
+        ctx.set_spins(0, b)
+        assert np.array_equal(ctx.get_spins(0).reshape(shape), b)
+        assert tuple(ctx.recompute(0)) == sums(b, GAPBC)
+
+
+@pytest.mark.parametrize("count", [2048, 2049, 8192, 8193])
+def test_records_at_the_edges_of_the_result_buffer(count):
+    """Records and energies around the sizes at which they come in one piece, from a ring that has wrapped."""
+    p = config1(Lx=2, Ly=4, Lz=4, seed=SEED, replica=0)
+    cap, n = 9000, 13000
+    with islf.Context([islf.Replica(**p)], spin_format=islf.INT8, obs_capacity=cap) as ctx:
+        ctx.sweep(n)
+        first = n - count - 3
+        one = np.concatenate([ctx.measure(0, k, min(1000, n - k)) for k in range(n - cap, n, 1000)])
+        assert np.array_equal(ctx.measure(0, first, count), one[first - (n - cap):][:count])
+        E = ctx.energy(0, first, count)
+        r = one[first - (n - cap):][:count].astype(np.float64)
+        e = -p["J"] * r[:, 0]
+        for k, h in enumerate(("H", "h1", "hn")):
+            e = e - p[h] * r[:, k + 1]
+        assert np.array_equal(E, e)
