@@ -55,7 +55,7 @@ hipError_t launch_integrate(const double *h, const double *m1, const double *mn,
                             double norm, double *out, hipStream_t s);
 hipError_t noalloc_scratch(double **out);
 hipError_t resident_lds_limit(int fmt, size_t bytes);
-hipError_t launch_resident(int fmt, bool small, const ResLaunch &L, size_t lds, hipStream_t s);
+hipError_t launch_resident(int fmt, int form, const ResLaunch &L, size_t lds, hipStream_t s);
 }  // namespace islf
 
 using namespace islf;
@@ -238,7 +238,7 @@ struct ResPlan {
     ResLaunch L{};         // tables (device memory) and counts; n, check_error and part per launch
     size_t jobs_b = 0, first_b = 0, planes_b = 0, rows_b = 0, reps_b = 0, part_b = 0, mbox_b = 0;   // bytes allocated
     std::vector<int4 *> outgrown;   // smaller sum buffers that captured graphs may still use
-    bool small = false;    // no clusters and few words per film: one lane per four-site group
+    int form = RES_WORDS;  // RES_GROUPS: no clusters and few words per film; RES_FINE: few words per stage
     size_t lds = 0;
     uint32_t max_sweeps = 0;
     double sweep_us = 0.0, fixed_us = 0.0, chain_us = 0.0;   // expected: per sweep, per launch; a sweep of the launch chain
@@ -320,7 +320,7 @@ struct islf_ctx {
     bool graph_valid = false;
 
     // the cuts of the shapes planned so far (kMaxShapes at most)
-    std::map<std::array<int, 3>, std::vector<ShareChoice>> choices;
+    std::map<std::array<int, 4>, std::vector<ShareChoice>> choices;
 
     // device bytes the context holds, by allocation
     std::unordered_map<void *, size_t> alloc_bytes;
@@ -957,6 +957,12 @@ constexpr size_t kLatticeLds = 160 * 1024 - kResStaticLds;   // of a gfx950 CU's
 // stage's barrier and the tail of its last chunks.
 constexpr double kChunkUs = 0.80, kPartUs = 0.18, kGroupUs = 0.092, kLoneUs = 1.3, kExchangeUs = 0.8, kMailUs = 0.4,
                  kStageUs = 1.1;
+// The fine form: a chunk of 16 words, the latency of a lone one, and what the
+// form must promise against whole words where those are cut along y alone (at
+// 0.97 of them, one film of 30x164x164 measured 11.2 us a sweep against 10.6;
+// cut along x too, whole words fall short of their estimate: 16 x 40x120x120,
+// both 11 by estimate, 15.8 us and 11.4 fine).
+constexpr double kFineUs = 0.30, kFineLoneUs = 0.5, kFineGain = 0.95;
 // Films of at most this many four-site groups per phase are updated by one
 // lane per group when no film of the launch needs a cluster.
 constexpr long kSmallGroups = (long)kSmallTasks * kResThreads;
@@ -965,8 +971,9 @@ constexpr long kSmallGroups = (long)kSmallTasks * kResThreads;
 // one the middle planes), py blocks of rows.
 struct ShareCost {
     const islf_replica_desc &d;
+    bool fine;
     int Wq, Wf, ng;
-    explicit ShareCost(const islf_replica_desc &d_) : d(d_)
+    explicit ShareCost(const islf_replica_desc &d_, bool fine_ = false) : d(d_), fine(fine_)
     {
         const int nbits = d.Lz / 2;
         Wq = (nbits + 31) / 32;
@@ -1005,11 +1012,12 @@ struct ShareCost {
     // SIMD time of a row set's chunks
     double work(long np, long rows) const
     {
+        if (fine) return ceil_div(np * rows * Wf, kResFineChunk) * kFineUs + (ng ? ceil_div(np * rows, kResFineChunk) * kFineUs : 0.0);
         return ceil_div(np * rows * Wf, 64) * kChunkUs + (ng ? ceil_div(np * rows, 64) * (kPartUs + ng * kGroupUs) : 0.0);
     }
     double stage(double work_us) const
     {
-        return std::max(work_us / 4.0, Wf ? kLoneUs : 0.4 + 0.15 * ng) + kStageUs;
+        return std::max(work_us / 4.0, fine ? kFineLoneUs : Wf ? kLoneUs : 0.4 + 0.15 * ng) + kStageUs;
     }
     // a sweep of a share of np planes and `rows` rows (see ResStage)
     double sweep(long np, long rows, bool row0, bool has_x, bool has_y) const
@@ -1020,7 +1028,8 @@ struct ShareCost {
         const long r = rows - (has_y ? 2 : 0);   // beside the edge rows
         if (!row0) return 2.0 * stage(edge + (r > 0 ? work(np, r) : 0.0)) + xch;
         const double seam = work(np, 2), inner = r > 3 ? work(np, r - 3) : 0.0;
-        return stage(edge + seam + inner) + stage(edge + seam) + 2.0 * stage(work(np, 1) + inner / 2.0) + xch;
+        return stage(edge + seam + inner) + stage(edge + seam) + 2.0 * stage(work(np, 1) + inner / 2.0) + xch +
+               (fine && has_x ? 4.0 * kExchangeUs : 0.0);   // row 0's own mail
     }
     // rows of the shares with row 0 (Ly-1, 0, 1 at least) and the most rows of
     // the others when py >= 2; false if there are too few rows
@@ -1057,9 +1066,9 @@ struct ShareCost {
 // sites, whose stages cost much the same at 4 shares as at 24, were cut fine
 // for nothing and paid in mail (eight of them, 24 and 4 to 10 shares each: 14.4
 // and 13.7 us a sweep; planning them took 0.5 and 0.35 ms).
-static std::vector<ShareChoice> share_choices(const islf_replica_desc &d, int NW)
+static std::vector<ShareChoice> share_choices(const islf_replica_desc &d, bool fine, int NW)
 {
-    const ShareCost k(d);
+    const ShareCost k(d, fine);
     std::vector<ShareChoice> all, best;
     const int H = (d.Lx + 1) / 2;
     for (int px : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16}) {
@@ -1107,7 +1116,7 @@ struct ResTablesHost {
 
 // The px x py shares of a film, appended to the tables; jobs go to `put`.
 template <class PUT>
-static void cut_film(const islf_replica_desc &d, int rep, int px, int py, bool small, int &id, ResTablesHost &h, PUT put)
+static void cut_film(const islf_replica_desc &d, int rep, int px, int py, int form, int &id, ResTablesHost &h, PUT put)
 {
     const ShareCost k(d);
     const int P = px * py;
@@ -1192,7 +1201,7 @@ static void cut_film(const islf_replica_desc &d, int rep, int px, int py, bool s
         for (int lr = 1; lr <= R[j]; ++lr) {
             if (lr == lr0) continue;
             if (py > 1 && (lr == 1 || lr == R[j])) edge.push_back(lr);
-            else if (lr0 && (lr == ls || lr == lr0 + 1) && !small) last.push_back(lr);
+            else if (lr0 && (lr == ls || lr == lr0 + 1) && form != RES_GROUPS) last.push_back(lr);
             else inner.push_back(lr);
         }
         add(RES_EDGE, edge);
@@ -1215,10 +1224,11 @@ static void cut_film(const islf_replica_desc &d, int rep, int px, int py, bool s
             b.n_edge = ne[i];
             b.n_head = nh[i];
             b.n_tail = nt[i];
+            const long per = form == RES_FINE ? kResFineChunk : 64;   // words of a chunk
             for (int q = 0; q < 4; ++q) {
                 b.set[q] = set[q];
-                b.set[q].whole = (int)ceil_div((long)np[i] * set[q].n * k.Wf, 64);
-                b.set[q].part = k.ng ? (int)ceil_div((long)np[i] * set[q].n, 64) : 0;
+                b.set[q].whole = (int)ceil_div((long)np[i] * set[q].n * k.Wf, per);
+                b.set[q].part = k.ng ? (int)ceil_div((long)np[i] * set[q].n, per) : 0;
             }
             // Stages.  Row 0's phases 2 and 3 follow phase 1 of the rows beside it and precede their next
             // phase 0; a share with row 0 does those rows first and splits the interior rows' phase 1 over
@@ -1274,20 +1284,9 @@ static bool plan_resident(islf_ctx *c, const std::vector<int> &reps, ResPlan &p,
     // replicas of one shape share their choices
     if (c->choices.size() > kMaxShapes) c->choices.clear();
     std::vector<const std::vector<ShareChoice> *> shape(n);
-    double total = 0.0;
-    for (int i = 0; i < n; ++i) {
-        const islf_replica_desc &d = c->reps[reps[i]].desc;
-        if (d.Lx > 32000 || d.Ly > 32000) return false;   // 16-bit table entries
-        const std::array<int, 3> key = {d.Lx, d.Ly, d.Lz};
-        auto it = c->choices.find(key);
-        if (it == c->choices.end()) it = c->choices.emplace(key, share_choices(d, NW)).first;
-        if (it->second.empty()) return false;
-        shape[i] = &it->second;
-        const ShareChoice &f = shape[i]->front();
-        total += f.P * f.us;
-    }
     std::vector<const ShareChoice *> pick(n), best_pick;
     double best = 1e300;
+    p.form = RES_WORDS;
     auto pack = [&](std::vector<int> *where) -> double {
         // cluster workgroups first, then singles by LPT; returns the longest workgroup
         std::vector<std::pair<double, int>> heap;   // (-load, workgroup)
@@ -1314,43 +1313,61 @@ static bool plan_resident(islf_ctx *c, const std::vector<int> &reps, ResPlan &p,
         }
         return longest;
     };
-    const double t0 = std::max(2.0, 0.7 * total / NW);
-    for (int step = 0; step < 64; ++step) {
-        const double T = t0 * pow(1.04, step);
-        long used = 0;
+    for (int form : {RES_WORDS, RES_FINE}) {
+        double total = 0.0;
         for (int i = 0; i < n; ++i) {
-            // the fewest shares within T, else the fastest cut
-            const std::vector<ShareChoice> &v = *shape[i];
-            size_t q = 0;
-            while (q + 1 < v.size() && v[q].us > T) ++q;
-            pick[i] = &v[q];
-            if (v[q].P > 1) used += v[q].P;
+            const islf_replica_desc &d = c->reps[reps[i]].desc;
+            if (d.Lx > 32000 || d.Ly > 32000) return false;   // 16-bit table entries
+            const std::array<int, 4> key = {d.Lx, d.Ly, d.Lz, form};
+            auto it = c->choices.find(key);
+            if (it == c->choices.end()) it = c->choices.emplace(key, share_choices(d, form == RES_FINE, NW)).first;
+            if (it->second.empty()) return false;
+            shape[i] = &it->second;
+            const ShareChoice &f = shape[i]->front();
+            total += f.P * f.us;
         }
-        if (used > NW) continue;
-        const double m = pack(nullptr);
-        if (m < best) {
-            best = m;
-            best_pick = pick;
+        const double t0 = std::max(2.0, 0.7 * total / NW);
+        for (int step = 0; step < 64; ++step) {
+            const double T = t0 * pow(1.04, step);
+            long used = 0;
+            for (int i = 0; i < n; ++i) {
+                // the fewest shares within T, else the fastest cut
+                const std::vector<ShareChoice> &v = *shape[i];
+                size_t q = 0;
+                while (q + 1 < v.size() && v[q].us > T) ++q;
+                pick[i] = &v[q];
+                if (v[q].P > 1) used += v[q].P;
+            }
+            if (used > NW) continue;
+            const double m = pack(nullptr);
+            const bool cut_x = form != p.form && std::any_of(best_pick.begin(), best_pick.end(),
+                                                             [](const ShareChoice *q) { return q->px > 1; });
+            if (m < (form == p.form || cut_x ? 1.0 : kFineGain) * best) {
+                best = m;
+                best_pick = pick;
+                p.form = form;
+            }
+            if (m < T) break;
         }
-        if (m < T) break;
     }
     if (best_pick.empty()) return false;
     pick = best_pick;
     std::vector<int> where(n, -1);
     p.sweep_us = pack(&where);
-    p.small = true;
+    bool groups = true;
     for (int i = 0; i < n; ++i) {
         const islf_replica_desc &d = c->reps[reps[i]].desc;
         const long row = (long)d.Lx * ((d.Lz + 7) / 8);   // groups of a row
-        p.small = p.small && pick[i]->P == 1 && row <= kResThreads && row * (d.Ly - 1) <= kSmallGroups;
+        groups = groups && pick[i]->P == 1 && row <= kResThreads && row * (d.Ly - 1) <= kSmallGroups;
     }
+    if (groups) p.form = RES_GROUPS;
     std::vector<std::vector<ResJob>> wg(NW);
     p.L.members = 0;
     p.lds = 0;
     int id = 0;
     for (int i = 0; i < n; ++i) {
         h.reps.push_back(ResRep{reps[i], id, pick[i]->P, 0});
-        cut_film(c->reps[reps[i]].desc, reps[i], pick[i]->px, pick[i]->py, p.small, id, h,
+        cut_film(c->reps[reps[i]].desc, reps[i], pick[i]->px, pick[i]->py, p.form, id, h,
                  [&](const ResJob &j, size_t lds) {
                      wg[j.P > 1 ? p.L.members++ : where[i]].push_back(j);
                      p.lds = std::max(p.lds, lds);
@@ -1501,7 +1518,7 @@ static hipError_t enqueue_resident(islf_ctx *c, uint32_t n)
         hipError_t e = hipSuccess;
         for (uint32_t done = 0; done < n && e == hipSuccess; done += L.n) {
             L.n = std::min(n - done, p.max_sweeps);
-            e = launch_resident(c->fmt, p.small, L, p.lds, c->stream);
+            e = launch_resident(c->fmt, p.form, L, p.lds, c->stream);
         }
         return e;
     };

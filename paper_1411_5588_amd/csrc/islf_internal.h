@@ -113,6 +113,8 @@ struct TeamInfo {
 constexpr int kResThreads = 1024;      // threads per workgroup: 4 waves per SIMD, one workgroup per CU
 constexpr int kResMaxSweeps = 256;     // sweeps one launch may run
 constexpr int kResStaticLds = 10880;    // LDS bytes beside the lattice: pair tables, thresholds, control words
+constexpr int kResFineChunk = 16;       // words of a chunk in the fine form
+enum { RES_WORDS, RES_GROUPS, RES_FINE };   // how a launch's words go to lanes: see k_resident
 constexpr int kSmallTasks = 2;         // four-site groups a lane of the small form may hold per phase
 
 // Tables of a share, as the host writes them: its planes in the order of
@@ -132,7 +134,7 @@ struct ResRow {
 struct ResRows {
     int32_t r0, n;
     uint32_t m, m_w;              // ceil(2^32 / d) of d = n and of d = n * whole words of a row
-    int32_t whole, part;          // chunks of 64 whole words, of 64 partial last words
+    int32_t whole, part;          // chunks of whole words, of partial last words
     int32_t seam;                 // holds row y = 0 or Ly-1
 };
 enum { RES_EDGE = 0, RES_SEAM = 1, RES_INNER = 2, RES_ROW0 = 3 };

@@ -288,7 +288,13 @@ __device__ __forceinline__ void mail_put(unsigned long long *mbox, uint32_t at, 
 // Updates chunk c of a row set in one phase: words run planes slowest, then
 // rows, then words of a row, 64 to a chunk.  send: new words of edge rows and
 // edge planes go to the neighbours' mailboxes.
-template <bool SEAM, bool WHOLE>
+//
+// FINE: 16 words to a chunk, four lanes to a word with two of its groups each
+// (they read and count the word's neighbours alike, and join their flips).  A
+// chunk takes a third of the time, all words together half as long again: for
+// stages of few words, which lie on one chunk's latency (24 x 20x64x64 11.1 ->
+// 7.7 us a sweep, 16 x 40x120x120 15.8 -> 11.4, 22x142x142 11.4 -> 9.9).
+template <bool SEAM, bool WHOLE, bool FINE>
 __device__ __forceinline__ void share_chunk(const Share &g, const ResJob &jb, char *lat, const ResTables &tb,
                                             const DrawKey &key, const ResRows &rs, int c, int phase, bool send,
                                             bool edge_rows, unsigned long long *mbox, uint32_t epoch, Sums &a)
@@ -298,8 +304,10 @@ __device__ __forceinline__ void share_chunk(const Share &g, const ResJob &jb, ch
     const uint32_t m = WHOLE ? rs.m_w : rs.m;
     const uint32_t *ct = g.ct + (WHOLE ? rs.r0 * jb.Wf : g.R * jb.Wf + rs.r0);
     const int T = g.np * plane;
-    const int tk = c * 64 + lane;
-    const bool ok = tk < T;
+    constexpr int PER = FINE ? kResFineChunk : 64;
+    const int tk = c * PER + (FINE ? lane >> 2 : lane);
+    const uint32_t p8 = FINE ? 8u * (uint32_t)(lane & 3) : 0u;   // the lane's first site in the word
+    bool ok = tk < T;
     const uint32_t tau = (uint32_t)min(tk, T - 1);
     const uint32_t pi = div_m(tau, (uint32_t)plane, m);
     const uint32_t *cp = ct + (tau - __umul24(pi, (uint32_t)plane));
@@ -307,10 +315,20 @@ __device__ __forceinline__ void share_chunk(const Share &g, const ResJob &jb, ch
     const uint4 pl = g.pt[pi];
     const Word o = share_gather<SEAM, WHOLE>(g, lat, pl, cl, phase);
     // chunks of bulk planes read the bulk table at a fixed base
-    const bool surf = c * 64 < jb.n_head * plane || c * 64 + 63 >= T - jb.n_tail * plane;
+    const bool surf = c * PER < jb.n_head * plane || c * PER + PER - 1 >= T - jb.n_tail * plane;
     const bool x0 = (pl.w & PL_X0) != 0, xl = (pl.w & PL_XL) != 0;
     uint32_t F;
-    if (g.sym && !surf) {
+    if (FINE) {
+        const Word f = {o.S >> p8, o.b0 >> p8, o.b1 >> p8, o.b2 >> p8, o.own, o.gq + (p8 >> 1)};
+        if (g.sym && !surf) F = few_flips<true>(f, 2, key, tb.quad, tb.pair, tb.thr, false);
+        else
+            F = few_flips<false>(f, 2, key, tb.quad, tb.pair + (x0 ? 256 : xl ? 512 : 0),
+                                 tb.thr + kThrPerClass * ((x0 ? 1 : 0) + (xl ? 2 : 0)), g.never);
+        F = (F & 0xFFu) << p8;
+        F |= (uint32_t)__builtin_amdgcn_mov_dpp((int)F, 0xB1, 0xF, 0xF, true);   // lanes 1 0 3 2 of each four
+        F |= (uint32_t)__builtin_amdgcn_mov_dpp((int)F, 0x4E, 0xF, 0xF, true);   // lanes 2 3 0 1
+        ok = ok && p8 == 0u;
+    } else if (g.sym && !surf) {
         if (WHOLE) F = bp_flips_quads(o.S, o.b2, o.b1, o.b0, o.gq, key, tb.quad);
         else F = few_flips<true>(o, jb.ng, key, tb.quad, tb.pair, tb.thr, false);
     } else {
@@ -330,7 +348,7 @@ __device__ __forceinline__ void share_chunk(const Share &g, const ResJob &jb, ch
             mail_put(mbox, ay, v);
             if (g.R == 1) mail_put(mbox, ay + (jb.out_y[1] - jb.out_y[0]), v);   // one row is both edges
         }
-        if (c * 64 < jb.n_edge * plane && ok && (int)pi < jb.n_edge) {
+        if (c * PER < jb.n_edge * plane && ok && (int)pi < jb.n_edge) {
             const uint2 px = g.pm[pi];
             const uint32_t ax = cp[6 * g.nc] + sl;
             mail_put(mbox, px.x + ax, v);
@@ -598,9 +616,9 @@ __device__ __forceinline__ unsigned int res_census(ResSync *rs, unsigned int mem
 // and 3.6 us, 168 ladder films 37 and 3.0 us, 64 x 40x120x120 31 and 22.1 us,
 // 96 uneven films int8 85 and 60 us, 184x504x504 39 and 25.7 us, 3 x
 // 160x480x600 int8 95 and 62 us, persistent 78 and 62 us.
-// SMALL: no clusters, and films of few words, updated one four-site group per
-// lane (share_groups).
-template <int FMT, bool SMALL>
+// FORM: RES_GROUPS = no clusters, and films of few words, updated one four-site
+// group per lane (group_update); RES_FINE = chunks of 16 words.
+template <int FMT, int FORM>
 __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restrict__ descs,
                                                           const RepState *__restrict__ st,
                                                           const ResJob *__restrict__ jobs,
@@ -608,6 +626,7 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
                                                           const ResPlane *__restrict__ plane_tables,
                                                           const ResRow *__restrict__ row_tables, const ResLaunch L)
 {
+    constexpr bool SMALL = FORM == RES_GROUPS, FINE = FORM == RES_FINE;
     extern __shared__ uint32_t smem[];
     __shared__ ResTables tb;
     __shared__ ResCtl ctl_s;
@@ -787,12 +806,12 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
                         const bool send = cluster && (!(phase & 1) || s + 1 < n);
                         const uint32_t e = ep + (uint32_t)phase;
                         if (c < rs.whole) {
-                            if (rs.seam) share_chunk<true, true>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
-                            else share_chunk<false, true>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
+                            if (rs.seam) share_chunk<true, true, FINE>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
+                            else share_chunk<false, true, FINE>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
                         } else {
                             c -= rs.whole;
-                            if (rs.seam) share_chunk<true, false>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
-                            else share_chunk<false, false>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
+                            if (rs.seam) share_chunk<true, false, FINE>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
+                            else share_chunk<false, false, FINE>(g, jb, lat, tb, key, rs, c, phase, send, edge, L.mbox, e, a);
                         }
                     }
                     if (i + 1 < jb.stages) __syncthreads();
@@ -951,31 +970,36 @@ __global__ __launch_bounds__(kResThreads) void k_resident_close(const ResLaunch 
 // ---------------------------------------------------------------------------
 // Host-callable launchers
 // ---------------------------------------------------------------------------
+using ResKernel = void (*)(const RepDesc *, const RepState *, const ResJob *, const int *, const ResPlane *,
+                           const ResRow *, ResLaunch);
+
+static ResKernel resident_kernel(int fmt, int form)
+{
+    static const ResKernel k[2][3] = {
+        {k_resident<ISLF_SPIN_INT8, RES_WORDS>, k_resident<ISLF_SPIN_INT8, RES_GROUPS>, k_resident<ISLF_SPIN_INT8, RES_FINE>},
+        {k_resident<ISLF_SPIN_BITPACK, RES_WORDS>, k_resident<ISLF_SPIN_BITPACK, RES_GROUPS>,
+         k_resident<ISLF_SPIN_BITPACK, RES_FINE>}};
+    return k[fmt == ISLF_SPIN_INT8 ? 0 : 1][form];
+}
+
 // Lets the kernels use `bytes` of dynamic LDS.
 hipError_t resident_lds_limit(int fmt, size_t bytes)
 {
-    const void *f[2] = {fmt == ISLF_SPIN_INT8 ? (const void *)k_resident<ISLF_SPIN_INT8, false>
-                                              : (const void *)k_resident<ISLF_SPIN_BITPACK, false>,
-                        fmt == ISLF_SPIN_INT8 ? (const void *)k_resident<ISLF_SPIN_INT8, true>
-                                              : (const void *)k_resident<ISLF_SPIN_BITPACK, true>};
     hipError_t e = hipSuccess;
-    for (int i = 0; i < 2 && e == hipSuccess; ++i)
-        e = hipFuncSetAttribute(f[i], hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    for (int form : {RES_WORDS, RES_GROUPS, RES_FINE})
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute((const void *)resident_kernel(fmt, form), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)bytes);
     return e;
 }
 
-hipError_t launch_resident(int fmt, bool small, const ResLaunch &L, size_t lds, hipStream_t s)
+hipError_t launch_resident(int fmt, int form, const ResLaunch &L, size_t lds, hipStream_t s)
 {
-    const dim3 g(L.grid), gr(L.nreps), b(kResThreads);
-    if (fmt == ISLF_SPIN_INT8) {
-        if (small) hipLaunchKernelGGL((k_resident<ISLF_SPIN_INT8, true>), g, b, lds, s, L.descs, L.st, L.jobs, L.first, L.planes, L.rows, L);
-        else hipLaunchKernelGGL((k_resident<ISLF_SPIN_INT8, false>), g, b, lds, s, L.descs, L.st, L.jobs, L.first, L.planes, L.rows, L);
-        hipLaunchKernelGGL(k_resident_close<ISLF_SPIN_INT8>, gr, b, 0, s, L);
-    } else {
-        if (small) hipLaunchKernelGGL((k_resident<ISLF_SPIN_BITPACK, true>), g, b, lds, s, L.descs, L.st, L.jobs, L.first, L.planes, L.rows, L);
-        else hipLaunchKernelGGL((k_resident<ISLF_SPIN_BITPACK, false>), g, b, lds, s, L.descs, L.st, L.jobs, L.first, L.planes, L.rows, L);
-        hipLaunchKernelGGL(k_resident_close<ISLF_SPIN_BITPACK>, gr, b, 0, s, L);
-    }
+    const dim3 b(kResThreads);
+    hipLaunchKernelGGL(resident_kernel(fmt, form), dim3(L.grid), b, lds, s, L.descs, L.st, L.jobs, L.first, L.planes,
+                       L.rows, L);
+    if (fmt == ISLF_SPIN_INT8) hipLaunchKernelGGL(k_resident_close<ISLF_SPIN_INT8>, dim3(L.nreps), b, 0, s, L);
+    else hipLaunchKernelGGL(k_resident_close<ISLF_SPIN_BITPACK>, dim3(L.nreps), b, 0, s, L);
     return hipGetLastError();
 }
 

@@ -120,3 +120,17 @@ def test_contexts_on_two_threads():
     for k in range(2):
         _, rec, s = oracle_trajectory(ps[k], 40)
         assert np.array_equal(out[k][0], rec) and np.array_equal(out[k][1], s), k
+
+
+@pytest.mark.parametrize("fmt", [islf.INT8, islf.BITPACK])
+@pytest.mark.parametrize("shape", [(25, 76, 76), (24, 40, 94), (30, 60, 126), (14, 90, 42), (60, 40, 300),
+                                   (120, 12, 200)])
+def test_few_words_a_stage(fmt, shape):
+    # four lanes to a word: partial words of 2 to 8 groups, rows without a whole word, cuts along y and along x;
+    # the four-site table, a bulk field, and moves that are never accepted
+    ps = [config1(Lx=shape[0], Ly=shape[1], Lz=shape[2], ybc=ybc, beta=b, H=H, replica=i)
+          for i, (ybc, b, H) in enumerate(((O.GAPBC, 1 / 3, 0.0), (O.APBC, 0.6, 0.3), (O.PBC, 40.0, 0.1)))]
+    with islf.Context([islf.Replica(**p) for p in ps], spin_format=fmt, obs_capacity=32) as ctx:
+        ctx.sweep(2)
+        ctx.sweep(5)
+        check(ctx, ps, 7)
