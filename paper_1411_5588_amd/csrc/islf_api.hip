@@ -3039,6 +3039,61 @@ extern "C" islf_status islf_testing_abort_resident(islf_ctx *ctx)
     return ISLF_OK;
 }
 
+// Test support, not part of the public header: the plan of a resident launch
+// over n films on a device of num_cu CUs, built on the host, as a list of
+// int32: form, grid, jobs, mailbox words; then per job its replica, shares,
+// id, workgroup, rows, words of a row, whole ones, groups of the last one,
+// has, in, slot, out_y, out_x, planes (count, x of each), row sets (count, y of
+// each, chunks of whole and of partial words) and stages (count, parts (set,
+// phase, c0, c1) and the phases taken in).  *len: the words there are (0: no
+// plan); at most `room` are written.
+extern "C" islf_status islf_testing_resident_plan(const islf_replica_desc *descs, int32_t n, int32_t spin_format,
+                                                  int32_t num_cu, int32_t *out, int64_t room, int64_t *len)
+{
+    if (!descs || n < 1 || !len || (room > 0 && !out)) return fail(ISLF_EINVAL, "NULL argument");
+    *len = 0;
+    islf_ctx c;
+    c.fmt = spin_format;
+    c.num_cu = num_cu;
+    std::vector<int> reps(n);
+    c.reps.resize(n);
+    for (int i = 0; i < n; ++i) {
+        const islf_status st = validate(&descs[i]);
+        if (st != ISLF_OK) return st;
+        c.reps[i].desc = descs[i];
+        reps[i] = i;
+    }
+    ResPlan p;
+    ResTablesHost h;
+    if (!plan_resident(&c, reps, p, h)) return ISLF_OK;
+    std::vector<int32_t> v = {p.form, p.L.grid, p.L.njobs, (int32_t)h.mbox_words};
+    for (int w = 0; w < p.L.grid; ++w)
+        for (int q = h.first[w]; q < h.first[w + 1]; ++q) {
+            const ResJob &j = h.jobs[q];
+            const islf_replica_desc &d = descs[j.rep];
+            const int np = j.n1 + j.n2;
+            v.insert(v.end(), {j.rep, j.P, j.id, w, j.R, (d.Lz + 63) / 64, j.Wf, j.ng, j.has, (int32_t)j.in,
+                               (int32_t)j.slot, (int32_t)j.out_y[0], (int32_t)j.out_y[1], (int32_t)j.out_x[0],
+                               (int32_t)j.out_x[1], np});
+            for (int k = 0; k < np; ++k) v.push_back(h.planes[j.planes + k].x);
+            for (const ResRows &r : j.set) {
+                v.push_back(r.n);
+                for (int k = 0; k < r.n; ++k) v.push_back(h.rows[j.rows + r.r0 + k].y);
+                v.push_back(r.whole);
+                v.push_back(r.part);
+            }
+            v.push_back(j.stages);
+            for (int t = 0; t < j.stages; ++t) {
+                for (const ResPart &r : j.stage[t].part) v.insert(v.end(), {r.set, r.phase, r.c0, r.c1});
+                v.push_back(j.stage[t].mail);
+                v.push_back(j.stage[t].mail_row0);
+            }
+        }
+    *len = (int64_t)v.size();
+    std::copy(v.begin(), v.begin() + std::min<int64_t>(*len, room), out);
+    return ISLF_OK;
+}
+
 extern "C" islf_status islf_set_taper(islf_ctx *ctx, double taper)
 {
     if (!ctx) return fail(ISLF_EINVAL, "NULL context");

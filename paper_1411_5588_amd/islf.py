@@ -132,6 +132,7 @@ def lib():
             "islf_get_taper": [vp, P(dbl)],
             "islf_testing_raise_barrier_error": [vp],
             "islf_testing_abort_resident": [vp],
+            "islf_testing_resident_plan": [vp, C.c_int32, C.c_int32, C.c_int32, vp, C.c_int64, vp],
         }
         for name, args in sig.items():
             f = getattr(L, name)
