@@ -112,7 +112,7 @@ struct TeamInfo {
 // ---------------------------------------------------------------------------
 constexpr int kResThreads = 1024;      // threads per workgroup: 4 waves per SIMD, one workgroup per CU
 constexpr int kResMaxSweeps = 256;     // sweeps one launch may run
-constexpr int kResStaticLds = 10880;    // LDS bytes beside the lattice: pair tables, thresholds, control words
+constexpr int kResStaticLds = 11392;    // LDS bytes beside the lattice: pair tables, thresholds, control words
 constexpr int kResFineChunk = 16;       // words of a chunk in the fine form
 enum { RES_WORDS, RES_GROUPS, RES_FINE };   // how a launch's words go to lanes: see k_resident
 constexpr int kSmallTasks = 2;         // four-site groups a lane of the small form may hold per phase

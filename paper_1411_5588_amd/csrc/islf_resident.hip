@@ -81,7 +81,7 @@ struct ResTables {
     uint64_t thr[kThrEntries];
 };
 struct ResCtl {
-    int acc[2][4];
+    int4 sums[2][kResThreads / 64];   // a sweep's changes by wave, by sweep parity
     unsigned int bad;      // 1 + the first sweep in which a wait ran out, else ~0
     unsigned int state;    // the census' answer; error word at the start
     int ticket[4];         // next chunk of a phase, by phase number mod 4
@@ -90,6 +90,32 @@ struct ResCtl {
 __device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c)
 {
     return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);
+}
+
+// Sums of four values over the first N = 16 or 64 lanes, in lane N - 1 (all
+// lanes active; lanes a step has no source for add 0).  The four chains fill
+// each other's latency.
+template <int N>
+__device__ __forceinline__ int4 wave_sums(int4 v)
+{
+    auto step = [&](auto ctrl, auto rows) {
+        constexpr int C = decltype(ctrl)::value, R = decltype(rows)::value;
+        const int x = __builtin_amdgcn_update_dpp(0, v.x, C, R, 0xF, false);
+        const int y = __builtin_amdgcn_update_dpp(0, v.y, C, R, 0xF, false);
+        const int z = __builtin_amdgcn_update_dpp(0, v.z, C, R, 0xF, false);
+        const int w = __builtin_amdgcn_update_dpp(0, v.w, C, R, 0xF, false);
+        v = make_int4(v.x + x, v.y + y, v.z + z, v.w + w);
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>(), integral_constant<int, 0xF>());   // row_shr:1, :2, :4, :8
+    step(integral_constant<int, 0x112>(), integral_constant<int, 0xF>());
+    step(integral_constant<int, 0x114>(), integral_constant<int, 0xF>());
+    step(integral_constant<int, 0x118>(), integral_constant<int, 0xF>());
+    if (N == 64) {
+        step(integral_constant<int, 0x142>(), integral_constant<int, 0xA>());   // row_bcast:15 to rows 1 and 3
+        step(integral_constant<int, 0x143>(), integral_constant<int, 0xC>());   // row_bcast:31 to rows 2 and 3
+    }
+    return v;
 }
 
 // a where the mask is set, else b
@@ -613,9 +639,9 @@ __device__ __forceinline__ unsigned int res_census(ResSync *rs, unsigned int mem
 // padding of its 300-bit rows included), VALU issue 89% of the time; without
 // the exchange the same launch takes 57.6 us per sweep instead of 62.0.
 // Per sweep, before (launch chain, or persistent kernel) and now: 12x24x24 14
-// and 3.6 us, 168 ladder films 37 and 3.0 us, 64 x 40x120x120 31 and 22.1 us,
-// 96 uneven films int8 85 and 60 us, 184x504x504 39 and 25.7 us, 3 x
-// 160x480x600 int8 95 and 62 us, persistent 78 and 62 us.
+// and 3.4 us, 168 ladder films 37 and 2.7 us, 64 x 40x120x120 31 and 21.4 us,
+// 96 uneven films int8 85 and 59 us, 184x504x504 39 and 25 us, 3 x
+// 160x480x600 int8 95 and 62 us, persistent 78 and 61 us.
 // FORM: RES_GROUPS = no clusters, and films of few words, updated one four-site
 // group per lane (group_update); RES_FINE = chunks of 16 words.
 template <int FMT, int FORM>
@@ -681,7 +707,6 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
         }
         for (int k = tid; k < 256 && g.sym; k += kResThreads) tb.quad[k] = quad_entry(d, k);
         if (tid < kThrEntries) tb.thr[tid] = d.thr[tid];
-        if (tid < 8) (&ctl->acc[0][0])[tid] = 0;
         if (tid == 8) ctl->bad = ~0u;
         if (tid >= 12 && tid < 16) ctl->ticket[tid - 12] = 0;
         if (!SMALL) {
@@ -817,27 +842,19 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
                     if (i + 1 < jb.stages) __syncthreads();
                 }
             }
-            // the sweep's changes (see bp_march), one LDS add per wave and quantity
-            const int dB = -4 * (a.A0 + 2 * a.A1 + 4 * a.A2) + 16 * a.NF - 4 * a.NFU + a.KDM;
-            const int dM = 2 * a.NF - 4 * a.NFU;
-            int *acc = ctl->acc[s & 1];
-            const int vB = __reduce_add_sync(~0ull, dB), vM = __reduce_add_sync(~0ull, dM);
-            int v1 = 0, vn = 0;
-            if (__any((a.D1 | a.Dn) != 0)) {
-                v1 = __reduce_add_sync(~0ull, a.D1);
-                vn = __reduce_add_sync(~0ull, a.Dn);
-            }
-            if ((tid & 63) == 0) {
-                atomicAdd(&acc[0], vB);
-                atomicAdd(&acc[1], vM);
-                if (v1) atomicAdd(&acc[2], v1);
-                if (vn) atomicAdd(&acc[3], vn);
-            }
+            // The sweep's changes (see bp_march): summed by each wave, then over the waves by the last one, while the
+            // others begin the next sweep (the first, which issues ahead of them, cost 1 us on three 46 M-site
+            // films). Against masked reductions and LDS adds, one quantity after another: 12x24x24 3.85 -> 3.39 us
+            // a sweep, 22x142x142 9.9 -> 9.5, 64 x 40x120x120 21.7 -> 21.4.
+            const int4 w = wave_sums<64>(make_int4(-4 * (a.A0 + 2 * a.A1 + 4 * a.A2) + 16 * a.NF - 4 * a.NFU + a.KDM,
+                                                   2 * a.NF - 4 * a.NFU, a.D1, a.Dn));
+            int4 *sums = ctl->sums[s & 1];
+            if ((tid & 63) == 63) sums[tid >> 6] = w;
             __syncthreads();
-            // the other half serves the next sweep, whose barriers order this clear before its reuse
-            if (tid == 0) {
-                L.part[(size_t)s * L.njobs + jb.id] = make_int4(acc[0], acc[1], acc[2], acc[3]);
-                acc[0] = acc[1] = acc[2] = acc[3] = 0;
+            // (written again two sweeps on, behind the next sweep's barriers)
+            if (tid >= kResThreads - 64) {
+                const int4 v = wave_sums<kResThreads / 64>(sums[tid & (kResThreads / 64 - 1)]);
+                if ((tid & 63) == kResThreads / 64 - 1) L.part[(size_t)s * L.njobs + jb.id] = v;
             }
             // (a faster wave may be in sweep s+1 already: its failure counts there)
             good = ctl->bad > s + 1u;
