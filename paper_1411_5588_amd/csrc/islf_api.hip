@@ -1118,7 +1118,7 @@ struct ResTablesHost {
 template <class PUT>
 static void cut_film(const islf_replica_desc &d, int rep, int px, int py, int form, int &id, ResTablesHost &h, PUT put)
 {
-    const ShareCost k(d);
+    const ShareCost k(d, form == RES_FINE);   // the split that was checked against the LDS
     const int P = px * py;
     const uint32_t Wq = (uint32_t)k.Wq;
     int rows0, rmax;
@@ -1374,6 +1374,7 @@ static bool plan_resident(islf_ctx *c, const std::vector<int> &reps, ResPlan &p,
                  });
         if (h.mbox_words >= (1ull << 29)) return false;   // 32-bit byte offsets
     }
+    if (p.lds > kLatticeLds) return false;   // (a launch that asks for more is refused)
     // a workgroup's cluster share comes before its single films
     h.first.assign(1, 0);
     for (int w = 0; w < NW; ++w) {
