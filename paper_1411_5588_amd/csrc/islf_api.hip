@@ -696,16 +696,20 @@ static islf_status upload_plan(islf_ctx *c, Plan &p, const std::vector<Entry> &i
 static islf_status sync_tables(islf_ctx *c)
 {
     if (!c->dirty) return ISLF_OK;
-    c->live.clear();
+    // (the lists in use stay whole if the new one cannot be had)
+    std::vector<int> live;
     const int n = (int)c->reps.size();
     for (int i = 0; i < n; ++i)
-        if (c->reps[i].live) c->live.push_back(i);
-    if ((int)c->live.size() > c->live_capacity) {
+        if (c->reps[i].live) live.push_back(i);
+    if ((int)live.size() > c->live_capacity) {
+        const int cap = std::max<int>((int)live.size(), 2 * c->live_capacity);
+        int *d = (int *)dev_alloc(c, sizeof(int) * cap);
+        if (!d) return fail(ISLF_ENOMEM, "cannot allocate live list");
         dev_free(c, c->d_live);
-        c->live_capacity = std::max<int>((int)c->live.size(), 2 * c->live_capacity);
-        c->d_live = (int *)dev_alloc(c, sizeof(int) * c->live_capacity);
-        if (!c->d_live) return fail(ISLF_ENOMEM, "cannot allocate live list");
+        c->d_live = d;
+        c->live_capacity = cap;
     }
+    c->live = std::move(live);
     if (!c->live.empty())
         HIP_TRY(hipMemcpyAsync(c->d_live, c->live.data(), sizeof(int) * c->live.size(), hipMemcpyHostToDevice, c->stream));
     std::vector<RepDesc> all(n);
@@ -2477,8 +2481,12 @@ extern "C" islf_status islf_batch_add(islf_ctx *ctx, const islf_replica_desc *de
     if (st == ISLF_OK && e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) st = fail(ISLF_EDEVICE, "replica init failed: %s", hipGetErrorString(e));
     if (st != ISLF_OK) {
+        // the tables without it again (they were not replaced if there was no memory)
+        const std::string keep = g_err;
         ctx->reps[s].live = false;
         ctx->dirty = true;
+        (void)sync_tables(ctx);
+        g_err = keep;
         return st;
     }
     *slot = s;
