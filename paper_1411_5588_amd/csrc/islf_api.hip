@@ -235,7 +235,7 @@ struct Plan {
 struct ResPlan {
     bool valid = false;    // built for the current replicas
     bool usable = false;   // they fit and the form is expected to be the faster one
-    ResLaunch L{};         // tables (device memory) and counts; n, check_error and part per launch
+    ResLaunch L{};         // the plan's tables (device memory) and counts; the rest is the context's, filled in per launch
     size_t jobs_b = 0, first_b = 0, planes_b = 0, rows_b = 0, reps_b = 0, part_b = 0, mbox_b = 0;   // bytes allocated
     std::vector<int4 *> outgrown;   // smaller sum buffers that captured graphs may still use
     int form = RES_WORDS;  // RES_GROUPS: no clusters and few words per film; RES_FINE: few words per stage
@@ -1453,10 +1453,6 @@ static islf_status build_resident(islf_ctx *c, ResPlan &p, const std::vector<int
     HIP_TRY(e);
     HIP_TRY(es);
     if (!p.L.mbox) return ISLF_OK;
-    p.L.descs = c->d_desc;
-    p.L.st = c->d_state;
-    p.L.rs = c->d_rsy;
-    p.L.sync = c->d_sync;
     p.usable = true;
     return ISLF_OK;
 }
@@ -1519,6 +1515,10 @@ static hipError_t enqueue_resident(islf_ctx *c, uint32_t n)
 {
     auto run = [&](const ResPlan &p) -> hipError_t {
         ResLaunch L = p.L;
+        L.descs = c->d_desc;
+        L.st = c->d_state;
+        L.rs = c->d_rsy;
+        L.sync = c->d_sync;
         L.check_error = c->exec == ISLF_EXEC_PERSISTENT;
         hipError_t e = hipSuccess;
         for (uint32_t done = 0; done < n && e == hipSuccess; done += L.n) {

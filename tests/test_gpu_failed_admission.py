@@ -51,7 +51,7 @@ def check(ctx, n, skip=(), means=True):
 
 
 @pytest.mark.parametrize("mode", [islf.EXEC_PLAIN, islf.EXEC_BATCHED])
-@pytest.mark.parametrize("nth", [4])   # the live list
+@pytest.mark.parametrize("nth", [3, 4])   # the replica's block, once the tables have grown; the live list
 def test_batch_goes_on_after_a_refused_admission(monkeypatch, nth, mode):
     monkeypatch.setattr(islf, "_TorchAllocator", Refusing)
     with islf.Context([islf.Replica(**film(r)) for r in range(N)], spin_format=islf.BITPACK, obs_capacity=32,
