@@ -1600,12 +1600,13 @@ static islf_status add_replica(islf_ctx *c, const islf_replica_desc *desc, int *
             slot = i;
             break;
         }
+    // no slot without a place in the device tables: they are uploaded whole
+    st = ensure_slots(c, slot < 0 ? (int)c->reps.size() + 1 : (int)c->reps.size());
+    if (st != ISLF_OK) return st;
     if (slot < 0) {
         slot = (int)c->reps.size();
         c->reps.emplace_back();
     }
-    st = ensure_slots(c, (int)c->reps.size());
-    if (st != ISLF_OK) return st;
     Replica &R = c->reps[slot];
     R.desc = *desc;
     const size_t bytes = replica_bytes(desc, c->fmt, c->cap);
