@@ -16,6 +16,7 @@
 #include <map>
 #include <string>
 #include <thread>
+#include <type_traits>
 #include <unordered_map>
 #include <vector>
 
@@ -237,7 +238,6 @@ struct ResPlan {
     bool usable = false;   // they fit and the form is expected to be the faster one
     ResLaunch L{};         // the plan's tables (device memory) and counts; the rest is the context's, filled in per launch
     size_t jobs_b = 0, first_b = 0, planes_b = 0, rows_b = 0, reps_b = 0, part_b = 0, mbox_b = 0;   // bytes allocated
-    std::vector<int4 *> outgrown;   // smaller sum buffers that captured graphs may still use
     int form = RES_WORDS;  // RES_GROUPS: no clusters and few words per film; RES_FINE: few words per stage
     size_t lds = 0;
     uint32_t max_sweeps = 0;
@@ -948,7 +948,6 @@ static void free_resident(islf_ctx *c, ResPlan &p)
     dev_free(c, (void *)p.L.rows);
     dev_free(c, (void *)p.L.reps);
     dev_free(c, p.L.part);
-    for (int4 *o : p.outgrown) dev_free(c, o);
     dev_free(c, p.L.mbox);
     p = ResPlan();
 }
@@ -1416,8 +1415,6 @@ static islf_status build_resident(islf_ctx *c, ResPlan &p, const std::vector<int
 {
     p.valid = true;
     p.usable = false;
-    for (int4 *o : p.outgrown) dev_free(c, o);
-    p.outgrown.clear();
     ResTablesHost h;
     if (reps.empty() || !plan_resident(c, reps, p, h)) return ISLF_OK;
     long long sites = 0;
@@ -1430,7 +1427,7 @@ static islf_status build_resident(islf_ctx *c, ResPlan &p, const std::vector<int
     p.chain_us = chain_sweep_us(c, sites, (int)reps.size());
     p.fixed_us = 16.0 + 2.0 * (double)bytes / 2.0e6;
     if (p.sweep_us >= p.chain_us) return ISLF_OK;
-    // per-sweep sums: 8 MiB at most (allocated by the longest run, see size_sums)
+    // per-sweep sums: 8 MiB at most, had here for the longest launch, so that runs allocate nothing
     p.max_sweeps = (uint32_t)std::max<size_t>(1, std::min<size_t>(kResMaxSweeps, (8u << 20) / (16 * (size_t)p.L.njobs)));
     hipError_t e = hipSuccess;
     if (!put_table(c, p.L.jobs, p.jobs_b, h.jobs, e) || !put_table(c, p.L.first, p.first_b, h.first, e) ||
@@ -1439,35 +1436,23 @@ static islf_status build_resident(islf_ctx *c, ResPlan &p, const std::vector<int
         (void)hipStreamSynchronize(c->stream);   // no copy may outlive its source
         return ISLF_OK;
     }
-    const size_t mb = 8 * std::max<size_t>(1, h.mbox_words);
-    if (mb > p.mbox_b) {
-        dev_free(c, p.L.mbox);
-        p.mbox_b = 0;
-        p.L.mbox = (unsigned long long *)dev_alloc(c, mb);
-        if (p.L.mbox) p.mbox_b = mb;
-    }
+    auto grow = [&](auto *&ptr, size_t &have, size_t bytes) {
+        if (bytes <= have) return;
+        dev_free(c, ptr);
+        ptr = (std::remove_reference_t<decltype(ptr)>)dev_alloc(c, bytes);
+        have = ptr ? bytes : 0;
+    };
+    grow(p.L.mbox, p.mbox_b, 8 * std::max<size_t>(1, h.mbox_words));
+    grow(p.L.part, p.part_b, sizeof(int4) * p.max_sweeps * (size_t)p.L.njobs);
     // no mailbox word may carry an epoch still to come
     if (e == hipSuccess && p.L.mbox) e = launch_zero(p.L.mbox, (long)h.mbox_words, c->stream);
     if (e == hipSuccess) e = resident_lds_limit(c->fmt, kLatticeLds);
     const hipError_t es = hipStreamSynchronize(c->stream);
     HIP_TRY(e);
     HIP_TRY(es);
-    if (!p.L.mbox) return ISLF_OK;
+    if (!p.L.mbox || !p.L.part) return ISLF_OK;
     p.usable = true;
     return ISLF_OK;
-}
-
-// Room for the per-sweep sums of a run of n sweeps.
-static bool size_sums(islf_ctx *c, ResPlan &p, uint32_t n)
-{
-    const size_t bytes = sizeof(int4) * std::min(n, p.max_sweeps) * (size_t)p.L.njobs;
-    if (bytes <= p.part_b) return true;
-    int4 *np = (int4 *)dev_alloc(c, bytes);
-    if (!np) return false;
-    if (p.L.part) p.outgrown.push_back(p.L.part);
-    p.L.part = np;
-    p.part_b = bytes;
-    return true;
 }
 
 // Whether a run of n sweeps takes the resident form (its plans are then
@@ -1503,10 +1488,6 @@ static islf_status resident_applies(islf_ctx *c, uint32_t n, bool *use)
         if (st != ISLF_OK) return st;
     }
     *use = res < chain;
-    // without room for the sums the launch chain does it
-    if (c->exec == ISLF_EXEC_PLAIN)
-        for (size_t i = 0; i < c->live.size() && *use; ++i) *use = size_sums(c, c->resident_plain[c->live[i]], n);
-    else if (*use) *use = size_sums(c, c->resident, n);
     return ISLF_OK;
 }
 
