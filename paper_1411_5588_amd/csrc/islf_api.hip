@@ -234,14 +234,17 @@ struct Plan {
 // A launch of the resident form over some replicas: shares (jobs) by
 // workgroup, cluster workgroups first, with their mailboxes and per-sweep sums.
 struct ResPlan {
-    bool valid = false;    // built for the current replicas
-    bool usable = false;   // they fit and the form is expected to be the faster one
+    bool valid = false;    // planned for the current replicas
+    bool usable = false;   // they fit and the tables are on the device
+    bool put_off = false;  // they fit, but the launch chain was the faster form when it was planned: no tables yet
     ResLaunch L{};         // the plan's tables (device memory) and counts; the rest is the context's, filled in per launch
     size_t jobs_b = 0, first_b = 0, planes_b = 0, rows_b = 0, reps_b = 0, part_b = 0, mbox_b = 0;   // bytes allocated
     int form = RES_WORDS;  // RES_GROUPS: no clusters and few words per film; RES_FINE: few words per stage
     size_t lds = 0;
     uint32_t max_sweeps = 0;
-    double sweep_us = 0.0, fixed_us = 0.0, chain_us = 0.0;   // expected: per sweep, per launch; a sweep of the launch chain
+    double sweep_us = 0.0, fixed_us = 0.0;   // expected: per sweep, per launch
+    long long sites = 0;
+    int nreps = 0;
 };
 
 // A number of shares worth taking for a film: fewer are slower.
@@ -1095,7 +1098,7 @@ static std::vector<ShareChoice> share_choices(const islf_replica_desc &d, bool f
 
 static uint32_t magic_of(int d) { return d >= 2 ? (uint32_t)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d) : 0u; }
 
-// A sweep of the launch chain, measured: one chain takes 20 us a sweep in
+// A sweep of the launch chain in the context's form, measured: one chain takes 20 us a sweep in
 // launches whose work does not overlap (19.5 us per launch of a 46 M-site
 // bit-packed film), concurrent groups hide all but a few us of that on large
 // replicas (3 x 160x480x600: 57 us bit-packed, 95 us int8) and less on many
@@ -1414,19 +1417,20 @@ static bool put_table(islf_ctx *c, const T *&ptr, size_t &have, const std::vecto
 static islf_status build_resident(islf_ctx *c, ResPlan &p, const std::vector<int> &reps)
 {
     p.valid = true;
-    p.usable = false;
+    p.usable = p.put_off = false;
     ResTablesHost h;
     if (reps.empty() || !plan_resident(c, reps, p, h)) return ISLF_OK;
-    long long sites = 0;
+    p.sites = 0;
+    p.nreps = (int)reps.size();
     size_t bytes = 0;
     for (int r : reps) {
         const islf_replica_desc &d = c->reps[r].desc;
-        sites += (long long)d.Lx * d.Ly * d.Lz;
+        p.sites += (long long)d.Lx * d.Ly * d.Lz;
         bytes += spin_bytes(&d, c->fmt);
     }
-    p.chain_us = chain_sweep_us(c, sites, (int)reps.size());
     p.fixed_us = 16.0 + 2.0 * (double)bytes / 2.0e6;
-    if (p.sweep_us >= p.chain_us) return ISLF_OK;
+    p.put_off = p.sweep_us >= chain_sweep_us(c, p.sites, p.nreps);
+    if (p.put_off) return ISLF_OK;
     // per-sweep sums: 8 MiB at most, had here for the longest launch, so that runs allocate nothing
     p.max_sweeps = (uint32_t)std::max<size_t>(1, std::min<size_t>(kResMaxSweeps, (8u << 20) / (16 * (size_t)p.L.njobs)));
     hipError_t e = hipSuccess;
@@ -1469,12 +1473,13 @@ static islf_status resident_applies(islf_ctx *c, uint32_t n, bool *use)
         if (c->reps[r].tile_set) return ISLF_OK;
     double res = 0.0, chain = 0.0;
     auto add = [&](ResPlan &p, const std::vector<int> &reps) -> islf_status {
-        if (!p.valid) {
+        // (the chain's time depends on the execution form, which may have changed since the plan was built)
+        if (!p.valid || (p.put_off && p.sweep_us < chain_sweep_us(c, p.sites, p.nreps))) {
             islf_status s = build_resident(c, p, reps);
             if (s != ISLF_OK) return s;
         }
         res += p.usable ? p.fixed_us * (double)((n + p.max_sweeps - 1) / p.max_sweeps) + n * p.sweep_us : 1e300;
-        chain += 8.0 + n * p.chain_us;
+        chain += 8.0 + n * chain_sweep_us(c, p.sites, p.nreps);
         return ISLF_OK;
     };
     if (c->exec == ISLF_EXEC_PLAIN) {
@@ -3028,6 +3033,17 @@ extern "C" islf_status islf_testing_abort_resident(islf_ctx *ctx)
     HIP_TRY(hipMemcpyAsync(&ctx->d_rsy->state, &v, sizeof v, hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     return ISLF_OK;
+}
+
+// Test support, not part of the public header: whether a run of n sweeps would
+// take the resident form now.
+extern "C" islf_status islf_testing_takes_resident(islf_ctx *ctx, uint32_t n, int32_t *takes)
+{
+    if (!ctx || !takes) return fail(ISLF_EINVAL, "NULL argument");
+    bool use = false;
+    const islf_status st = resident_applies(ctx, n, &use);
+    *takes = use ? 1 : 0;
+    return st;
 }
 
 // Test support, not part of the public header: the plan of a resident launch
