@@ -270,6 +270,12 @@ struct islf_ctx {
     int sweep_slots = 0;       // default workgroups per sweep launch (2 per resident slot)
     int grid_override = 0;     // workgroups per batched / plain launch (0: sweep_slots)
     double taper_override = -1.0;   // share taper of the batched and persistent plans (< 0: the built-in one)
+    // islf_autotune's launch configuration of the chain is in use, not a caller's;
+    // tuned_us: a sweep of this batch with it, measured (0: of another batch), in form tuned_exec
+    bool tuned = false;
+    double tuned_us = 0.0;
+    int tuned_exec = -1;
+    bool chain_only = false;   // while it is being tuned
     int persistent_grid = 0;   // workgroups of the persistent kernel's cooperative launch
     int persistent_bound = 0;  // co-residency bound computed for it on this device
     double *noalloc_scratch = nullptr;   // this device's copy of the means scratch array
@@ -725,6 +731,7 @@ static islf_status sync_tables(islf_ctx *c)
     c->groups_valid = false;
     c->resident.valid = false;
     for (ResPlan &p : c->resident_plain) p.valid = false;
+    c->tuned_us = 0.0;
     c->dirty = false;
     c->graph_valid = false;
     return ISLF_OK;
@@ -1098,6 +1105,8 @@ static std::vector<ShareChoice> share_choices(const islf_replica_desc &d, bool f
 
 static uint32_t magic_of(int d) { return d >= 2 ? (uint32_t)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d) : 0u; }
 
+constexpr double kChainRunUs = 8.0;   // of a run of the launch chain, beside its sweeps
+
 // A sweep of the launch chain in the context's form, measured: one chain takes 20 us a sweep in
 // launches whose work does not overlap (19.5 us per launch of a 46 M-site
 // bit-packed film), concurrent groups hide all but a few us of that on large
@@ -1105,6 +1114,7 @@ static uint32_t magic_of(int d) { return d >= 2 ? (uint32_t)(((1ull << 32) + (un
 // small ones (64 x 40x120x120: 31 us bit-packed).
 static double chain_sweep_us(const islf_ctx *c, long long sites, int nreps)
 {
+    if (c->tuned && c->tuned_us > 0.0 && c->exec == c->tuned_exec) return c->tuned_us;
     const double work = (double)sites / (c->fmt == ISLF_SPIN_BITPACK ? 2.65e6 : 1.53e6);
     if (c->exec != ISLF_EXEC_BATCHED || nreps == 1) return std::max(14.0, 20.0 + work);
     return std::max(20.0, 5.0 + 0.15 * nreps + work);
@@ -1459,16 +1469,23 @@ static islf_status build_resident(islf_ctx *c, ResPlan &p, const std::vector<int
     return ISLF_OK;
 }
 
+// Whether the caller has chosen a launch configuration of the chain or of the persistent kernel.
+static bool config_chosen(const islf_ctx *c)
+{
+    return !c->tuned && (c->grid_override || c->groups_req || c->taper_override >= 0.0 || c->team_mode >= 0);
+}
+
 // Whether a run of n sweeps takes the resident form (its plans are then
 // built).  A launch configuration chosen by the caller (grid, groups, taper,
-// barriers, a tile) asks for the launch chain or the persistent kernel.
+// barriers, a tile) asks for the launch chain or the persistent kernel; one
+// that islf_autotune found is only the chain's own.
 static islf_status resident_applies(islf_ctx *c, uint32_t n, bool *use)
 {
     *use = false;
     islf_status st = sync_tables(c);
     if (st != ISLF_OK) return st;
     if (n == 0 || c->live.empty()) return ISLF_OK;
-    if (c->grid_override || c->groups_req || c->taper_override >= 0.0 || c->team_mode >= 0) return ISLF_OK;
+    if (c->chain_only || config_chosen(c)) return ISLF_OK;
     for (int r : c->live)
         if (c->reps[r].tile_set) return ISLF_OK;
     double res = 0.0, chain = 0.0;
@@ -1479,7 +1496,7 @@ static islf_status resident_applies(islf_ctx *c, uint32_t n, bool *use)
             if (s != ISLF_OK) return s;
         }
         res += p.usable ? p.fixed_us * (double)((n + p.max_sweeps - 1) / p.max_sweeps) + n * p.sweep_us : 1e300;
-        chain += 8.0 + n * chain_sweep_us(c, p.sites, p.nreps);
+        chain += kChainRunUs + n * chain_sweep_us(c, p.sites, p.nreps);
         return ISLF_OK;
     };
     if (c->exec == ISLF_EXEC_PLAIN) {
@@ -2729,7 +2746,10 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
     // persistent: barrier form x grid (up to the co-residency bound) x taper.
     // Each trial captures `sweeps` sweeps as graphs and times replays of
     // them; the chains advance during the trials and are restored once
-    // afterwards.
+    // afterwards.  The resident form has none of these settings: whether it
+    // is the faster one depends on a run's length, so each run decides, by
+    // the time measured here.
+    double tuned_ms = 0.0;
     if (result == ISLF_OK && !ctx->live.empty() &&
         (ctx->exec == ISLF_EXEC_BATCHED || ctx->exec == ISLF_EXEC_PERSISTENT)) {
         ctx->dirty = true;
@@ -2738,6 +2758,8 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
         const double keep_taper = ctx->taper_override;
         struct Trial { int groups, grid; double taper; int team; };
         const int keep_team = ctx->team_mode;
+        const bool chosen = config_chosen(ctx);
+        ctx->chain_only = true;
         std::vector<Trial> trials;
         const double tapers[] = {0.0, 0.1, 0.2};
         if (ctx->exec == ISLF_EXEC_BATCHED) {
@@ -2771,8 +2793,7 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
             ctx->groups_valid = false;
             ctx->batched.valid = false;
             ctx->persistent.valid = false;
-            bool resident = false;
-            islf_status rs = prepare_form(ctx, sweeps, &resident);
+            islf_status rs = prepare_plans(ctx, ctx->exec);
             if (rs != ISLF_OK) return rs;
             hipError_t e = hipSuccess;
             int G = 1;
@@ -2789,7 +2810,7 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
                         e = hipGraphLaunch(ctx->graph_execs[g], group_stream(ctx, g, G));
                     if (e == hipSuccess && G > 1) e = join_groups(ctx, G);
                 } else if (e == hipSuccess) {
-                    rs = enqueue_form(ctx, run == 0 ? 1 : sweeps, resident);
+                    rs = enqueue_sweeps(ctx, run == 0 ? 1 : sweeps);
                     if (rs != ISLF_OK) break;
                 }
                 if (run >= 1 && e == hipSuccess) {
@@ -2830,7 +2851,10 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
                     best_t = trials[first[k].second];
                 }
             }
+            tuned_ms = best;
         }
+        ctx->chain_only = false;
+        if (result == ISLF_OK) ctx->tuned = !chosen;
         if (e0) (void)hipEventDestroy(e0);
         if (e1) (void)hipEventDestroy(e1);
         ctx->groups_req = (result == ISLF_OK && best_t.groups) ? best_t.groups : keep_groups;
@@ -2852,7 +2876,10 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
     dev_free(ctx, st_backup);
     ctx->dirty = true;
     if (result != ISLF_OK) return result;
-    return sync_tables(ctx);
+    result = sync_tables(ctx);
+    ctx->tuned_us = std::max(0.0, 1e3 * tuned_ms - kChainRunUs) / sweeps;
+    ctx->tuned_exec = ctx->exec;
+    return result;
 }
 
 // 32-bit words per (x, y) row of the spin array
@@ -2899,6 +2926,7 @@ extern "C" islf_status islf_set_grid(islf_ctx *ctx, int32_t workgroups)
         return fail(ISLF_ERANGE, "persistent grid %d exceeds the co-residency bound %d of this device", workgroups,
                     ctx->persistent_bound);
     ctx->grid_override = workgroups;
+    ctx->tuned = false;
     ctx->batched.valid = false;
     ctx->persistent.valid = false;
     ctx->groups_valid = false;
@@ -2912,6 +2940,7 @@ extern "C" islf_status islf_set_groups(islf_ctx *ctx, int32_t groups)
     if (!ctx) return fail(ISLF_EINVAL, "NULL context");
     if (groups < 0 || groups > kMaxStreamGroups) return fail(ISLF_EINVAL, "invalid group count %d", groups);
     ctx->groups_req = groups;
+    ctx->tuned = false;
     ctx->groups_valid = false;
     ctx->graph_valid = false;
     return ISLF_OK;
@@ -3106,6 +3135,7 @@ extern "C" islf_status islf_set_taper(islf_ctx *ctx, double taper)
     if (!ctx) return fail(ISLF_EINVAL, "NULL context");
     if (!(taper < 1.0)) return fail(ISLF_EINVAL, "taper must be below 1 (got %g)", taper);
     ctx->taper_override = taper < 0.0 ? -1.0 : taper;
+    ctx->tuned = false;
     ctx->batched.valid = false;
     ctx->persistent.valid = false;
     ctx->groups_valid = false;
@@ -3129,6 +3159,7 @@ extern "C" islf_status islf_set_barriers(islf_ctx *ctx, int32_t mode)
     if (mode != ISLF_BARRIER_GRID && mode != ISLF_BARRIER_TEAM && mode != ISLF_BARRIER_AUTO)
         return fail(ISLF_EINVAL, "invalid barrier mode %d", mode);
     ctx->team_mode = mode == ISLF_BARRIER_TEAM ? 1 : mode == ISLF_BARRIER_GRID ? 0 : -1;
+    ctx->tuned = false;
     ctx->persistent.valid = false;
     ctx->graph_valid = false;
     return ISLF_OK;

@@ -40,3 +40,17 @@ def test_choice_does_not_depend_on_the_forms_before():
             for form in order + order[:1]:
                 ctx.set_exec(form)
                 assert [takes_resident(ctx, n) for n in (2, 100)] == want[form], (order, form)
+
+
+@pytest.mark.parametrize("mode", [islf.EXEC_BATCHED, islf.EXEC_PERSISTENT])
+@pytest.mark.parametrize("shape,n", [((12, 24, 24), 1), ((20, 64, 64), 24), ((40, 120, 120), 16)])
+def test_tuning_leaves_long_runs_resident(shape, n, mode):
+    # trials of one or two sweeps, in which a resident launch cannot pay for itself, tune the launch chain only
+    ps = [config1(Lx=shape[0], Ly=shape[1], Lz=shape[2], replica=r) for r in range(n)]
+    with islf.Context([islf.Replica(**p) for p in ps], spin_format=islf.INT8, obs_capacity=64, exec_mode=mode) as ctx:
+        for sweeps in (1, 2):
+            assert takes_resident(ctx, 200) == 1
+            ctx.autotune(sweeps=sweeps)
+        assert takes_resident(ctx, 200) == 1
+        ctx.set_grid(256)      # the caller's own choice asks for the chain
+        assert takes_resident(ctx, 200) == 0
