@@ -14,6 +14,7 @@
 #include <array>
 #include <atomic>
 #include <map>
+#include <mutex>
 #include <string>
 #include <thread>
 #include <type_traits>
@@ -57,6 +58,7 @@ hipError_t launch_integrate(const double *h, const double *m1, const double *mn,
 hipError_t noalloc_scratch(double **out);
 hipError_t resident_lds_limit(int fmt, size_t bytes);
 hipError_t launch_resident(int fmt, int form, const ResLaunch &L, size_t lds, hipStream_t s);
+hipError_t launch_mark(ResSync *rs, unsigned long long *host, hipStream_t s);
 }  // namespace islf
 
 using namespace islf;
@@ -294,8 +296,8 @@ struct islf_ctx {
     int rsync_cap = 0;
     int team_mode = -1;        // 1: team barriers when every live replica can have a workgroup; 0: grid; -1: automatic
     unsigned long long *d_scratch = nullptr;   // 64 x u64
-    // what calls bring back, in pinned memory: word 0 the error word, results
-    // from word 8 on; and two windows for spins too many for it (made by the
+    // what calls bring back, in pinned memory: word 0 the error word, HOST_*,
+    // results from word 8 on; and two windows for spins too many for it (made by the
     // first call with such spins)
     unsigned long long *h_res = nullptr;
     int8_t *h_win = nullptr;
@@ -307,6 +309,17 @@ struct islf_ctx {
     ResPlan resident;                           // all live replicas (batched and persistent forms)
     std::vector<ResPlan> resident_plain;        // per slot (plain form)
     ResSync *d_rsy = nullptr;
+    // turns among the contexts of a device (see Turns; under its lock)
+    int device = 0;
+    hipEvent_t turn = nullptr;     // recorded behind every run with clusters
+    uint32_t issued = 0;           // launches that will count HOST_ENDED up
+    uint32_t aborts_seen = 0;
+    int members = 0;               // cluster workgroups of the launches in flight, at most
+    bool chain = false;            // the chain or the persistent kernel is in flight,
+    bool unmarked = false;         // and not counted in `issued`
+    bool chain_if_met = false;     // its last run with clusters would rather be a chain beside another context's
+    int apart = 0;                 // runs that keep to the chain
+    uint64_t cluster_runs = 0, chain_runs = 0;
     // batched form with concurrent replica groups: group g sweeps its
     // replicas on side_stream[g], a stream the context creates; the
     // context's stream only forks them and joins them
@@ -327,6 +340,11 @@ struct islf_ctx {
     std::vector<hipGraphExec_t> graph_execs;
     uint32_t graph_sweeps = 0;
     bool graph_valid = false;
+    int graph_exec = 0;             // the form it was captured in,
+    bool graph_resident = false;    // resident or not,
+    int graph_members = 0;          // with so many cluster workgroups at most
+    uint32_t graph_launches = 0;    // and so many resident launches;
+    bool graph_prefers_chain = false;
 
     // the cuts of the shapes planned so far (kMaxShapes at most)
     std::map<std::array<int, 4>, std::vector<ShareChoice>> choices;
@@ -1105,6 +1123,16 @@ static std::vector<ShareChoice> share_choices(const islf_replica_desc &d, bool f
 
 static uint32_t magic_of(int d) { return d >= 2 ? (uint32_t)(((1ull << 32) + (unsigned)d - 1) / (unsigned)d) : 0u; }
 
+static double chain_work_us(const islf_ctx *c, long long sites)
+{
+    return (double)sites / (c->fmt == ISLF_SPIN_BITPACK ? 2.65e6 : 1.53e6);
+}
+
+static double grouped_sweep_us(const islf_ctx *c, long long sites, int nreps)
+{
+    return 5.0 + 0.15 * nreps + chain_work_us(c, sites);
+}
+
 constexpr double kChainRunUs = 8.0;   // of a run of the launch chain, beside its sweeps
 
 // A sweep of the launch chain in the context's form, measured: one chain takes 20 us a sweep in
@@ -1115,9 +1143,8 @@ constexpr double kChainRunUs = 8.0;   // of a run of the launch chain, beside it
 static double chain_sweep_us(const islf_ctx *c, long long sites, int nreps)
 {
     if (c->tuned && c->tuned_us > 0.0 && c->exec == c->tuned_exec) return c->tuned_us;
-    const double work = (double)sites / (c->fmt == ISLF_SPIN_BITPACK ? 2.65e6 : 1.53e6);
-    if (c->exec != ISLF_EXEC_BATCHED || nreps == 1) return std::max(14.0, 20.0 + work);
-    return std::max(20.0, 5.0 + 0.15 * nreps + work);
+    if (c->exec != ISLF_EXEC_BATCHED || nreps == 1) return std::max(14.0, 20.0 + chain_work_us(c, sites));
+    return std::max(20.0, grouped_sweep_us(c, sites, nreps));
 }
 
 // The tables of a resident plan on the host.
@@ -1522,6 +1549,7 @@ static hipError_t enqueue_resident(islf_ctx *c, uint32_t n)
         L.st = c->d_state;
         L.rs = c->d_rsy;
         L.sync = c->d_sync;
+        L.host = c->h_res;
         L.check_error = c->exec == ISLF_EXEC_PERSISTENT;
         hipError_t e = hipSuccess;
         for (uint32_t done = 0; done < n && e == hipSuccess; done += L.n) {
@@ -1534,6 +1562,119 @@ static hipError_t enqueue_resident(islf_ctx *c, uint32_t n)
     hipError_t e = hipSuccess;
     for (size_t i = 0; i < c->live.size() && e == hipSuccess; ++i) e = run(c->resident_plain[c->live[i]]);
     return e;
+}
+
+// Contexts that sweep at the same time.  The workgroups of a cluster launch
+// wait for each other, and each needs a whole CU: two such launches dispatched
+// into each other would both give up, and a launch chain on other streams can
+// keep every CU partly busy for as long as it has launches queued.  So, for the
+// contexts of a process on one device (of different streams):
+//  - Cluster launches that do not all find a CU each beside those that others
+//    have in flight are ordered behind them.
+//  - A run of the chain is ordered behind the clusters that others have in flight.
+//  - While another context has a chain in flight, a run takes the chain too.
+//  - Where chains side by side are the faster form (see prefers_chain),
+//    contexts that met keep to the chain for kApartRuns runs; so does a context
+//    with a launch that the census called off (work of another process or of
+//    the caller on the CUs).
+// Measured, two contexts on threads of their own, 250 sweeps each, ms for both,
+// on the chain and so: 64 x 40x120x120 bit-packed 15.8 and 10.6 (in turn), 8 x
+// 28x94x94 12.3 and 2.5 (side by side), 3 x 160x480x600 int8 46 and 31 (in
+// turn), one 88x504x504 int8 12.0 and 8.1 (in turn), bit-packed 7.2 and 7.2 (on
+// the chain; in turn 8.2, and 16 against 14.0 for four contexts).
+// What is in flight is read from the counts that closing kernels write to
+// pinned memory (an event query from another thread would break a stream
+// capture in global mode there).  Runs that a caller captures on the context's
+// stream, and replays of them, are not seen: for them the census stands.
+struct Turns {
+    std::mutex m;
+    std::vector<islf_ctx *> all;
+};
+constexpr int kMaxDevices = 64, kApartRuns = 256;
+
+static Turns &turns(const islf_ctx *c)
+{
+    static Turns *t = new Turns[kMaxDevices];   // (outlives contexts closed at exit)
+    return t[c->device % kMaxDevices];
+}
+
+static bool in_flight(islf_ctx *o)
+{
+    const uint32_t ended = (uint32_t)__atomic_load_n(o->h_res + HOST_ENDED, __ATOMIC_RELAXED);
+    if (o->unmarked || (int32_t)(o->issued - ended) > 0) return true;
+    o->members = 0;
+    o->chain = false;
+    return false;
+}
+
+// After the host has waited for the context's stream.
+static void landed(islf_ctx *c)
+{
+    std::lock_guard<std::mutex> lock(turns(c).m);
+    c->issued = (uint32_t)__atomic_load_n(c->h_res + HOST_ENDED, __ATOMIC_RELAXED);
+    c->unmarked = c->chain = false;
+    c->members = 0;
+}
+
+static bool being_captured(const islf_ctx *c)
+{
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return c->stream && hipStreamIsCapturing(c->stream, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
+}
+
+// Whether clusters of `members` workgroups may be enqueued now (lock held), put
+// behind those of others where need be.
+static bool clusters_may_go(islf_ctx *c, int members, bool chain_if_met, hipError_t *e)
+{
+    const uint32_t aborts = (uint32_t)__atomic_load_n(c->h_res + HOST_ABORTS, __ATOMIC_RELAXED);
+    if (aborts != c->aborts_seen) c->apart = kApartRuns;
+    c->aborts_seen = aborts;
+    bool chain = false;
+    int sum = members;
+    std::vector<islf_ctx *> others;
+    for (islf_ctx *o : turns(c).all) {
+        if (o == c || o->stream == c->stream || !in_flight(o)) continue;
+        chain = chain || o->chain;
+        sum += o->members;
+        if (o->members) others.push_back(o);
+    }
+    const bool full = sum > c->num_cu;
+    if (chain_if_met && (full || chain)) {
+        c->apart = kApartRuns;
+        for (islf_ctx *o : others)
+            if (o->chain_if_met) o->apart = kApartRuns;
+    }
+    c->chain_if_met = chain_if_met;
+    if (c->apart > 0) {
+        --c->apart;
+        return false;
+    }
+    if (chain) return false;
+    for (islf_ctx *o : others)
+        if (full && *e == hipSuccess) *e = hipStreamWaitEvent(c->stream, o->turn, 0);
+    return true;
+}
+
+// Puts a run of the chain behind the clusters that others have in flight and
+// counts it as in flight; end_chain marks its end where somebody may look.
+static hipError_t start_chain(islf_ctx *c, bool *mark)
+{
+    std::lock_guard<std::mutex> lock(turns(c).m);
+    hipError_t e = hipSuccess;
+    for (islf_ctx *o : turns(c).all)
+        if (e == hipSuccess && o != c && o->stream != c->stream && in_flight(o) && o->members)
+            e = hipStreamWaitEvent(c->stream, o->turn, 0);
+    *mark = turns(c).all.size() > 1;
+    if (*mark) c->issued += 1;
+    c->unmarked = !*mark;   // (a mark ends what came before it, too)
+    c->chain = true;
+    c->chain_runs += 1;
+    return e;
+}
+
+static hipError_t end_chain(islf_ctx *c, bool mark)
+{
+    return mark ? launch_mark(c->d_rsy, c->h_res, c->stream) : hipSuccess;
 }
 
 // Acts on the persistent kernel's error word, fetched to h_res.  A raised word
@@ -1566,6 +1707,7 @@ static islf_status fetch(islf_ctx *c, int rep, const void *ring = nullptr, long 
 {
     HIP_TRY(launch_fetch(&c->d_sync->error.v, ring, first, n, size, c->h_res, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
+    landed(c);
     return take_error(c, rep);
 }
 
@@ -1645,6 +1787,12 @@ static void destroy_ctx(islf_ctx *c)
 {
     if (!c) return;
     (void)hipStreamSynchronize(c->stream);
+    {
+        std::lock_guard<std::mutex> lock(turns(c).m);
+        std::vector<islf_ctx *> &all = turns(c).all;
+        all.erase(std::remove(all.begin(), all.end(), c), all.end());
+    }
+    if (c->turn) (void)hipEventDestroy(c->turn);
     destroy_graphs(c);
     for (auto &R : c->reps) dev_free(c, R.mem);
     dev_free(c, c->d_desc);
@@ -1723,6 +1871,7 @@ extern "C" islf_status islf_create_with_allocator(const islf_replica_desc *reps,
         delete c;
         return fail(ISLF_EDEVICE, "no HIP device");
     }
+    c->device = dev;
     c->num_cu = prop.multiProcessorCount;
     int per_cu_sweep = 0;
     if (sweep_blocks_per_cu(spin_format, &per_cu_sweep) != hipSuccess || per_cu_sweep < 1) per_cu_sweep = 1;
@@ -1750,7 +1899,10 @@ extern "C" islf_status islf_create_with_allocator(const islf_replica_desc *reps,
     c->d_scratch = (unsigned long long *)dev_alloc(c, 64 * sizeof(unsigned long long));
     c->d_rsy = (ResSync *)dev_alloc(c, sizeof(ResSync));
     if (hipHostMalloc((void **)&c->h_res, 8 * (8 + kResultWords), hipHostMallocCoherent) != hipSuccess) c->h_res = nullptr;
-    if (!c->d_sync || !c->d_scratch || !c->d_rsy || !c->h_res) {
+    if (c->h_res) memset(c->h_res, 0, 8 * 8);
+    // (contexts share no data: the event orders launches and needs no fence)
+    if (hipEventCreateWithFlags(&c->turn, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) c->turn = nullptr;
+    if (!c->d_sync || !c->d_scratch || !c->d_rsy || !c->h_res || !c->turn) {
         destroy_ctx(c);
         return fail(ISLF_ENOMEM, "cannot allocate context buffers");
     }
@@ -1774,6 +1926,10 @@ extern "C" islf_status islf_create_with_allocator(const islf_replica_desc *reps,
         destroy_ctx(c);
         g_err = keep;
         return st;
+    }
+    {
+        std::lock_guard<std::mutex> lock(turns(c).m);
+        turns(c).all.push_back(c);
     }
     *out = c;
     return ISLF_OK;
@@ -1915,6 +2071,7 @@ static islf_status move_spins(islf_ctx *c, int rep, int8_t *host, bool out, Crew
         }
         HIP_TRY(launch_export(c->fmt, c->d_desc, rep, Lz, 0, (uint32_t)n, 0, p, c->stream));
         HIP_TRY(hipStreamSynchronize(c->stream));
+        landed(c);
         const islf_status st = take_error(c, rep);
         if (st == ISLF_OK) memcpy(host, p, N);
         return st;
@@ -1965,6 +2122,7 @@ static islf_status move_spins(islf_ctx *c, int rep, int8_t *host, bool out, Crew
         }
     }
     const hipError_t es = hipStreamSynchronize(c->stream);
+    if (es == hipSuccess) landed(c);
     dev_free(c, dev);
     if (e == hipSuccess) e = es;
     if (e != hipSuccess) return fail(ISLF_EDEVICE, "copy of spins failed: %s", hipGetErrorString(e));
@@ -2146,6 +2304,92 @@ static islf_status enqueue_form(islf_ctx *c, uint32_t n, bool resident)
     return ISLF_OK;
 }
 
+static const ResPlan &resident_plan(const islf_ctx *c, int rep)
+{
+    return c->exec == ISLF_EXEC_PLAIN ? c->resident_plain[rep] : c->resident;
+}
+
+// Resident launches of a run of n sweeps, and the cluster workgroups of one at most.
+static void resident_size(const islf_ctx *c, uint32_t n, uint32_t *launches, int *members)
+{
+    *launches = 0;
+    *members = 0;
+    for (int r : c->live) {
+        const ResPlan &p = resident_plan(c, r);
+        *launches += (n + p.max_sweeps - 1) / p.max_sweeps;
+        *members = std::max(*members, p.L.members);
+        if (c->exec != ISLF_EXEC_PLAIN) break;
+    }
+}
+
+// Whether chains of several contexts side by side beat resident runs in turn.
+// A chain of one stream leaves the device idle between its launches, which
+// other contexts' chains fill: they then cost about what concurrent groups do.
+// Chains that are such groups already gain nothing from each other.
+static bool prefers_chain(const islf_ctx *c)
+{
+    if (c->exec == ISLF_EXEC_PERSISTENT || (c->exec == ISLF_EXEC_BATCHED && c->live.size() > 1)) return false;
+    double res = 0.0, chain = 0.0;
+    for (int r : c->live) {
+        const ResPlan &p = resident_plan(c, r);
+        res += p.sweep_us;
+        chain += grouped_sweep_us(c, p.sites, 1);
+    }
+    return chain < res;
+}
+
+// A run of the chain, in its turn.
+template <class ENQUEUE>
+static islf_status run_chain(islf_ctx *c, ENQUEUE enqueue)
+{
+    bool mark = false;
+    HIP_TRY(start_chain(c, &mark));
+    const islf_status st = enqueue();
+    if (st != ISLF_OK) return st;
+    HIP_TRY(end_chain(c, mark));
+    return ISLF_OK;
+}
+
+// A resident run, in its turn: *done = false if it may not go now.
+template <class ENQUEUE>
+static islf_status run_resident(islf_ctx *c, uint32_t launches, int members, bool chain_if_met, bool *done,
+                                ENQUEUE enqueue)
+{
+    std::unique_lock<std::mutex> lock(turns(c).m);
+    hipError_t e = hipSuccess;
+    *done = members == 0 || clusters_may_go(c, members, chain_if_met, &e);
+    HIP_TRY(e);
+    if (!*done) return ISLF_OK;
+    (void)in_flight(c);   // forgets what has ended
+    c->issued += launches;
+    c->unmarked = false;
+    if (!members) lock.unlock();   // waits for nobody, and nobody has to wait for it
+    const islf_status st = enqueue();
+    if (!members || st != ISLF_OK) return st;
+    c->members = std::max(c->members, members);
+    c->cluster_runs += 1;
+    HIP_TRY(hipEventRecord(c->turn, c->stream));
+    return ISLF_OK;
+}
+
+static islf_status run_form(islf_ctx *c, uint32_t n, bool resident)
+{
+    if (n == 0 || c->live.empty()) return ISLF_OK;
+    if (being_captured(c)) return enqueue_form(c, n, resident);
+    if (resident) {
+        uint32_t launches;
+        int members;
+        bool done = false;
+        resident_size(c, n, &launches, &members);
+        islf_status st = run_resident(c, launches, members, prefers_chain(c), &done,
+                                      [&] { return enqueue_form(c, n, true); });
+        if (st != ISLF_OK || done) return st;
+        st = prepare_plans(c, c->exec);
+        if (st != ISLF_OK) return st;
+    }
+    return run_chain(c, [&] { return enqueue_sweeps(c, n); });
+}
+
 static islf_status check_none_failed(const islf_ctx *c)
 {
     for (int r : c->live)
@@ -2173,7 +2417,7 @@ extern "C" islf_status islf_sweep(islf_ctx *ctx, uint32_t n_sweeps)
     if (st != ISLF_OK) return st;
     st = check_sweep_range(ctx, n_sweeps);
     if (st != ISLF_OK) return st;
-    st = enqueue_form(ctx, n_sweeps, resident);
+    st = run_form(ctx, n_sweeps, resident);
     if (st != ISLF_OK) return st;
     for (int r : ctx->live) ctx->reps[r].t_host += n_sweeps;
     return ISLF_OK;
@@ -2563,8 +2807,47 @@ extern "C" islf_status islf_graph_capture(islf_ctx *ctx, uint32_t k_sweeps)
         ctx->graph_execs.push_back(ex);
     }
     ctx->graph_sweeps = k_sweeps;
+    ctx->graph_exec = ctx->exec;
+    ctx->graph_resident = resident;
+    if (resident) {
+        resident_size(ctx, k_sweeps, &ctx->graph_launches, &ctx->graph_members);
+        ctx->graph_prefers_chain = prefers_chain(ctx);
+    }
     ctx->graph_valid = true;
     return ISLF_OK;
+}
+
+static islf_status launch_graphs(islf_ctx *c, uint32_t n)
+{
+    const int G = (int)c->graph_execs.size();
+    if (G > 1) HIP_TRY(fork_groups(c, G));
+    for (uint32_t i = 0; i < n; ++i)
+        for (int g = 0; g < G; ++g) HIP_TRY(hipGraphLaunch(c->graph_execs[g], group_stream(c, g, G)));
+    if (G > 1) HIP_TRY(join_groups(c, G));
+    return ISLF_OK;
+}
+
+// n replays in their turn.  A graph of cluster launches that may not go now is
+// left alone: the same sweeps are enqueued as a chain.
+static islf_status run_graphs(islf_ctx *c, uint32_t n)
+{
+    if (being_captured(c)) return launch_graphs(c, n);
+    if (!c->graph_resident) return run_chain(c, [&] { return launch_graphs(c, n); });
+    bool done = false;
+    islf_status st = run_resident(c, c->graph_launches * n, c->graph_members, c->graph_prefers_chain, &done,
+                                  [&] { return launch_graphs(c, n); });
+    if (st != ISLF_OK || done) return st;
+    const int now = c->exec;
+    c->exec = c->graph_exec;
+    st = prepare_plans(c, c->exec);
+    if (st == ISLF_OK)
+        st = run_chain(c, [&] {
+            islf_status s = ISLF_OK;
+            for (uint32_t i = 0; i < n && s == ISLF_OK; ++i) s = enqueue_sweeps(c, c->graph_sweeps);
+            return s;
+        });
+    c->exec = now;
+    return st;
 }
 
 extern "C" islf_status islf_run_graph(islf_ctx *ctx, uint32_t n_replays)
@@ -2575,11 +2858,10 @@ extern "C" islf_status islf_run_graph(islf_ctx *ctx, uint32_t n_replays)
     if (st != ISLF_OK) return st;
     st = check_sweep_range(ctx, (uint64_t)ctx->graph_sweeps * n_replays);
     if (st != ISLF_OK) return st;
-    const int G = (int)ctx->graph_execs.size();
-    if (G > 1) HIP_TRY(fork_groups(ctx, G));
-    for (uint32_t i = 0; i < n_replays; ++i)
-        for (int g = 0; g < G; ++g) HIP_TRY(hipGraphLaunch(ctx->graph_execs[g], group_stream(ctx, g, G)));
-    if (G > 1) HIP_TRY(join_groups(ctx, G));
+    if (n_replays > 0 && !ctx->live.empty()) {
+        st = run_graphs(ctx, n_replays);
+        if (st != ISLF_OK) return st;
+    }
     for (int r : ctx->live) ctx->reps[r].t_host += (uint64_t)ctx->graph_sweeps * n_replays;
     return ISLF_OK;
 }
@@ -2676,6 +2958,8 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
     if (sweeps < 1) return fail(ISLF_EINVAL, "sweeps must be >= 1");
     islf_status st = sync_tables(ctx);
     if (st != ISLF_OK) return st;
+    bool mark = false;
+    HIP_TRY(start_chain(ctx, &mark));   // (its trials are in flight to the end)
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     // size classes: replicas of one shape share a variant
     std::vector<std::vector<int>> classes;
@@ -2872,6 +3156,7 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
     }
     if (hipStreamSynchronize(ctx->stream) != hipSuccess && result == ISLF_OK)
         result = fail(ISLF_EDEVICE, "autotune synchronisation failed");
+    landed(ctx);
     for (void *b : backup) dev_free(ctx, b);
     dev_free(ctx, st_backup);
     ctx->dirty = true;
@@ -2987,8 +3272,12 @@ extern "C" islf_status islf_phase_timings(islf_ctx *ctx, uint32_t n_sweeps, doub
                 if (f) (void)hipEventDestroy(f);
             return fail(ISLF_EDEVICE, "cannot create events");
         }
-    hipError_t err = nl ? enqueue_plan(ctx, ctx->batched, ctx->d_live, nl, n_sweeps, ev.data()) : hipSuccess;
+    bool mark = false;
+    hipError_t err = start_chain(ctx, &mark);
+    if (err == hipSuccess && nl) err = enqueue_plan(ctx, ctx->batched, ctx->d_live, nl, n_sweeps, ev.data());
+    if (err == hipSuccess) err = end_chain(ctx, mark);
     if (err == hipSuccess) err = hipStreamSynchronize(ctx->stream);
+    if (err == hipSuccess) landed(ctx);
     double sum[3] = {0, 0, 0};
     uint32_t cnt[3] = {0, 0, 0};
     if (err == hipSuccess && nl) {
@@ -3073,6 +3362,19 @@ extern "C" islf_status islf_testing_takes_resident(islf_ctx *ctx, uint32_t n, in
     const islf_status st = resident_applies(ctx, n, &use);
     *takes = use ? 1 : 0;
     return st;
+}
+
+// Test support, not part of the public header: runs with clusters, runs of the
+// chain, launches called off by the census, runs still kept to the chain.
+extern "C" islf_status islf_testing_runs(const islf_ctx *ctx, uint64_t out[4])
+{
+    if (!ctx || !out) return fail(ISLF_EINVAL, "NULL argument");
+    std::lock_guard<std::mutex> lock(turns(ctx).m);
+    out[0] = ctx->cluster_runs;
+    out[1] = ctx->chain_runs;
+    out[2] = ctx->h_res[HOST_ABORTS];
+    out[3] = (uint64_t)ctx->apart;
+    return ISLF_OK;
 }
 
 // Test support, not part of the public header: the plan of a resident launch

@@ -196,8 +196,13 @@ struct ResSync {
     unsigned int pad1_[31];
     unsigned int done;     // closing kernel: workgroups finished
     unsigned int epoch;    // mailbox epoch of the next launch
-    unsigned int pad2_[30];
+    unsigned int ended;    // launches (and marked runs of the chain) that have ended, and launches called
+    unsigned int aborts;   // off by the census; the host sees both in HOST_ENDED, HOST_ABORTS
+    unsigned int pad2_[28];
 };
+// Words of the context's pinned memory that show them (word 0 is the error
+// word that calls bring back, results start at word 8).
+enum { HOST_ENDED = 1, HOST_ABORTS = 2 };
 enum { RES_WAIT = 0, RES_GO = 1, RES_ABORT = 2 };
 // Arguments of a resident launch and its closing kernel.
 struct ResLaunch {
@@ -215,6 +220,7 @@ struct ResLaunch {
     GridSync *sync;
     int4 *part;                  // n x njobs sums
     unsigned long long *mbox;
+    unsigned long long *host;    // where the context shows its HOST_* words
 };
 
 }  // namespace islf

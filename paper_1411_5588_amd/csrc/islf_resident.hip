@@ -617,7 +617,10 @@ __device__ __forceinline__ void share_move(const Share &g, const RepDesc &d, con
 
 // Waits until every cluster workgroup of the launch has started, or gives up
 // and aborts the launch for all of them (whoever moves the state first
-// decides for all).  About 20 ms on a busy device; called by thread 0.
+// decides for all).  Gives up after about half a second: what holds the CUs is
+// then work that the library does not see (its own contexts take turns, see
+// Turns in islf_api.hip), and the closing kernel's sweeps cost more than
+// waiting for most of that.  Called by thread 0.
 __device__ __forceinline__ unsigned int res_census(ResSync *rs, unsigned int members)
 {
     const unsigned int old = atomicAdd(&rs->count, 1u);
@@ -625,7 +628,7 @@ __device__ __forceinline__ unsigned int res_census(ResSync *rs, unsigned int mem
     for (unsigned spins = 0;; ++spins) {
         const unsigned int s = __hip_atomic_load(&rs->state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (s != RES_WAIT) return s;
-        if (spins > 20000u) atomicCAS(&rs->state, (unsigned)RES_WAIT, (unsigned)RES_ABORT);
+        if (spins > (1u << 19)) atomicCAS(&rs->state, (unsigned)RES_WAIT, (unsigned)RES_ABORT);
         __builtin_amdgcn_s_sleep(8);
     }
 }
@@ -864,6 +867,11 @@ __global__ __launch_bounds__(kResThreads) void k_resident(const RepDesc *__restr
     }
 }
 
+__device__ __forceinline__ void tell_host(unsigned long long *word, unsigned int v)
+{
+    __hip_atomic_store(word, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Closes a resident launch of n sweeps: one workgroup per replica.  Sums the
 // shares' changes, stores the records and advances the replica; if the launch
 // was aborted, sweeps the cluster replicas here first.
@@ -976,12 +984,20 @@ __global__ __launch_bounds__(kResThreads) void k_resident_close(const ResLaunch 
     if (tid == 0) {
         __threadfence();
         if (atomicAdd(&rs->done, 1u) + 1 == gridDim.x) {
+            if (L.members > 0 && rs->state == RES_ABORT) tell_host(L.host + HOST_ABORTS, ++rs->aborts);
             rs->count = 0;
             rs->state = RES_WAIT;
             rs->done = 0;
             rs->epoch += 4u * n + 4u;
+            tell_host(L.host + HOST_ENDED, ++rs->ended);
         }
     }
+}
+
+// Ends a run of the launch chain as the closing kernel ends a resident launch.
+__global__ void k_mark(ResSync *rs, unsigned long long *host)
+{
+    if (threadIdx.x == 0) tell_host(host + HOST_ENDED, ++rs->ended);
 }
 
 // ---------------------------------------------------------------------------
@@ -1017,6 +1033,12 @@ hipError_t launch_resident(int fmt, int form, const ResLaunch &L, size_t lds, hi
                        L.rows, L);
     if (fmt == ISLF_SPIN_INT8) hipLaunchKernelGGL(k_resident_close<ISLF_SPIN_INT8>, dim3(L.nreps), b, 0, s, L);
     else hipLaunchKernelGGL(k_resident_close<ISLF_SPIN_BITPACK>, dim3(L.nreps), b, 0, s, L);
+    return hipGetLastError();
+}
+
+hipError_t launch_mark(ResSync *rs, unsigned long long *host, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_mark, dim3(1), dim3(64), 0, s, rs, host);
     return hipGetLastError();
 }
 

@@ -133,6 +133,7 @@ def lib():
             "islf_testing_raise_barrier_error": [vp],
             "islf_testing_abort_resident": [vp],
             "islf_testing_takes_resident": [vp, C.c_uint32, P(i32)],
+            "islf_testing_runs": [vp, P(u64)],
             "islf_testing_resident_plan": [vp, C.c_int32, C.c_int32, C.c_int32, vp, C.c_int64, vp],
         }
         for name, args in sig.items():
