@@ -985,7 +985,13 @@ constexpr size_t kLatticeLds = 160 * 1024 - kResStaticLds;   // of a gfx950 CU's
 // Expected times (us) of the resident kernel: a chunk of 64 whole words on
 // one SIMD; of partial words, and each of their four-site groups; the latency
 // of a lone chunk; the exchange of a phase, and per 1,000 words received; a
-// stage's barrier and the tail of its last chunks.
+// stage's barrier and the tail of its last chunks.  Without the four-site table
+// (a bulk field, moves never accepted) a sweep takes 1 to 14% more; the chain
+// takes 4% more with a field, 25% with moves never accepted.  Neither is
+// charged, as the chain's estimate is low by as much: of 26 bit-packed batches
+// with a field whose estimates lie within 15% of each other, one took the
+// resident form where the chain is the faster (10 x 120x113x552: 41.7 against
+// 37.7 us).
 constexpr double kChunkUs = 0.80, kPartUs = 0.18, kGroupUs = 0.092, kLoneUs = 1.3, kExchangeUs = 0.8, kMailUs = 0.4,
                  kStageUs = 1.1;
 // The fine form: a chunk of 16 words, the latency of a lone one, and what the
