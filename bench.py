@@ -101,6 +101,13 @@ def replicas(islf, n=None):
                          seed=SEED + i, replica=i, init=islf.INIT_RANDOM) for i in range(n)]
 
 
+def takes_resident(islf, ctx, sweeps):
+    """Whether runs of this many sweeps keep the spins in LDS (the resident form)."""
+    v = islf.C.c_int32()
+    islf._check(islf.lib().islf_testing_takes_resident(ctx._h, sweeps, islf.C.byref(v)))
+    return bool(v.value)
+
+
 def run_form(islf, torch, form, fmt, steps, warmup, chunk, n_reps=None, groups=0, reps=None, autotune=0, grid=0,
              tile=-1, min_warm_s=0.5, barriers=None, taper=None):
     """Times `steps` sweeps of a batch in one execution form: graph replays of
@@ -134,6 +141,7 @@ def run_form(islf, torch, form, fmt, steps, warmup, chunk, n_reps=None, groups=0
         if tile >= 0:
             for i in range(len(reps)):
                 ctx.set_tile(i, tile)
+        resident = takes_resident(islf, ctx, chunk)
         ctx.capture(chunk)
         # warm-up: always one untimed replay of the graph (the first replay of
         # a new graph is slower), eager sweeps for the remainder, then replays
@@ -165,8 +173,10 @@ def run_form(islf, torch, form, fmt, steps, warmup, chunk, n_reps=None, groups=0
         for i in range(len(reps)):
             assert ctx.sweep_count(i) == done
         out = dict(ms_per_sweep=total_ms / steps, sweeps_per_launch=chunk, launches=n_launch,
-                   warmup_sweeps=done - steps, groups=ctx.get_groups() if form == "batched" else 1,
-                   grid=ctx.get_grid(), sites=sum(r.N for r in reps), ctx_means=None)
+                   warmup_sweeps=done - steps, resident=resident,
+                   # (of the launch chain or the persistent kernel: the resident form has neither)
+                   groups=None if resident else ctx.get_groups() if form == "batched" else 1,
+                   grid=None if resident else ctx.get_grid(), sites=sum(r.N for r in reps), ctx_means=None)
         if autotune:
             out["autotune_s"] = round(tuned, 2)
             out["tuned"] = {"groups": ctx.get_groups() if form == "batched" else 1, "grid": ctx.get_grid(),
@@ -457,6 +467,43 @@ def cpu_baseline(n_sweeps, max_threads=16):
     return out
 
 
+def roofline_of(fmt, chain, grouped):
+    """Roofline of the sweep kernel of the launch chain, from a timed run of one
+    chain over all replicas and, optionally, one of concurrent groups.  Its A
+    and B launches of one sweep together update every site of every replica
+    once (A: phase 0 and the previous sweep's phase 3, B: phases 1 and 2), so
+    one launch updates half a sweep of every replica; the timed region over
+    its 2 x steps launches is the average launch duration (the region also
+    holds one closing launch and fold per graph launch, so this slightly
+    overstates it).  Runs in the resident form have no such launches."""
+    assert not chain["resident"] and not (grouped and grouped["resident"])
+    bpu = BYTES_PER_UPDATE[fmt]
+    alg_bytes = bpu * chain["sites"] / 2
+    launch_ms = chain["ms_per_sweep"] / 2
+    achieved = alg_bytes / (launch_ms * 1e-3) / 1e9
+    out = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+           "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": committed_traffic(fmt),
+           "kernel": "k_sweep (A and B launches), one launch over all three replicas",
+           "launch_ms": round(launch_ms, 5), "workgroups": chain["grid"],
+           "algorithmic_bytes_per_launch": alg_bytes, "bytes_per_update": bpu,
+           "roofline_updates_per_ns": HBM_PEAK_GBS / bpu}
+    if grouped is not None:
+        wave_ms = grouped["ms_per_sweep"] / 2
+        gbs = alg_bytes / (wave_ms * 1e-3) / 1e9
+        out["grouped_wave"] = {"wave_ms": round(wave_ms, 5), "achieved": round(gbs, 1),
+                               "frac": round(gbs / HBM_PEAK_GBS, 4),
+                               "unit": f"wave of {grouped['groups']} concurrent group dispatches of "
+                                       f"{grouped['grid']} workgroups, half a sweep of every replica"}
+    out["valu"] = committed_valu(fmt)
+    if grouped is not None and out["valu"] and out["valu"].get("issue_us_per_launch"):
+        # the same half sweep's VALU issue time over the grouped wave: the
+        # share of the wave the SIMDs spend issuing VALU instructions
+        out["grouped_wave"]["valu_issue_frac"] = round(
+            out["valu"]["issue_us_per_launch"] / (out["grouped_wave"]["wave_ms"] * 1e3), 3)
+    out["limiter"] = "VALU issue: Philox4x32-10 costs 5 64-bit products and 5 xors per update"
+    return out
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -514,15 +561,15 @@ def main():
                         grid=args.grid, tile=args.tile, min_warm_s=WARM_S, barriers=bars, taper=args.taper)
     print(f"# {args.form}/{args.fmt}: {brief(main_run)}", file=sys.stderr, flush=True)
     value = rate(main_run)
-    # the same form as one launch chain over all replicas, timed the same way:
-    # its launches run one after another, so timed region / launches is the
-    # sweep kernel's own average launch duration
-    if main_run["groups"] == 1:
+    # one launch chain over all replicas, timed the same way: its launches run
+    # one after another, so timed region / launches is the sweep kernel's own
+    # average launch duration
+    if args.form == "batched" and main_run["groups"] == 1 and not main_run["resident"]:
         chain_run = main_run
     else:
-        chain_run = run_form(islf, torch, args.form, args.fmt, min(args.steps, 400), min(args.warmup, 100),
+        chain_run = run_form(islf, torch, "batched", args.fmt, min(args.steps, 400), min(args.warmup, 100),
                              args.chunk, groups=1, tile=args.tile, min_warm_s=WARM_S)
-        print(f"# {args.form}/{args.fmt} one launch chain: {brief(chain_run)}", file=sys.stderr, flush=True)
+        print(f"# {args.fmt} one launch chain: {brief(chain_run)}", file=sys.stderr, flush=True)
 
     forms = {}
     if not args.no_extras:
@@ -550,51 +597,28 @@ def main():
         configs = config_figures(islf, torch, args.steps, args.warmup, args.chunk, args.serve_requests,
                                  args.serve_budget_mib)
 
-    # dominant kernel: the sweep kernel.  Its A and B launches of one sweep
-    # together update every site of every replica once (A: phase 0 and the
-    # previous sweep's phase 3, B: phases 1 and 2), so one launch updates half
-    # a sweep of every replica; the one-chain timed region over its 2 x steps
-    # launches is the average launch duration (the region also holds one
-    # closing launch and fold per graph launch, so this slightly overstates it)
-    def roofline_of(fmt, chain, grouped):
-        bpu = BYTES_PER_UPDATE[fmt]
-        alg_bytes = bpu * n_reps * N / 2
-        launch_ms = chain["ms_per_sweep"] / 2
-        achieved = alg_bytes / (launch_ms * 1e-3) / 1e9
-        out = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-               "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": committed_traffic(fmt),
-               "kernel": "k_sweep (A and B launches), one launch over all three replicas",
-               "launch_ms": round(launch_ms, 5), "workgroups": chain["grid"],
-               "algorithmic_bytes_per_launch": alg_bytes, "bytes_per_update": bpu,
-               "roofline_updates_per_ns": HBM_PEAK_GBS / bpu}
-        if grouped is not None:
-            wave_ms = grouped["ms_per_sweep"] / 2
-            gbs = alg_bytes / (wave_ms * 1e-3) / 1e9
-            out["grouped_wave"] = {"wave_ms": round(wave_ms, 5), "achieved": round(gbs, 1),
-                                   "frac": round(gbs / HBM_PEAK_GBS, 4),
-                                   "unit": f"wave of {grouped['groups']} concurrent group dispatches of "
-                                           f"{grouped['grid']} workgroups, half a sweep of every replica"}
-        out["valu"] = committed_valu(fmt)
-        if grouped is not None and out["valu"] and out["valu"].get("issue_us_per_launch"):
-            # the same half sweep's VALU issue time over the grouped wave: the
-            # share of the wave the SIMDs spend issuing VALU instructions
-            out["grouped_wave"]["valu_issue_frac"] = round(
-                out["valu"]["issue_us_per_launch"] / (out["grouped_wave"]["wave_ms"] * 1e3), 3)
-        out["limiter"] = "VALU issue: Philox4x32-10 costs 5 64-bit products and 5 xors per update"
-        return out
+    def grouped_run(fmt, min_warm_s):
+        return run_form(islf, torch, "batched", fmt, min(args.steps, 400), min(args.warmup, 100), args.chunk,
+                        groups=min(3, n_reps), min_warm_s=min_warm_s)
 
-    roofline = roofline_of(args.fmt, chain_run, main_run if args.form == "batched" else None)
-    roofline["grouped_wave_is_headline_form"] = args.form == "batched"
+    wave = None
+    if args.form == "batched":
+        wave = grouped_run(args.fmt, WARM_S) if main_run["resident"] else main_run
+    roofline = roofline_of(args.fmt, chain_run, wave)
+    roofline["grouped_wave_is_headline_form"] = wave is main_run
     if not args.no_extras:
         # the other spin format's sweep kernel, measured the same way
         other = "int8" if args.fmt == "bitpack" else "bitpack"
         oc = run_form(islf, torch, "batched", other, min(args.steps, 400), min(args.warmup, 100), args.chunk,
                       groups=1, min_warm_s=0.2)
-        og = run_form(islf, torch, "batched", other, min(args.steps, 400), min(args.warmup, 100), args.chunk,
+        og = grouped_run(other, 0.2)
+        ob = run_form(islf, torch, "batched", other, min(args.steps, 400), min(args.warmup, 100), args.chunk,
                       min_warm_s=0.2)
         roofline[f"other_format_{other}"] = roofline_of(other, oc, og)
-        roofline[f"other_format_{other}"]["updates_per_ns_batched"] = round(rate(og), 2)
-        print(f"# {other} one chain: {brief(oc)}; grouped: {brief(og)}", file=sys.stderr, flush=True)
+        roofline[f"other_format_{other}"]["updates_per_ns_batched"] = round(rate(ob), 2)
+        roofline[f"other_format_{other}"]["batched_form_is_resident"] = ob["resident"]
+        print(f"# {other} one chain: {brief(oc)}; grouped: {brief(og)}; default: {brief(ob)}", file=sys.stderr,
+              flush=True)
 
     prof = hio = None
     if not args.no_aux:
@@ -614,6 +638,7 @@ def main():
                                f"{main_run['sweeps_per_launch']} sweeps per graph launch",
                    "sites_per_replica": N, "replicas": n_reps, "form": args.form, "spin_format": args.fmt,
                    "groups": main_run["groups"], "workgroups_per_launch": main_run["grid"],
+                   "resident": main_run["resident"],
                    "warmup_sweeps_run": main_run["warmup_sweeps"]},
         "roofline": roofline,
         "forms": forms,
