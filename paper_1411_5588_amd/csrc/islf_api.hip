@@ -258,6 +258,7 @@ struct ShareChoice {
 constexpr size_t kMaxShapes = 256;
 constexpr long kResultWords = 8192;            // 64 KiB of results
 constexpr size_t kWindow = 2u << 20;           // bytes of spins per window
+constexpr size_t kPlanBytes = 32u << 20;       // of resident plans (3 x 160x480x600: 8 MB; thin films of 9,000-site rows: 20 MB)
 
 struct islf_ctx {
     int fmt = 0;
@@ -1438,6 +1439,11 @@ static bool plan_resident(islf_ctx *c, const std::vector<int> &reps, ResPlan &p,
     return true;
 }
 
+static size_t resident_bytes(const ResPlan &p)
+{
+    return p.jobs_b + p.first_b + p.planes_b + p.rows_b + p.reps_b + p.part_b + p.mbox_b;
+}
+
 // Puts a host table into a device buffer of the plan, grown if needed.
 template <class T>
 static bool put_table(islf_ctx *c, const T *&ptr, size_t &have, const std::vector<T> &v, hipError_t &e)
@@ -1476,6 +1482,14 @@ static islf_status build_resident(islf_ctx *c, ResPlan &p, const std::vector<int
     if (p.put_off) return ISLF_OK;
     // per-sweep sums: 8 MiB at most, had here for the longest launch, so that runs allocate nothing
     p.max_sweeps = (uint32_t)std::max<size_t>(1, std::min<size_t>(kResMaxSweeps, (8u << 20) / (16 * (size_t)p.L.njobs)));
+    // a context's plans of one kind hold at most kPlanBytes (no part of the replicas' footprint)
+    size_t held = sizeof(ResJob) * h.jobs.size() + sizeof(int) * h.first.size() + sizeof(ResPlane) * h.planes.size() +
+                  sizeof(ResRow) * h.rows.size() + sizeof(ResRep) * h.reps.size() + 8 * h.mbox_words +
+                  sizeof(int4) * p.max_sweeps * (size_t)p.L.njobs;
+    if (&p != &c->resident)
+        for (const ResPlan &o : c->resident_plain)
+            if (&o != &p) held += resident_bytes(o);
+    if (held > kPlanBytes) return ISLF_OK;
     hipError_t e = hipSuccess;
     if (!put_table(c, p.L.jobs, p.jobs_b, h.jobs, e) || !put_table(c, p.L.first, p.first_b, h.first, e) ||
         !put_table(c, p.L.planes, p.planes_b, h.planes, e) || !put_table(c, p.L.rows, p.rows_b, h.rows, e) ||
