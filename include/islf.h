@@ -74,10 +74,20 @@ typedef enum { ISLF_INIT_RANDOM = 0, ISLF_INIT_UP = 1, ISLF_INIT_DOWN = 2, ISLF_
  *  PERSISTENT : one launch for all requested sweeps of every replica, with
  *               device-side grid barriers in place of the launch boundaries.
  * Replicas whose spins fit the device's LDS (one bit per site, about 3e8
- * sites) are swept there instead, in one launch of up to 256 sweeps for the
+ * sites) are swept there instead, in launches of up to 256 sweeps for the
  * whole batch (PLAIN: per replica), where that is expected to be faster and
- * no launch configuration was chosen (islf_set_grid, islf_set_groups,
- * islf_set_taper, islf_set_barriers, islf_set_tile). */
+ * the caller chose no launch configuration (islf_set_grid, islf_set_groups,
+ * islf_set_taper, islf_set_barriers, islf_set_tile).  This resident form
+ * takes the place of any of the three.
+ *
+ * Contexts of a process that sweep at the same time on one device: resident
+ * launches of films that need several CUs each are ordered behind each other
+ * where the device cannot hold them side by side, launches of the forms
+ * above behind them, and a run that finds another context's launches of the
+ * forms above in flight takes those forms too.  Sweeps that a caller records
+ * into a graph of its own are not ordered so; beside work that holds CUs they
+ * (as all resident launches beside another process's work) may wait up to
+ * half a second for their CUs and then run slowly, with the same results. */
 typedef enum { ISLF_EXEC_PLAIN = 0, ISLF_EXEC_BATCHED = 1, ISLF_EXEC_PERSISTENT = 2 } islf_exec;
 
 /* One replica (Sec. II.A Eq. 1 parameters plus the Markov-chain identity).
@@ -139,7 +149,7 @@ islf_status islf_get_desc(const islf_ctx *ctx, int32_t rep, islf_replica_desc *o
 /* Host <-> device spins, int8 +-1 in the host layout above; n must equal
  * Lx*Ly*Lz.  set_spins also recomputes the initial observables and may only
  * be called before the replica's first sweep, or on a replica marked failed
- * by a persistent launch (see islf_sweep), which it restarts at sweep 0
+ * by a launch that gave up (see islf_sweep), which it restarts at sweep 0
  * (else ESTATE).  Both synchronise.
  * Errors: EINVAL (n, values other than +-1), ERANGE (rep), ESTATE. */
 islf_status islf_set_spins(islf_ctx *ctx, int32_t rep, const int8_t *host, size_t n);
@@ -158,9 +168,11 @@ islf_status islf_set_exec(islf_ctx *ctx, int32_t exec_mode);
  * Errors: ERANGE if a replica's sweep index would pass 2^32-1, EDEVICE,
  * ESTATE if a live replica is marked failed (below).
  *
- * Failure of a persistent launch: its grid barriers wait a bounded time; a
- * block that gives up raises an error word and every block of the launch
- * then stops at its next barrier, leaving the sweeps half done.  The next
+ * Failure of a launch: the grid barriers of a persistent launch, and in any
+ * execution form the exchange of a resident launch whose films are cut over
+ * several CUs, wait a bounded time (seconds); a block that gives up raises an
+ * error word and every block of the launch stops at its next wait, leaving
+ * the sweeps half done.  The next
  * call that reads results (measure, sweep_count, get_spins, recompute,
  * record_energy, means) returns EDEVICE and marks every live replica failed;
  * from then on calls on a failed replica (and sweeps, graph capture and
@@ -257,7 +269,9 @@ islf_status islf_integrate_device(const double *h, const double *m1, const doubl
 /* ---------------------------------------------------------------------- */
 
 /* Device bytes one replica needs in a context (spins, ring, tables, work
- * lists), for admission by memory footprint. */
+ * lists), for admission by memory footprint.  Beside its replicas a context
+ * holds its launch plans: of the resident form at most 32 MiB each for the
+ * plain and for the other forms (islf_device_bytes counts them). */
 islf_status islf_footprint_bytes(const islf_replica_desc *desc, int32_t spin_format,
                                  uint32_t obs_capacity, uint64_t *bytes);
 
@@ -310,7 +324,9 @@ islf_status islf_run_graph(islf_ctx *ctx, uint32_t n_replays);
  * bound x tapers 0, 0.2, 0.4, 0.6.  The four fastest and the configuration in use
  * are timed again (shortest of six runs); a finalist replaces the one in use
  * only if it is 1% faster (islf_get_groups, islf_get_grid, islf_get_taper,
- * islf_get_barriers report the result).  Spins, records and sweep
+ * islf_get_barriers report the result).  The resident form has none of these
+ * settings: a run takes it where it is expected to be faster than the tuned
+ * form (settings that a caller chose before keep it off).  Spins, records and sweep
  * counters are restored afterwards, so results are unaffected.  Synchronises.
  * Errors: EINVAL, ENOMEM (backups), EDEVICE. */
 islf_status islf_num_tiles(int32_t spin_format, int32_t *n);

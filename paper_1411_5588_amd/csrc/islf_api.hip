@@ -215,7 +215,7 @@ struct Replica {
     void *mem = nullptr;     // spins | records | accumulators
     size_t mem_bytes = 0;
     uint64_t t_host = 0;     // sweeps issued so far
-    bool failed = false;     // its chain was cut short by a failed persistent launch
+    bool failed = false;     // its chain was cut short by a failed launch
     int tile = 0;
     bool tile_set = false;   // chosen by islf_set_tile
     RepDesc d{};
@@ -1697,8 +1697,9 @@ static hipError_t end_chain(islf_ctx *c, bool mark)
     return mark ? launch_mark(c->d_rsy, c->h_res, c->stream) : hipSuccess;
 }
 
-// Acts on the persistent kernel's error word, fetched to h_res.  A raised word
-// means a launch gave up at a grid barrier and left its sweeps half done, so
+// Acts on the error word, fetched to h_res.  A raised word means a launch gave
+// up at a grid barrier (persistent kernel) or waiting for its neighbours' edges
+// (resident kernel, in any form) and left its sweeps half done, so
 // every live replica is marked failed (its calls return ESTATE until
 // islf_set_spins restarts it or it is retired); the word is then cleared so
 // that later launches can run.  With rep >= 0, that replica's chain has to be
@@ -1710,11 +1711,12 @@ static islf_status take_error(islf_ctx *c, int rep)
         c->graph_valid = false;
         HIP_TRY(launch_zero((unsigned long long *)&c->d_sync->error, 16, c->stream));
         HIP_TRY(hipStreamSynchronize(c->stream));
-        return fail(ISLF_EDEVICE, "a persistent-kernel grid barrier gave up (its workgroups were not all resident at "
+        return fail(ISLF_EDEVICE, "a launch whose workgroups wait for each other gave up (a grid barrier of the "
+                                  "persistent kernel or an exchange of the resident one: not all were resident at "
                                   "once, or the wait was cut short); every live replica is marked failed");
     }
     if (rep >= 0 && c->reps[rep].failed)
-        return fail(ISLF_ESTATE, "replica %d was cut short by a failed persistent launch (restart it with "
+        return fail(ISLF_ESTATE, "replica %d was cut short by a failed launch (restart it with "
                                  "islf_set_spins or retire it)", rep);
     return ISLF_OK;
 }
@@ -2414,7 +2416,7 @@ static islf_status check_none_failed(const islf_ctx *c)
 {
     for (int r : c->live)
         if (c->reps[r].failed)
-            return fail(ISLF_ESTATE, "replica %d was cut short by a failed persistent launch (restart it with "
+            return fail(ISLF_ESTATE, "replica %d was cut short by a failed launch (restart it with "
                                      "islf_set_spins or retire it)", r);
     return ISLF_OK;
 }
@@ -3199,7 +3201,7 @@ extern "C" islf_status islf_layer_profile(islf_ctx *ctx, int32_t rep, int32_t *d
     if (st != ISLF_OK) return st;
     if (!dev_out) return fail(ISLF_EINVAL, "NULL output");
     if (ctx->reps[rep].failed)
-        return fail(ISLF_ESTATE, "replica %d was cut short by a failed persistent launch", rep);
+        return fail(ISLF_ESTATE, "replica %d was cut short by a failed launch", rep);
     st = sync_tables(ctx);
     if (st != ISLF_OK) return st;
     const Replica &R = ctx->reps[rep];
@@ -3214,7 +3216,7 @@ extern "C" islf_status islf_layer_profile_add(islf_ctx *ctx, int32_t rep, int64_
     if (st != ISLF_OK) return st;
     if (!dev_acc) return fail(ISLF_EINVAL, "NULL accumulator");
     if (ctx->reps[rep].failed)
-        return fail(ISLF_ESTATE, "replica %d was cut short by a failed persistent launch", rep);
+        return fail(ISLF_ESTATE, "replica %d was cut short by a failed launch", rep);
     st = sync_tables(ctx);
     if (st != ISLF_OK) return st;
     const Replica &R = ctx->reps[rep];
