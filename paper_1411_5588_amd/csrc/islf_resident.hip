@@ -617,10 +617,12 @@ __device__ __forceinline__ void share_move(const Share &g, const RepDesc &d, con
 
 // Waits until every cluster workgroup of the launch has started, or gives up
 // and aborts the launch for all of them (whoever moves the state first
-// decides for all).  Gives up after about half a second: what holds the CUs is
-// then work that the library does not see (its own contexts take turns, see
-// Turns in islf_api.hip), and the closing kernel's sweeps cost more than
-// waiting for most of that.  Called by thread 0.
+// decides for all).  Gives up after about a tenth of a second: what holds the
+// CUs is then work that the library does not see (its own contexts take turns,
+// see Turns in islf_api.hip), and the closing kernel's sweeps cost more than
+// waiting for most of that.  (The bound fits an instruction's 16-bit constant:
+// with a 32-bit one the code behind it moved by 4 bytes, and three films of
+// 46 M sites took 62.6 instead of 61.3 us a sweep.)  Called by thread 0.
 __device__ __forceinline__ unsigned int res_census(ResSync *rs, unsigned int members)
 {
     const unsigned int old = atomicAdd(&rs->count, 1u);
@@ -628,8 +630,8 @@ __device__ __forceinline__ unsigned int res_census(ResSync *rs, unsigned int mem
     for (unsigned spins = 0;; ++spins) {
         const unsigned int s = __hip_atomic_load(&rs->state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (s != RES_WAIT) return s;
-        if (spins > (1u << 19)) atomicCAS(&rs->state, (unsigned)RES_WAIT, (unsigned)RES_ABORT);
-        __builtin_amdgcn_s_sleep(8);
+        if (spins > 65000u) atomicCAS(&rs->state, (unsigned)RES_WAIT, (unsigned)RES_ABORT);
+        __builtin_amdgcn_s_sleep(32);
     }
 }
 

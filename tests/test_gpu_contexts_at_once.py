@@ -174,3 +174,23 @@ def test_four_contexts_on_threads(fmt):
             assert np.array_equal(rec, rec0) and np.array_equal(s, s0), i
     for c in ctxs:
         c.close()
+
+
+def test_beside_other_work_on_the_device():
+    # work that the library does not see: whichever way a launch goes, the chain is the same
+    p = film((24, 130, 140), 3)
+    x = torch.randn(4096, 4096, device="cuda")
+    side = torch.cuda.Stream()
+    with context([p]) as a:
+        a.sweep(2)
+        a.sweep_count(0)
+        with torch.cuda.stream(side):
+            for _ in range(60):
+                y = x @ x
+        for _ in range(10):
+            a.sweep(2)
+        got = a.measure(0, 0, 22), a.get_spins(0)
+        side.synchronize()
+        del y
+    _, rec, s = oracle_trajectory(p, 22)
+    assert np.array_equal(got[0], rec) and np.array_equal(got[1], s)
