@@ -7,6 +7,7 @@ share.  No launch is called off, and the chains are the same as alone.
 """
 import ctypes as C
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -68,6 +69,25 @@ def test_single_chains_that_meet_share_the_device():
         b.sweep(20)
         assert runs(b)["cluster"] == 2 and runs(b)["apart"] == 0
         assert runs(a)["aborts"] == runs(b)["aborts"] == 0
+
+
+def test_a_new_context_comes_behind_the_clusters_of_one_that_was_alone():
+    with context([film(BIG)], islf.INT8) as a:
+        a.sweep(2000)
+        with context([film(BIG, 1)], islf.INT8) as b:
+            # a had 32 ms of work and no event of its own to be ordered behind; the runtime notices the end of a
+            # stream's last kernel some time after a query
+            done = False
+            for _ in range(4):
+                done = done or a.stream.query()
+                time.sleep(0.001)
+            assert done
+            b.sweep(500)
+            a.sweep(20)
+            b.sweep(20)
+            assert a.sweep_count(0) == 2020 and b.sweep_count(0) == 520
+            for c in (a, b):
+                assert runs(c) == dict(cluster=2, chain=0, aborts=0, apart=0)
 
 
 def test_clusters_meet_a_chain():
