@@ -1629,8 +1629,9 @@ static bool in_flight(islf_ctx *o)
     return false;
 }
 
-// A context that was alone recorded no events (each costs a run 3 us: five runs of
-// 10 sweeps of a 184x504x504 film 1,485 instead of 1,467 us): a new one waits for its clusters here, where creation waits for the device anyway.
+// A context that was alone recorded no events (each costs a run 3 us: five runs
+// of 10 sweeps of a 184x504x504 film take 1,485 instead of 1,467 us): a new one
+// waits for its clusters here, where creation waits for the device anyway.
 static void join_turns(islf_ctx *c)
 {
     {
@@ -1642,7 +1643,8 @@ static void join_turns(islf_ctx *c)
         busy = false;
         {
             std::lock_guard<std::mutex> lock(turns(c).m);
-            for (islf_ctx *o : turns(c).all) busy = busy || (o != c && o->members && o->bare && in_flight(o));
+            for (islf_ctx *o : turns(c).all) 
+                busy = busy || (o != c && o->stream != c->stream && o->members && o->bare && in_flight(o));
         }
         if (busy) std::this_thread::yield();
     }
