@@ -315,7 +315,7 @@ struct islf_ctx {
     int device = 0;
     hipEvent_t turn = nullptr;     // recorded behind a run with clusters,
     bool bare = false;             // unless the context was alone: not since it last was in flight
-    uint32_t issued = 0;           // launches that will count HOST_ENDED up
+    uint32_t issued = 0;           // cluster launches and marks that will count HOST_ENDED up
     uint32_t aborts_seen = 0;
     int members = 0;               // cluster workgroups of the launches in flight, at most
     bool chain = false;            // the chain or the persistent kernel is in flight,
@@ -346,7 +346,7 @@ struct islf_ctx {
     int graph_exec = 0;             // the form it was captured in,
     bool graph_resident = false;    // resident or not,
     int graph_members = 0;          // with so many cluster workgroups at most
-    uint32_t graph_launches = 0;    // and so many resident launches;
+    uint32_t graph_launches = 0;    // and so many launches of them;
     bool graph_prefers_chain = false;
 
     // the cuts of the shapes planned so far (kMaxShapes at most)
@@ -1694,7 +1694,7 @@ static bool clusters_may_go(islf_ctx *c, int members, bool chain_if_met, hipErro
     }
     if (chain) return false;
     for (islf_ctx *o : others)
-        if (full && *e == hipSuccess) *e = hipStreamWaitEvent(c->stream, o->turn, 0);
+        if (full && o->turn && *e == hipSuccess) *e = hipStreamWaitEvent(c->stream, o->turn, 0);
     return true;
 }
 
@@ -1705,7 +1705,7 @@ static hipError_t start_chain(islf_ctx *c, bool *mark)
     std::lock_guard<std::mutex> lock(turns(c).m);
     hipError_t e = hipSuccess;
     for (islf_ctx *o : turns(c).all)
-        if (e == hipSuccess && o != c && o->stream != c->stream && in_flight(o) && o->members)
+        if (e == hipSuccess && o != c && o->stream != c->stream && in_flight(o) && o->members && o->turn)
             e = hipStreamWaitEvent(c->stream, o->turn, 0);
     *mark = turns(c).all.size() > 1;
     if (*mark) c->issued += 1;
@@ -1945,9 +1945,7 @@ extern "C" islf_status islf_create_with_allocator(const islf_replica_desc *reps,
     c->d_rsy = (ResSync *)dev_alloc(c, sizeof(ResSync));
     if (hipHostMalloc((void **)&c->h_res, 8 * (8 + kResultWords), hipHostMallocCoherent) != hipSuccess) c->h_res = nullptr;
     if (c->h_res) memset(c->h_res, 0, 8 * 8);
-    // (contexts share no data: the event orders launches and needs no fence)
-    if (hipEventCreateWithFlags(&c->turn, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) c->turn = nullptr;
-    if (!c->d_sync || !c->d_scratch || !c->d_rsy || !c->h_res || !c->turn) {
+    if (!c->d_sync || !c->d_scratch || !c->d_rsy || !c->h_res) {
         destroy_ctx(c);
         return fail(ISLF_ENOMEM, "cannot allocate context buffers");
     }
@@ -2351,14 +2349,14 @@ static const ResPlan &resident_plan(const islf_ctx *c, int rep)
     return c->exec == ISLF_EXEC_PLAIN ? c->resident_plain[rep] : c->resident;
 }
 
-// Resident launches of a run of n sweeps, and the cluster workgroups of one at most.
+// Launches with clusters of a run of n sweeps, and the cluster workgroups of one at most.
 static void resident_size(const islf_ctx *c, uint32_t n, uint32_t *launches, int *members)
 {
     *launches = 0;
     *members = 0;
     for (int r : c->live) {
         const ResPlan &p = resident_plan(c, r);
-        *launches += (n + p.max_sweeps - 1) / p.max_sweeps;
+        if (p.L.members) *launches += (n + p.max_sweeps - 1) / p.max_sweeps;
         *members = std::max(*members, p.L.members);
         if (c->exec != ISLF_EXEC_PLAIN) break;
     }
@@ -2397,21 +2395,25 @@ template <class ENQUEUE>
 static islf_status run_resident(islf_ctx *c, uint32_t launches, int members, bool chain_if_met, bool *done,
                                 ENQUEUE enqueue)
 {
-    std::unique_lock<std::mutex> lock(turns(c).m);
+    *done = true;
+    if (!members) return enqueue();   // waits for nobody, and nobody has to wait for it
+    std::lock_guard<std::mutex> lock(turns(c).m);
     hipError_t e = hipSuccess;
-    *done = members == 0 || clusters_may_go(c, members, chain_if_met, &e);
+    *done = clusters_may_go(c, members, chain_if_met, &e);
     HIP_TRY(e);
     if (!*done) return ISLF_OK;
     (void)in_flight(c);   // forgets what has ended
     c->issued += launches;
     c->unmarked = false;
-    if (!members) lock.unlock();   // waits for nobody, and nobody has to wait for it
     const islf_status st = enqueue();
-    if (!members || st != ISLF_OK) return st;
+    if (st != ISLF_OK) return st;
     c->members = std::max(c->members, members);
     c->cluster_runs += 1;
     c->bare = turns(c).all.size() == 1;
-    if (!c->bare) HIP_TRY(hipEventRecord(c->turn, c->stream));
+    if (c->bare) return ISLF_OK;
+    // (contexts share no data: the event orders launches and needs no fence)
+    if (!c->turn) HIP_TRY(hipEventCreateWithFlags(&c->turn, hipEventDisableTiming | hipEventDisableSystemFence));
+    HIP_TRY(hipEventRecord(c->turn, c->stream));
     return ISLF_OK;
 }
 

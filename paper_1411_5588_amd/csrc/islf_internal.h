@@ -196,8 +196,8 @@ struct ResSync {
     unsigned int pad1_[31];
     unsigned int done;     // closing kernel: workgroups finished
     unsigned int epoch;    // mailbox epoch of the next launch
-    unsigned int ended;    // launches (and marked runs of the chain) that have ended, and launches called
-    unsigned int aborts;   // off by the census; the host sees both in HOST_ENDED, HOST_ABORTS
+    unsigned int ended;    // cluster launches (and marked runs of the chain) that have ended, and those
+    unsigned int aborts;   // called off by the census; the host sees both in HOST_ENDED, HOST_ABORTS
     unsigned int pad2_[28];
 };
 // Words of the context's pinned memory that show them (word 0 is the error

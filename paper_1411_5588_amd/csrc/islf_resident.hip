@@ -986,12 +986,13 @@ __global__ __launch_bounds__(kResThreads) void k_resident_close(const ResLaunch 
     if (tid == 0) {
         __threadfence();
         if (atomicAdd(&rs->done, 1u) + 1 == gridDim.x) {
+            // (launches without clusters: nobody has to wait for them, and a word to the host costs them 1 us)
             if (L.members > 0 && rs->state == RES_ABORT) tell_host(L.host + HOST_ABORTS, ++rs->aborts);
+            if (L.members > 0) tell_host(L.host + HOST_ENDED, ++rs->ended);
             rs->count = 0;
             rs->state = RES_WAIT;
             rs->done = 0;
             rs->epoch += 4u * n + 4u;
-            tell_host(L.host + HOST_ENDED, ++rs->ended);
         }
     }
 }
