@@ -313,13 +313,15 @@ struct islf_ctx {
     ResSync *d_rsy = nullptr;
     // turns among the contexts of a device (see Turns; under its lock)
     int device = 0;
-    hipEvent_t turn = nullptr;     // recorded behind a run with clusters,
+    hipEvent_t turn = nullptr;     // recorded behind a run with clusters or one that joined a chain,
     bool bare = false;             // unless the context was alone: not since it last was in flight
-    uint32_t issued = 0;           // cluster launches and marks that will count HOST_ENDED up
-    uint32_t aborts_seen = 0;
+    uint32_t issued = 0;           // cluster launches and marks that will count HOST_ENDED up;
+    uint32_t cluster_until = 0;    // the last one of clusters,
+    uint32_t chain_until = 0;      // of the chain or the persistent kernel by its own choice,
+    uint32_t joined_until = 0;     // and because another context's chain was in flight
+    bool unmarked = false;         // a chain that is not counted is in flight
     int members = 0;               // cluster workgroups of the launches in flight, at most
-    bool chain = false;            // the chain or the persistent kernel is in flight,
-    bool unmarked = false;         // and not counted in `issued`
+    uint32_t aborts_seen = 0;
     bool chain_if_met = false;     // its last run with clusters would rather be a chain beside another context's
     int apart = 0;                 // runs that keep to the chain
     uint64_t cluster_runs = 0, chain_runs = 0;
@@ -1594,7 +1596,9 @@ static hipError_t enqueue_resident(islf_ctx *c, uint32_t n)
 //  - Cluster launches that do not all find a CU each beside those that others
 //    have in flight are ordered behind them.
 //  - A run of the chain is ordered behind the clusters that others have in flight.
-//  - While another context has a chain in flight, a run takes the chain too.
+//  - While another context has a chain in flight, a run joins it: takes the
+//    chain too.  Runs that joined are no reason to join (contexts would keep
+//    each other on the chain): clusters are ordered behind them.
 //  - Where chains side by side are the faster form (see prefers_chain),
 //    contexts that met keep to the chain for kApartRuns runs; so does a context
 //    with a launch that the census called off (work of another process or of
@@ -1620,13 +1624,17 @@ static Turns &turns(const islf_ctx *c)
     return t[c->device % kMaxDevices];
 }
 
-static bool in_flight(islf_ctx *o)
+static bool ahead(const islf_ctx *o, uint32_t until)
 {
-    const uint32_t ended = (uint32_t)__atomic_load_n(o->h_res + HOST_ENDED, __ATOMIC_RELAXED);
-    if (o->unmarked || (int32_t)(o->issued - ended) > 0) return true;
-    o->members = 0;
-    o->chain = false;
-    return false;
+    return (int32_t)(until - (uint32_t)__atomic_load_n(o->h_res + HOST_ENDED, __ATOMIC_RELAXED)) > 0;
+}
+
+static bool chain_in_flight(const islf_ctx *o) { return o->unmarked || ahead(o, o->chain_until); }
+
+static int members_in_flight(islf_ctx *o)
+{
+    if (!ahead(o, o->cluster_until)) o->members = 0;
+    return o->members;
 }
 
 // A context that was alone recorded no events (each costs a run 3 us: five runs
@@ -1643,8 +1651,8 @@ static void join_turns(islf_ctx *c)
         busy = false;
         {
             std::lock_guard<std::mutex> lock(turns(c).m);
-            for (islf_ctx *o : turns(c).all) 
-                busy = busy || (o != c && o->stream != c->stream && o->members && o->bare && in_flight(o));
+            for (islf_ctx *o : turns(c).all)
+                busy = busy || (o != c && o->stream != c->stream && o->bare && members_in_flight(o));
         }
         if (busy) std::this_thread::yield();
     }
@@ -1655,7 +1663,8 @@ static void landed(islf_ctx *c)
 {
     std::lock_guard<std::mutex> lock(turns(c).m);
     c->issued = (uint32_t)__atomic_load_n(c->h_res + HOST_ENDED, __ATOMIC_RELAXED);
-    c->unmarked = c->chain = false;
+    c->cluster_until = c->chain_until = c->joined_until = c->issued;
+    c->unmarked = false;
     c->members = 0;
 }
 
@@ -1665,59 +1674,74 @@ static bool being_captured(const islf_ctx *c)
     return c->stream && hipStreamIsCapturing(c->stream, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
 }
 
-// Whether clusters of `members` workgroups may be enqueued now (lock held), put
-// behind those of others where need be.
-static bool clusters_may_go(islf_ctx *c, int members, bool chain_if_met, hipError_t *e)
+enum Turn { TURN_GO, TURN_CHAIN, TURN_JOIN };
+
+// What a run with clusters of `members` workgroups does now (lock held): goes,
+// put behind those of others where need be, or is a chain, or joins one.
+static Turn take_turn(islf_ctx *c, int members, bool chain_if_met, hipError_t *e)
 {
     const uint32_t aborts = (uint32_t)__atomic_load_n(c->h_res + HOST_ABORTS, __ATOMIC_RELAXED);
     if (aborts != c->aborts_seen) c->apart = kApartRuns;
     c->aborts_seen = aborts;
     bool chain = false;
     int sum = members;
-    std::vector<islf_ctx *> others;
+    std::vector<islf_ctx *> clusters, joined;
     for (islf_ctx *o : turns(c).all) {
-        if (o == c || o->stream == c->stream || !in_flight(o)) continue;
-        chain = chain || o->chain;
-        sum += o->members;
-        if (o->members) others.push_back(o);
+        if (o == c || o->stream == c->stream) continue;
+        chain = chain || chain_in_flight(o);
+        sum += members_in_flight(o);
+        if (o->members) clusters.push_back(o);
+        if (ahead(o, o->joined_until)) joined.push_back(o);
     }
     const bool full = sum > c->num_cu;
-    if (chain_if_met && (full || chain)) {
+    if (chain_if_met && (full || chain || !joined.empty())) {
         c->apart = kApartRuns;
-        for (islf_ctx *o : others)
+        for (islf_ctx *o : clusters)
             if (o->chain_if_met) o->apart = kApartRuns;
     }
     c->chain_if_met = chain_if_met;
     if (c->apart > 0) {
         --c->apart;
-        return false;
+        return TURN_CHAIN;
     }
-    if (chain) return false;
-    for (islf_ctx *o : others)
-        if (full && o->turn && *e == hipSuccess) *e = hipStreamWaitEvent(c->stream, o->turn, 0);
-    return true;
+    if (chain) return TURN_JOIN;
+    if (!full) clusters.clear();
+    clusters.insert(clusters.end(), joined.begin(), joined.end());
+    for (islf_ctx *o : clusters)
+        if (o->turn && *e == hipSuccess) *e = hipStreamWaitEvent(c->stream, o->turn, 0);
+    return TURN_GO;
+}
+
+static hipError_t record_turn(islf_ctx *c)
+{
+    // (contexts share no data: the event orders launches and needs no fence)
+    hipError_t e = hipSuccess;
+    if (!c->turn) e = hipEventCreateWithFlags(&c->turn, hipEventDisableTiming | hipEventDisableSystemFence);
+    return e == hipSuccess ? hipEventRecord(c->turn, c->stream) : e;
 }
 
 // Puts a run of the chain behind the clusters that others have in flight and
 // counts it as in flight; end_chain marks its end where somebody may look.
-static hipError_t start_chain(islf_ctx *c, bool *mark)
+static hipError_t start_chain(islf_ctx *c, bool joins, bool *mark)
 {
     std::lock_guard<std::mutex> lock(turns(c).m);
     hipError_t e = hipSuccess;
     for (islf_ctx *o : turns(c).all)
-        if (e == hipSuccess && o != c && o->stream != c->stream && in_flight(o) && o->members && o->turn)
+        if (e == hipSuccess && o != c && o->stream != c->stream && members_in_flight(o) && o->turn)
             e = hipStreamWaitEvent(c->stream, o->turn, 0);
     *mark = turns(c).all.size() > 1;
-    if (*mark) c->issued += 1;
+    if (*mark) (joins ? c->joined_until : c->chain_until) = ++c->issued;
     c->unmarked = !*mark;   // (a mark ends what came before it, too)
-    c->chain = true;
     c->chain_runs += 1;
     return e;
 }
 
-static hipError_t end_chain(islf_ctx *c, bool mark)
+static hipError_t end_chain(islf_ctx *c, bool joins, bool mark)
 {
-    return mark ? launch_mark(c->d_rsy, c->h_res, c->stream) : hipSuccess;
+    const hipError_t e = mark ? launch_mark(c->d_rsy, c->h_res, c->stream) : hipSuccess;
+    if (e != hipSuccess || !joins) return e;
+    std::lock_guard<std::mutex> lock(turns(c).m);
+    return record_turn(c);
 }
 
 // Acts on the error word, fetched to h_res.  A raised word means a launch gave
@@ -2380,40 +2404,37 @@ static bool prefers_chain(const islf_ctx *c)
 
 // A run of the chain, in its turn.
 template <class ENQUEUE>
-static islf_status run_chain(islf_ctx *c, ENQUEUE enqueue)
+static islf_status run_chain(islf_ctx *c, bool joins, ENQUEUE enqueue)
 {
     bool mark = false;
-    HIP_TRY(start_chain(c, &mark));
+    HIP_TRY(start_chain(c, joins, &mark));
     const islf_status st = enqueue();
     if (st != ISLF_OK) return st;
-    HIP_TRY(end_chain(c, mark));
+    HIP_TRY(end_chain(c, joins, mark));
     return ISLF_OK;
 }
 
-// A resident run, in its turn: *done = false if it may not go now.
+// A resident run, in its turn; enqueued if that is TURN_GO.
 template <class ENQUEUE>
-static islf_status run_resident(islf_ctx *c, uint32_t launches, int members, bool chain_if_met, bool *done,
+static islf_status run_resident(islf_ctx *c, uint32_t launches, int members, bool chain_if_met, Turn *turn,
                                 ENQUEUE enqueue)
 {
-    *done = true;
+    *turn = TURN_GO;
     if (!members) return enqueue();   // waits for nobody, and nobody has to wait for it
     std::lock_guard<std::mutex> lock(turns(c).m);
     hipError_t e = hipSuccess;
-    *done = clusters_may_go(c, members, chain_if_met, &e);
+    *turn = take_turn(c, members, chain_if_met, &e);
     HIP_TRY(e);
-    if (!*done) return ISLF_OK;
-    (void)in_flight(c);   // forgets what has ended
+    if (*turn != TURN_GO) return ISLF_OK;
+    c->members = std::max(members_in_flight(c), members);
     c->issued += launches;
-    c->unmarked = false;
+    c->cluster_until = c->issued;
+    c->unmarked = false;   // (these end what came before them, too)
     const islf_status st = enqueue();
     if (st != ISLF_OK) return st;
-    c->members = std::max(c->members, members);
     c->cluster_runs += 1;
     c->bare = turns(c).all.size() == 1;
-    if (c->bare) return ISLF_OK;
-    // (contexts share no data: the event orders launches and needs no fence)
-    if (!c->turn) HIP_TRY(hipEventCreateWithFlags(&c->turn, hipEventDisableTiming | hipEventDisableSystemFence));
-    HIP_TRY(hipEventRecord(c->turn, c->stream));
+    if (!c->bare) HIP_TRY(record_turn(c));
     return ISLF_OK;
 }
 
@@ -2421,18 +2442,18 @@ static islf_status run_form(islf_ctx *c, uint32_t n, bool resident)
 {
     if (n == 0 || c->live.empty()) return ISLF_OK;
     if (being_captured(c)) return enqueue_form(c, n, resident);
+    Turn turn = TURN_CHAIN;
     if (resident) {
         uint32_t launches;
         int members;
-        bool done = false;
         resident_size(c, n, &launches, &members);
-        islf_status st = run_resident(c, launches, members, prefers_chain(c), &done,
+        islf_status st = run_resident(c, launches, members, prefers_chain(c), &turn,
                                       [&] { return enqueue_form(c, n, true); });
-        if (st != ISLF_OK || done) return st;
+        if (st != ISLF_OK || turn == TURN_GO) return st;
         st = prepare_plans(c, c->exec);
         if (st != ISLF_OK) return st;
     }
-    return run_chain(c, [&] { return enqueue_sweeps(c, n); });
+    return run_chain(c, turn == TURN_JOIN, [&] { return enqueue_sweeps(c, n); });
 }
 
 static islf_status check_none_failed(const islf_ctx *c)
@@ -2877,16 +2898,16 @@ static islf_status launch_graphs(islf_ctx *c, uint32_t n)
 static islf_status run_graphs(islf_ctx *c, uint32_t n)
 {
     if (being_captured(c)) return launch_graphs(c, n);
-    if (!c->graph_resident) return run_chain(c, [&] { return launch_graphs(c, n); });
-    bool done = false;
-    islf_status st = run_resident(c, c->graph_launches * n, c->graph_members, c->graph_prefers_chain, &done,
+    if (!c->graph_resident) return run_chain(c, false, [&] { return launch_graphs(c, n); });
+    Turn turn = TURN_GO;
+    islf_status st = run_resident(c, c->graph_launches * n, c->graph_members, c->graph_prefers_chain, &turn,
                                   [&] { return launch_graphs(c, n); });
-    if (st != ISLF_OK || done) return st;
+    if (st != ISLF_OK || turn == TURN_GO) return st;
     const int now = c->exec;
     c->exec = c->graph_exec;
     st = prepare_plans(c, c->exec);
     if (st == ISLF_OK)
-        st = run_chain(c, [&] {
+        st = run_chain(c, turn == TURN_JOIN, [&] {
             islf_status s = ISLF_OK;
             for (uint32_t i = 0; i < n && s == ISLF_OK; ++i) s = enqueue_sweeps(c, c->graph_sweeps);
             return s;
@@ -3004,7 +3025,7 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
     islf_status st = sync_tables(ctx);
     if (st != ISLF_OK) return st;
     bool mark = false;
-    HIP_TRY(start_chain(ctx, &mark));   // (its trials are in flight to the end)
+    HIP_TRY(start_chain(ctx, false, &mark));   // (its trials are in flight to the end)
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     // size classes: replicas of one shape share a variant
     std::vector<std::vector<int>> classes;
@@ -3318,9 +3339,9 @@ extern "C" islf_status islf_phase_timings(islf_ctx *ctx, uint32_t n_sweeps, doub
             return fail(ISLF_EDEVICE, "cannot create events");
         }
     bool mark = false;
-    hipError_t err = start_chain(ctx, &mark);
+    hipError_t err = start_chain(ctx, false, &mark);
     if (err == hipSuccess && nl) err = enqueue_plan(ctx, ctx->batched, ctx->d_live, nl, n_sweeps, ev.data());
-    if (err == hipSuccess) err = end_chain(ctx, mark);
+    if (err == hipSuccess) err = end_chain(ctx, false, mark);
     if (err == hipSuccess) err = hipStreamSynchronize(ctx->stream);
     if (err == hipSuccess) landed(ctx);
     double sum[3] = {0, 0, 0};

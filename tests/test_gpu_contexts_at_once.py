@@ -148,6 +148,30 @@ def test_replays_that_meet(mode):
         assert all(runs(c)["aborts"] == 0 for c in (other, big, a))
 
 
+def test_runs_that_joined_a_chain_do_not_keep_others_on_it():
+    with context([film(BIG)], islf.INT8) as a, context([film(BIG, 1)], islf.INT8) as b:
+        assert islf.lib().islf_testing_abort_resident(a._h) == islf.OK
+        a.sweep(10)                    # called off: a keeps to the chain for 256 runs
+        a.sweep_count(0)
+        for _ in range(255):
+            a.sweep(10)
+        assert runs(a) == dict(cluster=1, chain=255, aborts=1, apart=1)
+        a.sweep(300)                   # the last of them, 7 ms
+        b.sweep(1500)                  # joins it: 36 ms on the chain
+        assert runs(b) == dict(cluster=0, chain=1, aborts=0, apart=0)
+        a.sweep(20)                    # behind b's run, resident again
+        assert runs(a) == dict(cluster=2, chain=256, aborts=1, apart=0)
+        n = a.sweep_count(0)
+        assert n == 2880 and b.sweep_count(0) == 1500
+        b.sweep(20)
+        assert runs(b)["cluster"] == 1
+        got = a.measure(0, n - 60, 60), a.get_spins(0)
+    with context([film(BIG)], islf.INT8) as c:
+        c.set_groups(1)
+        c.sweep(n)
+        assert np.array_equal(got[0], c.measure(0, n - 60, 60)) and np.array_equal(got[1], c.get_spins(0))
+
+
 def test_a_called_off_launch_keeps_to_the_chain():
     with context([film((24, 130, 140))]) as a:
         a.sweep(6)
