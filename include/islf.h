@@ -84,9 +84,10 @@ typedef enum { ISLF_INIT_RANDOM = 0, ISLF_INIT_UP = 1, ISLF_INIT_DOWN = 2, ISLF_
  * launches of films that need several CUs each are ordered behind each other
  * where the device cannot hold them side by side, launches of the forms
  * above behind them, and a run that finds another context's launches of the
- * forms above in flight takes those forms too.  islf_create waits for the
- * resident launches of a context that had the device to itself.  Sweeps that
- * a caller records into a graph of its own are not ordered so; beside work
+ * forms above in flight takes those forms too.  (A run that meets such
+ * launches on a stream on which their caller is just recording a graph of its
+ * own waits for them on the host.)  Sweeps that a caller records into a graph
+ * of its own are not ordered so; beside work
  * that holds CUs they (as all resident launches beside another process's
  * work) may wait up to a tenth of a second for their CUs and then run slowly,
  * with the same results. */

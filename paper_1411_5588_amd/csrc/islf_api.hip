@@ -313,8 +313,7 @@ struct islf_ctx {
     ResSync *d_rsy = nullptr;
     // turns among the contexts of a device (see Turns; under its lock)
     int device = 0;
-    hipEvent_t turn = nullptr;     // recorded behind a run with clusters or one that joined a chain,
-    bool bare = false;             // unless the context was alone: not since it last was in flight
+    hipEvent_t turn = nullptr;     // recorded on its stream by a context that is to come behind it
     uint32_t issued = 0;           // cluster launches and marks that will count HOST_ENDED up;
     uint32_t cluster_until = 0;    // the last one of clusters,
     uint32_t chain_until = 0;      // of the chain or the persistent kernel by its own choice,
@@ -1637,27 +1636,6 @@ static int members_in_flight(islf_ctx *o)
     return o->members;
 }
 
-// A context that was alone recorded no events (each costs a run 3 us: five runs
-// of 10 sweeps of a 184x504x504 film take 1,485 instead of 1,467 us): a new one
-// waits for its clusters here, where creation waits for the device anyway.
-static void join_turns(islf_ctx *c)
-{
-    {
-        std::lock_guard<std::mutex> lock(turns(c).m);
-        turns(c).all.push_back(c);
-    }
-    const auto give_up = std::chrono::steady_clock::now() + std::chrono::seconds(60);
-    for (bool busy = true; busy && std::chrono::steady_clock::now() < give_up;) {
-        busy = false;
-        {
-            std::lock_guard<std::mutex> lock(turns(c).m);
-            for (islf_ctx *o : turns(c).all)
-                busy = busy || (o != c && o->stream != c->stream && o->bare && members_in_flight(o));
-        }
-        if (busy) std::this_thread::yield();
-    }
-}
-
 // After the host has waited for the context's stream.
 static void landed(islf_ctx *c)
 {
@@ -1672,6 +1650,26 @@ static bool being_captured(const islf_ctx *c)
 {
     hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
     return c->stream && hipStreamIsCapturing(c->stream, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
+}
+
+// Puts what c enqueues next behind what o has in flight (lock held).  The event
+// is recorded here, on o's stream, and not by o behind each of its runs, which
+// cost a run 3 us (five of 10 sweeps of a 184x504x504 film: 1,485 instead of
+// 1,465 us).  While o's caller captures a graph of its own on that stream no event
+// can be recorded there, and c waits here.  (islf_graph_capture holds the lock.)
+static hipError_t order_behind(islf_ctx *c, islf_ctx *o)
+{
+    // (contexts share no data: the event orders launches and needs no fence)
+    hipError_t e = hipSuccess;
+    if (!o->turn) e = hipEventCreateWithFlags(&o->turn, hipEventDisableTiming | hipEventDisableSystemFence);
+    if (e != hipSuccess) return e;
+    if (!being_captured(o) && hipEventRecord(o->turn, o->stream) == hipSuccess && !being_captured(o))
+        return hipStreamWaitEvent(c->stream, o->turn, 0);
+    (void)hipGetLastError();
+    const auto give_up = std::chrono::steady_clock::now() + std::chrono::seconds(60);
+    while ((members_in_flight(o) || ahead(o, o->joined_until)) && std::chrono::steady_clock::now() < give_up)
+        std::this_thread::yield();
+    return hipSuccess;
 }
 
 enum Turn { TURN_GO, TURN_CHAIN, TURN_JOIN };
@@ -1708,27 +1706,18 @@ static Turn take_turn(islf_ctx *c, int members, bool chain_if_met, hipError_t *e
     if (!full) clusters.clear();
     clusters.insert(clusters.end(), joined.begin(), joined.end());
     for (islf_ctx *o : clusters)
-        if (o->turn && *e == hipSuccess) *e = hipStreamWaitEvent(c->stream, o->turn, 0);
+        if (*e == hipSuccess) *e = order_behind(c, o);
     return TURN_GO;
 }
 
-static hipError_t record_turn(islf_ctx *c)
-{
-    // (contexts share no data: the event orders launches and needs no fence)
-    hipError_t e = hipSuccess;
-    if (!c->turn) e = hipEventCreateWithFlags(&c->turn, hipEventDisableTiming | hipEventDisableSystemFence);
-    return e == hipSuccess ? hipEventRecord(c->turn, c->stream) : e;
-}
-
 // Puts a run of the chain behind the clusters that others have in flight and
-// counts it as in flight; end_chain marks its end where somebody may look.
+// counts it as in flight (lock held); end_chain marks its end where somebody
+// may look.
 static hipError_t start_chain(islf_ctx *c, bool joins, bool *mark)
 {
-    std::lock_guard<std::mutex> lock(turns(c).m);
     hipError_t e = hipSuccess;
     for (islf_ctx *o : turns(c).all)
-        if (e == hipSuccess && o != c && o->stream != c->stream && members_in_flight(o) && o->turn)
-            e = hipStreamWaitEvent(c->stream, o->turn, 0);
+        if (e == hipSuccess && o != c && o->stream != c->stream && members_in_flight(o)) e = order_behind(c, o);
     *mark = turns(c).all.size() > 1;
     if (*mark) (joins ? c->joined_until : c->chain_until) = ++c->issued;
     c->unmarked = !*mark;   // (a mark ends what came before it, too)
@@ -1736,12 +1725,9 @@ static hipError_t start_chain(islf_ctx *c, bool joins, bool *mark)
     return e;
 }
 
-static hipError_t end_chain(islf_ctx *c, bool joins, bool mark)
+static hipError_t end_chain(islf_ctx *c, bool mark)
 {
-    const hipError_t e = mark ? launch_mark(c->d_rsy, c->h_res, c->stream) : hipSuccess;
-    if (e != hipSuccess || !joins) return e;
-    std::lock_guard<std::mutex> lock(turns(c).m);
-    return record_turn(c);
+    return mark ? launch_mark(c->d_rsy, c->h_res, c->stream) : hipSuccess;
 }
 
 // Acts on the error word, fetched to h_res.  A raised word means a launch gave
@@ -1994,7 +1980,10 @@ extern "C" islf_status islf_create_with_allocator(const islf_replica_desc *reps,
         g_err = keep;
         return st;
     }
-    join_turns(c);
+    {
+        std::lock_guard<std::mutex> lock(turns(c).m);
+        turns(c).all.push_back(c);
+    }
     *out = c;
     return ISLF_OK;
 }
@@ -2406,11 +2395,14 @@ static bool prefers_chain(const islf_ctx *c)
 template <class ENQUEUE>
 static islf_status run_chain(islf_ctx *c, bool joins, ENQUEUE enqueue)
 {
+    std::unique_lock<std::mutex> lock(turns(c).m);
     bool mark = false;
     HIP_TRY(start_chain(c, joins, &mark));
+    // (clusters are ordered behind runs that joined, by an event behind all of them; nobody goes beside the others)
+    if (!joins) lock.unlock();
     const islf_status st = enqueue();
     if (st != ISLF_OK) return st;
-    HIP_TRY(end_chain(c, joins, mark));
+    HIP_TRY(end_chain(c, mark));
     return ISLF_OK;
 }
 
@@ -2433,8 +2425,6 @@ static islf_status run_resident(islf_ctx *c, uint32_t launches, int members, boo
     const islf_status st = enqueue();
     if (st != ISLF_OK) return st;
     c->cluster_runs += 1;
-    c->bare = turns(c).all.size() == 1;
-    if (!c->bare) HIP_TRY(record_turn(c));
     return ISLF_OK;
 }
 
@@ -2848,12 +2838,15 @@ extern "C" islf_status islf_graph_capture(islf_ctx *ctx, uint32_t k_sweeps)
     const int G = grouped ? num_groups(ctx) : 1;
     for (int gi = 0; gi < G; ++gi) {
         hipStream_t sg = group_stream(ctx, gi, G);
+        // (another context may record an event on the stream: not while it is captured)
+        std::unique_lock<std::mutex> lock(turns(ctx).m);
         HIP_TRY(hipStreamBeginCapture(sg, hipStreamCaptureModeThreadLocal));
         hipError_t ee = hipSuccess;
         if (grouped) ee = enqueue_group(ctx, gi, k_sweeps);
         else st = enqueue_form(ctx, k_sweeps, resident);
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(sg, &g);
+        lock.unlock();
         if (st != ISLF_OK || ee != hipSuccess) {
             if (g) (void)hipGraphDestroy(g);
             destroy_graphs(ctx);
@@ -3025,7 +3018,10 @@ extern "C" islf_status islf_autotune(islf_ctx *ctx, uint32_t sweeps)
     islf_status st = sync_tables(ctx);
     if (st != ISLF_OK) return st;
     bool mark = false;
-    HIP_TRY(start_chain(ctx, false, &mark));   // (its trials are in flight to the end)
+    {
+        std::lock_guard<std::mutex> lock(turns(ctx).m);
+        HIP_TRY(start_chain(ctx, false, &mark));   // (its trials are in flight to the end)
+    }
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     // size classes: replicas of one shape share a variant
     std::vector<std::vector<int>> classes;
@@ -3339,9 +3335,13 @@ extern "C" islf_status islf_phase_timings(islf_ctx *ctx, uint32_t n_sweeps, doub
             return fail(ISLF_EDEVICE, "cannot create events");
         }
     bool mark = false;
-    hipError_t err = start_chain(ctx, false, &mark);
+    hipError_t err;
+    {
+        std::lock_guard<std::mutex> lock(turns(ctx).m);
+        err = start_chain(ctx, false, &mark);
+    }
     if (err == hipSuccess && nl) err = enqueue_plan(ctx, ctx->batched, ctx->d_live, nl, n_sweeps, ev.data());
-    if (err == hipSuccess) err = end_chain(ctx, false, mark);
+    if (err == hipSuccess) err = end_chain(ctx, mark);
     if (err == hipSuccess) err = hipStreamSynchronize(ctx->stream);
     if (err == hipSuccess) landed(ctx);
     double sum[3] = {0, 0, 0};

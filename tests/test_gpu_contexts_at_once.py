@@ -7,7 +7,6 @@ share.  No launch is called off, and the chains are the same as alone.
 """
 import ctypes as C
 import threading
-import time
 
 import numpy as np
 import pytest
@@ -75,19 +74,45 @@ def test_a_new_context_comes_behind_the_clusters_of_one_that_was_alone():
     with context([film(BIG)], islf.INT8) as a:
         a.sweep(2000)
         with context([film(BIG, 1)], islf.INT8) as b:
-            # a had 32 ms of work and no event of its own to be ordered behind; the runtime notices the end of a
-            # stream's last kernel some time after a query
-            done = False
-            for _ in range(4):
-                done = done or a.stream.query()
-                time.sleep(0.001)
-            assert done
             b.sweep(500)
             a.sweep(20)
             b.sweep(20)
             assert a.sweep_count(0) == 2020 and b.sweep_count(0) == 520
             for c in (a, b):
                 assert runs(c) == dict(cluster=2, chain=0, aborts=0, apart=0)
+
+
+@pytest.mark.parametrize("mode", ["thread_local", "relaxed"])
+def test_meeting_a_stream_that_its_caller_captures(mode):
+    # no event can be recorded there: the run waits on the host, and the caller's graph is what it recorded
+    x = torch.zeros(64, device="cuda")
+    with context([film(BIG)], islf.INT8) as a, context([film(BIG, 1)], islf.INT8) as b:
+        b.sweep(20)
+        a.sweep(20)
+        b.sweep_count(0)
+        a.sweep_count(0)
+        g = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        a.sweep(1500)
+        with torch.cuda.stream(a.stream):
+            g.capture_begin(capture_error_mode=mode)
+            x.add_(1.0)
+            b.sweep(20)
+            x.add_(1.0)
+            g.capture_end()
+        for k in range(3):
+            g.replay()
+            b.sweep(20)
+        torch.cuda.synchronize()
+        assert (x == 6.0).all()
+        assert a.sweep_count(0) == 1520 and b.sweep_count(0) == 100
+        assert runs(a) == dict(cluster=2, chain=0, aborts=0, apart=0)
+        assert runs(b) == dict(cluster=5, chain=0, aborts=0, apart=0)
+        got = b.measure(0, 40, 60), b.get_spins(0)
+    with context([film(BIG, 1)], islf.INT8) as c:
+        c.set_groups(1)
+        c.sweep(100)
+        assert np.array_equal(got[0], c.measure(0, 40, 60)) and np.array_equal(got[1], c.get_spins(0))
 
 
 def test_clusters_meet_a_chain():
